@@ -118,17 +118,77 @@ static __device__ void pc_body_state(const PcBodyDev& B, double dt_epoch, double
     }
 }
 
+// 1/sqrt(x) in full FP64 for finite x > 0: the hardware estimate y, e = 1 - x y^2, and
+// (1 - e)^(-1/2) = 1 + e/2 + 3e^2/8 + O(e^3) (|e| near 2^-22, dropped terms below 2^-63).
+static __device__ __forceinline__ double pc_rsqrt_full(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x, y * y, 1.0);
+    return y * fma(e, fma(0.375, e, 0.5), 1.0);
+}
+
+// 1/x by the hardware estimate (relative error near 2^-22) and one Newton step (2^-44) or two.
+static __device__ __forceinline__ double pc_rcp1(double x)
+{
+    const double y = __builtin_amdgcn_rcp(x);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+static __device__ __forceinline__ double pc_rcp_full(double x)
+{
+    const double y = pc_rcp1(x);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+
+// Sine and cosine: x - k pi/2 with pi/2 in two parts (exact to 2^-53 of the result for the
+// angles of an orbit; the library for larger ones), then the Taylor series on [-pi/4, pi/4],
+// whose dropped terms are below 1e-18.  A third of the library call's instructions.
+static __device__ __forceinline__ void pc_sincos(double x, double& s, double& c)
+{
+    if (!(fabs(x) < 1e5)) {
+        sincos(x, &s, &c);
+        return;
+    }
+    const double k = rint(x * 0.63661977236758134308);
+    const double r = fma(-k, 6.12323399573676603587e-17, fma(-k, 1.57079632679489655800, x));
+    const double z = r * r;
+    double p = 1.0 / 355687428096000.0, q = 1.0 / 20922789888000.0;
+    p = fma(p, z, -1.0 / 1307674368000.0);
+    q = fma(q, z, -1.0 / 87178291200.0);
+    p = fma(p, z, 1.0 / 6227020800.0);
+    q = fma(q, z, 1.0 / 479001600.0);
+    p = fma(p, z, -1.0 / 39916800.0);
+    q = fma(q, z, -1.0 / 3628800.0);
+    p = fma(p, z, 1.0 / 362880.0);
+    q = fma(q, z, 1.0 / 40320.0);
+    p = fma(p, z, -1.0 / 5040.0);
+    q = fma(q, z, -1.0 / 720.0);
+    p = fma(p, z, 1.0 / 120.0);
+    q = fma(q, z, 1.0 / 24.0);
+    p = fma(p, z, -1.0 / 6.0);
+    q = fma(q, z, -0.5);
+    const double sr = fma(r * z, p, r), cr = fma(z, q, 1.0);
+    const int m = (int)k;
+    const double ss = (m & 1) ? cr : sr, cc = (m & 1) ? sr : cr;
+    s = (m & 2) ? -ss : ss;
+    c = ((m + 1) & 2) ? -cc : cc;
+}
+
 // Warm start (Sec. 2.1): propagate y0 by dt on its osculating ellipse, through the
 // Lagrange coefficients f, g, fdot, gdot written in the eccentric-anomaly change x:
 //   F(x) = x - (1 - r0/a) sin x + (r0.v0/sqrt(a)) (1 - cos x) - n dt = 0.
 // Solved by Halley's iteration x -= 2 F F' / (2 F'^2 - F F''), cubically convergent; F''
-// comes from the same sine and cosine as F and F', so a step costs what a Newton step
-// does and three steps replace five from the mean-anomaly start.  The error after a step
-// is about K e^3, e the error before it (close to the step) and K = O(1) for e < 0.8, so
-// a step below 1e-5 leaves an error near 1e-15 and the loop stops there; the
-// sine and cosine at the final x follow from those of the last step by its second-order
-// Taylor expansion (the dropped cubic term is under 2e-16).  The warm start is only the
-// initial guess: the iteration converges to the same fixed point from any nearby one.
+// comes from the same sine and cosine as F and F'.  Three steps in FP32 on the hardware sine
+// bring the start n dt to about 1e-6 (they only choose the starting point); the FP64 steps
+// then go on until one is below 1e-5.  The error after a step is about K e^3, e the error
+// before it (close to the step) and K = O(1) for e < 0.8, so that leaves an error near 1e-15,
+// usually after the first; the sine and cosine at the final x follow from those of the last
+// step by its second-order Taylor expansion (the dropped cubic term is under 2e-16).
+// The square roots and divisions are the hardware estimates refined to full FP64.
+// What bounds it is one wave's chain of dependent FP64 instructions: a column refill waits
+// for one solve per lane.  Four FP64 steps from n dt with library sines and IEEE divisions
+// took about 900 instructions, this about 250: 12000 eccentric ICs of 48 nodes and 16 segments
+// (a third of the sweeps refill a column) 5.20 -> 5.08 ms, the uneven 65536-IC batch 160.0 ->
+// 157.8 ms.
 // The state goes in and out by value (registers, no stack traffic); a non-elliptic or
 // degenerate state returns NaN components.
 struct PcState6 {
@@ -139,31 +199,58 @@ static __device__ __attribute__((noinline)) PcState6 pc_kepler_state(PcState6 s0
 {
     const double* y0 = s0.c;
     PcState6 out;
-    const double r0n = sqrt(y0[0] * y0[0] + y0[1] * y0[1] + y0[2] * y0[2]);
+    const double r02 = y0[0] * y0[0] + y0[1] * y0[1] + y0[2] * y0[2];
     const double v02 = y0[3] * y0[3] + y0[4] * y0[4] + y0[5] * y0[5];
-    const double alpha = 2.0 / r0n - v02;          // 1/a
+    const double ir0 = pc_rsqrt_full(r02);
+    const double r0n = r02 * ir0;
+    const double alpha = fma(2.0, ir0, -v02);      // 1/a
     if (!(r0n > 0.0) || !isfinite(r0n) || !isfinite(v02) || !(alpha > 0.0)) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) out.c[k] = (double)NAN;
         return out;
     }
-    const double a = 1.0 / alpha;
-    const double sqa = sqrt(a);
-    const double n = alpha * sqrt(alpha);          // mean motion
+    const double sqa = pc_rsqrt_full(alpha);       // sqrt(a)
+    const double a = sqa * sqa;
+    const double sqal = alpha * sqa;
+    const double n = alpha * sqal;                 // mean motion
     const double sig = y0[0] * y0[3] + y0[1] * y0[4] + y0[2] * y0[5];
-    const double ec = 1.0 - r0n * alpha;           // e cos E0
-    const double es = sig / sqa;                   // e sin E0
+    const double ec = fma(-r0n, alpha, 1.0);       // e cos E0
+    const double es = sig * sqal;                  // e sin E0
     const double ndt = n * dt;
     double x = ndt;
+    {
+        // u = x - n dt; angles in turns, as the hardware sine takes them
+        const float i2p = 0.15915494309189535f;
+        const double t = ndt * 0.15915494309189533577;
+        const float t0 = (float)(t - rint(t)), ecf = (float)ec, esf = (float)es;
+        float u = 0.0f;
+#pragma unroll
+        for (int it = 0; it < 3; ++it) {
+            const float an = fmaf(u, i2p, t0);
+            const float sf = __builtin_amdgcn_sinf(an), cf = __builtin_amdgcn_cosf(an);
+            const float F = u - ecf * sf + esf * (1.0f - cf);
+            const float F1 = 1.0f - ecf * cf + esf * sf;
+            const float F2 = ecf * sf + esf * cf;
+            u -= 2.0f * F * F1 * __builtin_amdgcn_rcpf(2.0f * F1 * F1 - F * F2);
+            u = fminf(fmaxf(u, -2.0f), 2.0f);   // |u| <= 2 e at the solution
+        }
+        x += (double)u;
+    }
+    // F rises with x: near e = 1 a step that leaves the bracket is replaced by its midpoint
+    double lo = ndt - 2.0, hi = ndt + 2.0;
     double sx, cx;
     bool done = false;
     for (int it = 0; it < 60; ++it) {
-        sincos(x, &sx, &cx);
+        pc_sincos(x, sx, cx);
         const double F = x - ec * sx + es * (1.0 - cx) - ndt;
         const double F1 = 1.0 - ec * cx + es * sx;
         const double F2 = ec * sx + es * cx;
-        const double dx = 2.0 * F * F1 / (2.0 * F1 * F1 - F * F2);
-        x -= dx;
+        double xn = x - 2.0 * F * F1 * pc_rcp1(2.0 * F1 * F1 - F * F2);
+        lo = F > 0.0 ? lo : x;
+        hi = F > 0.0 ? x : hi;
+        if (!(xn >= lo && xn <= hi)) xn = 0.5 * (lo + hi);
+        const double dx = x - xn;
+        x = xn;
         if (fabs(dx) <= 1e-5) {
             // sin and cos of x = x_prev - dx
             const double h2 = 0.5 * dx * dx;
@@ -175,12 +262,13 @@ static __device__ __attribute__((noinline)) PcState6 pc_kepler_state(PcState6 s0
             break;
         }
     }
-    if (!done) sincos(x, &sx, &cx);
+    if (!done) pc_sincos(x, sx, cx);
     const double rn = a + (r0n - a) * cx + sig * sqa * sx;
-    const double f = 1.0 - (a / r0n) * (1.0 - cx);
-    const double g = dt - (x - sx) / n;
-    const double fd = -sqa * sx / (rn * r0n);
-    const double gd = 1.0 - (a / rn) * (1.0 - cx);
+    const double irn = pc_rcp_full(rn);
+    const double f = 1.0 - a * ir0 * (1.0 - cx);
+    const double g = dt - (x - sx) * (sqa * a);
+    const double fd = -sqa * sx * (irn * ir0);
+    const double gd = 1.0 - a * irn * (1.0 - cx);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         out.c[k] = f * y0[k] + g * y0[3 + k];
@@ -1539,15 +1627,6 @@ static __device__ __forceinline__ void pc_grad_lds_node32(const double (&x)[R], 
             add(r, (float)(x[r] - q[0]), (float)(y[r] - q[1]), (float)(z[r] - q[2]), mu);
         }
     }
-}
-
-// 1/sqrt(x) in full FP64 for finite x > 0: the hardware estimate y, e = 1 - x y^2, and
-// (1 - e)^(-1/2) = 1 + e/2 + 3e^2/8 + O(e^3) (|e| near 2^-22, dropped terms below 2^-63).
-static __device__ __forceinline__ double pc_rsqrt_full(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x, y * y, 1.0);
-    return y * fma(e, fma(0.375, e, 0.5), 1.0);
 }
 
 // Records of the relativistic model per node: for every major body b = 0..P (0 = the
