@@ -27,11 +27,12 @@ constexpr int kMaxDevices = 64;
 
 struct OperatorCache {
     int N = 0, NP = 0;
-    double* kfrag = nullptr;   // device, [NP/16][NP/4][64]
-    float* kfrag32 = nullptr;  // device, FP32 fragments in kfrag order
-    float* kfrag32p = nullptr; // device, FP32 fragments with rows permuted per strip
-    double* kfragT = nullptr;  // device, fragments of K_N^T
-    double* kfrag2 = nullptr;  // device, fragments of K2_N
+    double* kfrag = nullptr;   // device, whole K_N, [NP/16][NP/4][64] (pc_apply_operator)
+    double* kpair = nullptr;   // device, fragments of pc_internal.h: K_N
+    float* kpair32 = nullptr;  //   FP32 copy
+    double* kpairT = nullptr;  //   K_N^T
+    double* kpair2 = nullptr;  //   K2_N
+    double* wts = nullptr;     // device, [3][KR] row weights
     double* tau = nullptr;     // device, [NP]
     std::vector<double> K;     // host copy, [N][N]
 };
@@ -39,12 +40,8 @@ struct OperatorCache {
 struct HostOperator {
     int N = 0, NP = 0;
     std::vector<double> K;        // [N][N]
-    std::vector<double> frag;     // [NP/16][NP/4][64]
-    std::vector<float> frag32;    // FP32, frag order
-    std::vector<float> frag32p;   // FP32, rows permuted per strip
-    std::vector<double> fragT;    // fragments of K_N^T
-    std::vector<double> frag2;    // fragments of K2_N (second-order sweeps)
-    std::vector<double> tau;      // [NP]
+    std::vector<double> frag, pair, pairT, pair2, wts, tau;
+    std::vector<float> pair32;
 };
 
 // Device memory of pc_propagate_batched_noalloc: the workspace of its calls (descriptor
@@ -148,8 +145,8 @@ long double cheb_at_node(int k, int j, int N)
 // fit g with the degree N-2 Chebyshev series c_k = 2/(N-1) sum''_l g_l T_k(tau_l),
 // integrate term by term, b_k = (c_{k-1} - c_{k+1})/(2k), and pin the constant so that
 // y(tau = -1) = y_0, which leaves y_j - y_0 = sum_{k>=1} b_k (T_k(tau_j) - (-1)^k).
-// Accumulated in long double, rounded once.
-void build_operator(int N, std::vector<double>& K)
+// In long double.
+void build_operator(int N, std::vector<long double>& K)
 {
     std::vector<long double> D((size_t)(N + 1) * N, 0.0L);   // fit coefficients c_m per unit g_l
     for (int m = 0; m <= N - 2; ++m)
@@ -164,14 +161,14 @@ void build_operator(int N, std::vector<double>& K)
             const long double up = (k + 1 <= N - 2) ? D[(size_t)(k + 1) * N + l] : 0.0L;
             Bc[(size_t)k * N + l] = (lo - up) / (2.0L * k);
         }
-    K.assign((size_t)N * N, 0.0);
+    K.assign((size_t)N * N, 0.0L);
     std::vector<long double> E(N);
     for (int j = 1; j < N; ++j) {                              // row 0 is exactly zero
         for (int k = 1; k <= N - 1; ++k) E[k] = cheb_at_node(k, j, N) - ((k & 1) ? -1.0L : 1.0L);
         for (int l = 0; l < N; ++l) {
             long double s = 0.0L;
             for (int k = 1; k <= N - 1; ++k) s += E[k] * Bc[(size_t)k * N + l];
-            K[(size_t)j * N + l] = (double)s;
+            K[(size_t)j * N + l] = s;
         }
     }
 }
@@ -181,14 +178,14 @@ void build_operator(int N, std::vector<double>& K)
 // of build_operator, integrated once to the velocity series b (zero at tau = -1, constant
 // b_0 = -2 sum_k (-1)^k b_k in the half-coefficient convention) and once more to the
 // position series d_k = (b_{k-1} - b_{k+1}) / (2k), k = 1..N, pinned to zero at tau = -1.
-// Accumulated in long double, rounded once.
-void build_operator2(int N, std::vector<double>& K2)
+// In long double.
+void build_operator2(int N, std::vector<long double>& K2)
 {
     std::vector<long double> Tt((size_t)(N + 1) * N);   // T_k(tau_j), k = 0..N
     for (int k = 0; k <= N; ++k)
         for (int j = 0; j < N; ++j) Tt[(size_t)k * N + j] = cheb_at_node(k, j, N);
     std::vector<long double> c(N + 2), b(N + 2), d(N + 2);
-    K2.assign((size_t)N * N, 0.0);
+    K2.assign((size_t)N * N, 0.0L);
     for (int l = 0; l < N; ++l) {
         std::fill(c.begin(), c.end(), 0.0L);
         std::fill(b.begin(), b.end(), 0.0L);
@@ -205,12 +202,32 @@ void build_operator2(int N, std::vector<double>& K2)
         for (int j = 1; j < N; ++j) {   // row 0 is exactly zero
             long double sx = 0.0L;
             for (int k = 1; k <= N; ++k) sx += d[k] * (Tt[(size_t)k * N + j] - ((k & 1) ? -1.0L : 1.0L));
-            K2[(size_t)j * N + l] = (double)sx;
+            K2[(size_t)j * N + l] = sx;
         }
     }
 }
 
-// Host copies of K_N and of its fragments in the kernels' layouts, built once per N.
+// Fragments of two values (pc_internal.h) of the row operators `at(row, col, h)`.
+template <class At>
+std::vector<double> pair_fragments(int KR, At at)
+{
+    const int NQ = KR / 4;
+    std::vector<double> f((size_t)KR * KR * 2, 0.0);
+    for (int strip = 0; strip < KR / 16; ++strip)
+        for (int q = 0; q < NQ; ++q)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int h = 0; h < 2; ++h)
+                    f[(((size_t)strip * NQ + q) * 64 + lane) * 2 + h] =
+                        (double)at(16 * strip + (lane & 15), 4 * q + (lane >> 4), h);
+    return f;
+}
+
+// Host copies of K_N and of the operators in the kernels' layouts, built once per N.  The even
+// and odd halves of an operator A over the rows (pairs p, p' = N-1-p) are
+// (A[i][p] +- A[i][p']) / 2, formed in long double and rounded once.  The kernels take an even
+// part as the sum over both places of the row, so the middle node of an odd count (both places
+// one node) has half its column there and none in the odd half; the adjoint holds the middle
+// node once, with its whole column.
 const HostOperator& host_operator(pc_ctx* ctx, int N)
 {
     auto it = ctx->host_ops.find(N);
@@ -218,7 +235,10 @@ const HostOperator& host_operator(pc_ctx* ctx, int N)
     HostOperator h;
     h.N = N;
     h.NP = padded_nodes(N);
-    build_operator(N, h.K);
+    std::vector<long double> K, K2;
+    build_operator(N, K);
+    build_operator2(N, K2);
+    h.K.assign(K.begin(), K.end());
     const int NP = h.NP, NQ = NP / 4;
     h.frag.assign((size_t)NP * NP, 0.0);
     for (int strip = 0; strip < NP / 16; ++strip)
@@ -228,40 +248,34 @@ const HostOperator& host_operator(pc_ctx* ctx, int N)
                 h.frag[((size_t)strip * NQ + q) * 64 + lane] =
                     (row < N && col < N) ? h.K[(size_t)row * N + col] : 0.0;
             }
-    // FP32 fragments.  frag32 has the frag order: it is the B operand of the transposed
-    // product of jobs with 16 or more ICs.  frag32p serves the node-row layout of 8-IC
-    // jobs: the f32 16x16x4 MFMA returns row 4(l/16) + r in element r, the f64 one row
-    // l/16 + 4r, and feeding A row i from strip row perm(i) = (i/4) + 4 (i%4) puts the same
-    // node in the same lane and element for both precisions.
-    h.frag32.assign((size_t)NP * NP, 0.0f);
-    for (size_t i = 0; i < h.frag.size(); ++i) h.frag32[i] = (float)h.frag[i];
-    h.frag32p.assign((size_t)NP * NP, 0.0f);
-    for (int strip = 0; strip < NP / 16; ++strip)
-        for (int q = 0; q < NQ; ++q)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int i = lane & 15;
-                const int row = 16 * strip + (i / 4) + 4 * (i % 4), col = 4 * q + (lane >> 4);
-                h.frag32p[((size_t)strip * NQ + q) * 64 + lane] =
-                    (row < N && col < N) ? (float)h.K[(size_t)row * N + col] : 0.0f;
-            }
-    h.fragT.assign((size_t)NP * NP, 0.0);
-    for (int strip = 0; strip < NP / 16; ++strip)
-        for (int q = 0; q < NQ; ++q)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int row = 16 * strip + (lane & 15), col = 4 * q + (lane >> 4);   // of K_N^T
-                h.fragT[((size_t)strip * NQ + q) * 64 + lane] =
-                    (row < N && col < N) ? h.K[(size_t)col * N + row] : 0.0;
-            }
-    std::vector<double> K2;
-    build_operator2(N, K2);
-    h.frag2.assign((size_t)NP * NP, 0.0);
-    for (int strip = 0; strip < NP / 16; ++strip)
-        for (int q = 0; q < NQ; ++q)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int row = 16 * strip + (lane & 15), col = 4 * q + (lane >> 4);
-                h.frag2[((size_t)strip * NQ + q) * 64 + lane] =
-                    (row < N && col < N) ? K2[(size_t)row * N + col] : 0.0;
-            }
+    const bool par = NP >= 32;
+    const int KR = par ? NP / 2 : NP, M = par ? (N + 1) / 2 : N;
+    // even (h 0) or odd (h 1) half of operator A in row i, column (pair) p
+    auto half = [N](const std::vector<long double>& A, int i, int p, int h) -> long double {
+        const int q = N - 1 - p;
+        if (p == q) return h ? 0.0L : 0.5L * A[(size_t)i * N + p];
+        return 0.5L * (A[(size_t)i * N + p] + (h ? -A[(size_t)i * N + q] : A[(size_t)i * N + q]));
+    };
+    auto rows = [&](const std::vector<long double>& A, bool transposed) {
+        return pair_fragments(KR, [&](int i, int p, int hh) -> long double {
+            if (i >= M || p >= M) return 0.0L;
+            const int r = transposed ? p : i, c = transposed ? i : p;
+            if (!par) return A[(size_t)r * N + c];
+            return half(A, r, c, hh) * (transposed && c == N - 1 - c ? 2.0L : 1.0L);
+        });
+    };
+    h.pair = rows(K, false);
+    h.pairT = rows(K, true);
+    h.pair2 = rows(K2, false);
+    h.pair32.assign(h.pair.begin(), h.pair.end());
+    h.wts.assign((size_t)3 * KR, 0.0);
+    if (par)
+        for (int p = 0; p < M; ++p) {
+            const long double w = half(K, N - 1, p, 0);
+            h.wts[p] = (double)w;
+            h.wts[KR + p] = (double)half(K2, N - 1, p, 1);
+            h.wts[2 * KR + p] = (double)(p == N - 1 - p ? w : 0.5L * w);
+        }
     h.tau.assign(NP, 0.0);
     const long double pi = 3.141592653589793238462643383279502884L;
     for (int j = 0; j < N; ++j) h.tau[j] = (double)(-cosl(pi * (long double)j / (long double)(N - 1)));
@@ -281,18 +295,18 @@ int get_operator(pc_ctx* ctx, int N, const OperatorCache** out)
     oc.NP = h.NP;
     oc.K = h.K;
     PC_HIP(ctx, hipSetDevice(ctx->device));
-    PC_HIP(ctx, hipMalloc(&oc.kfrag, h.frag.size() * sizeof(double)));
-    PC_HIP(ctx, hipMalloc(&oc.tau, h.tau.size() * sizeof(double)));
-    PC_HIP(ctx, hipMalloc(&oc.kfragT, h.fragT.size() * sizeof(double)));
-    PC_HIP(ctx, hipMemcpy(oc.kfragT, h.fragT.data(), h.fragT.size() * sizeof(double), hipMemcpyHostToDevice));
-    PC_HIP(ctx, hipMalloc(&oc.kfrag32, h.frag32.size() * sizeof(float)));
-    PC_HIP(ctx, hipMemcpy(oc.kfrag32, h.frag32.data(), h.frag32.size() * sizeof(float), hipMemcpyHostToDevice));
-    PC_HIP(ctx, hipMalloc(&oc.kfrag32p, h.frag32p.size() * sizeof(float)));
-    PC_HIP(ctx, hipMemcpy(oc.kfrag32p, h.frag32p.data(), h.frag32p.size() * sizeof(float), hipMemcpyHostToDevice));
-    PC_HIP(ctx, hipMemcpy(oc.kfrag, h.frag.data(), h.frag.size() * sizeof(double), hipMemcpyHostToDevice));
-    PC_HIP(ctx, hipMemcpy(oc.tau, h.tau.data(), h.tau.size() * sizeof(double), hipMemcpyHostToDevice));
-    PC_HIP(ctx, hipMalloc(&oc.kfrag2, h.frag2.size() * sizeof(double)));
-    PC_HIP(ctx, hipMemcpy(oc.kfrag2, h.frag2.data(), h.frag2.size() * sizeof(double), hipMemcpyHostToDevice));
+    auto upload = [](auto** dev, const auto& host) -> hipError_t {
+        const size_t bytes = host.size() * sizeof(host[0]);
+        const hipError_t e = hipMalloc(reinterpret_cast<void**>(dev), bytes);
+        return e != hipSuccess ? e : hipMemcpy(*dev, host.data(), bytes, hipMemcpyHostToDevice);
+    };
+    PC_HIP(ctx, upload(&oc.kfrag, h.frag));
+    PC_HIP(ctx, upload(&oc.kpair, h.pair));
+    PC_HIP(ctx, upload(&oc.kpair32, h.pair32));
+    PC_HIP(ctx, upload(&oc.kpairT, h.pairT));
+    PC_HIP(ctx, upload(&oc.kpair2, h.pair2));
+    PC_HIP(ctx, upload(&oc.wts, h.wts));
+    PC_HIP(ctx, upload(&oc.tau, h.tau));
     auto res = ctx->ops.emplace(N, std::move(oc));
     *out = &res.first->second;
     return PC_OK;
@@ -592,11 +606,11 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
                                  "pc_propagate_batched with that node count builds them)", G.nodes);
             int rc = get_operator(ctx, G.nodes, &oc);
             if (rc != PC_OK) return rc;
-            d.kfrag = oc->kfrag;
-            d.kfrag32 = oc->kfrag32;
-            d.kfrag32p = oc->kfrag32p;
-            d.kfragT = oc->kfragT;
-            d.kfrag2 = oc->kfrag2;
+            d.kpair = oc->kpair;
+            d.kpair32 = oc->kpair32;
+            d.kpairT = oc->kpairT;
+            d.kpair2 = oc->kpair2;
+            d.wts = oc->wts;
             d.tau = oc->tau;
         }
         plan.n_recs += (int64_t)d.S * G.nodes;
@@ -1153,12 +1167,9 @@ void pc_ctx_destroy(pc_ctx* ctx)
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
     for (auto& kv : ctx->ops) {
-        (void)hipFree(kv.second.kfrag);
-        (void)hipFree(kv.second.tau);
-        (void)hipFree(kv.second.kfrag32);
-        (void)hipFree(kv.second.kfrag32p);
-        (void)hipFree(kv.second.kfragT);
-        (void)hipFree(kv.second.kfrag2);
+        for (void* q : {(void*)kv.second.kfrag, (void*)kv.second.kpair, (void*)kv.second.kpair32,
+                        (void*)kv.second.kpairT, (void*)kv.second.kpair2, (void*)kv.second.wts, (void*)kv.second.tau})
+            (void)hipFree(q);
     }
     if (ctx->staging) (void)hipHostFree(ctx->staging);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);

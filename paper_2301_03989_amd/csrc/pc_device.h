@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <type_traits>
 #include "pc_internal.h"
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -293,6 +294,10 @@ static __device__ __forceinline__ bool pc_kepler(const double (&y0)[6], double d
     return ok;
 }
 
+// From here on the multiply-adds of the sweeps are written out and contraction is off, so that
+// every job body rounds alike: an IC's iterates do not depend on the body, job or column.
+#pragma clang fp contract(off)
+
 // mu / x^(3/2) in full FP64 for finite x > 0, the attraction factor of a point mass at
 // squared distance x: from the hardware estimate y of 1/sqrt(x) and e = 1 - x y^2 (x y^2
 // with y^2 rounded), x^(-3/2) = (y^2)^(3/2) (1 - e)^(-3/2) = y^3 (1 + 3e/2 + 15e^2/8 + O(e^3)).
@@ -307,6 +312,21 @@ static __device__ __forceinline__ double pc_mu_r3(double x, double mu, double mu
     return (y * t) * fma(e, fma(mu2, e, mu1), mu);
 }
 
+static __device__ __forceinline__ double pc_norm2(double x, double y, double z)
+{
+    return fma(z, z, fma(y, y, x * x));
+}
+
+// One attracting body's acceleration at offset d.
+static __device__ __forceinline__ void pc_pull(double dx, double dy, double dz, double mu, double mu1, double mu2,
+                                               double& ax, double& ay, double& az)
+{
+    const double s = pc_mu_r3(pc_norm2(dx, dy, dz), mu, mu1, mu2);
+    ax = fma(-s, dx, ax);
+    ay = fma(-s, dy, ay);
+    az = fma(-s, dz, az);
+}
+
 // ---------------------------------------------------------------------------
 // Force model: point masses in the heliocentric frame with the indirect term,
 //   a = -mu_S r/|r|^3 - sum_p mu_p (r - r_p)/|r - r_p|^3 - sum_p mu_p r_p/|r_p|^3.
@@ -316,17 +336,11 @@ static __device__ __forceinline__ void pc_accel(double x, double y, double z, co
                                                 int P, double mu_sun, double& ax, double& ay,
                                                 double& az)
 {
-    const double s = pc_mu_r3(x * x + y * y + z * z, mu_sun, 1.5 * mu_sun, 1.875 * mu_sun);
-    ax = -s * x;
-    ay = -s * y;
-    az = -s * z;
+    ax = ay = az = 0.0;
+    pc_pull(x, y, z, mu_sun, 1.5 * mu_sun, 1.875 * mu_sun, ax, ay, az);
     for (int p = 0; p < P; ++p) {
         const double4 q = rec[p];
-        const double dx = x - q.x, dy = y - q.y, dz = z - q.z;
-        const double sd = pc_mu_r3(dx * dx + dy * dy + dz * dz, q.w, 1.5 * q.w, 1.875 * q.w);
-        ax -= sd * dx;
-        ay -= sd * dy;
-        az -= sd * dz;
+        pc_pull(x - q.x, y - q.y, z - q.z, q.w, 1.5 * q.w, 1.875 * q.w, ax, ay, az);
     }
     const double4 ind = rec[P];
     ax -= ind.x;
@@ -339,7 +353,6 @@ static __device__ __forceinline__ void pc_accel(double x, double y, double z, co
 // Shared pieces of the propagation kernels
 // ---------------------------------------------------------------------------
 typedef const __attribute__((address_space(1))) double* gconst_dp;
-typedef const __attribute__((address_space(1))) float* gconst_fp;
 typedef const __attribute__((address_space(1))) char* gconst_cp;
 typedef double pc_d2v __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(1))) pc_d2v* gconst_d2p;
@@ -373,20 +386,147 @@ static __device__ __forceinline__ gdp pc_gd(double* q) { return (gdp)q; }
 static __device__ __forceinline__ gconst_dp pc_gcd(const double* q) { return (gconst_dp)q; }
 static __device__ __forceinline__ gi32p pc_gi(int32_t* q) { return (gi32p)q; }
 
+// Shape of a job: NP padded nodes x T = PAIRS / NP ICs on NT threads in W waves.
+//
+// From 32 padded nodes on (PAR) the sweep works on pairs of mirrored nodes (row i: node i and
+// node N-1-i, tau = -tau'), because integration maps the even and the odd part of F apart
+// (pc_product).  A wave owns 16 rows x 8 ICs: both nodes of the pair, all six components.
+// The 16 IC rows of an MFMA block are the position (rows 0..7) and the velocity (8..15)
+// component b of the 8 ICs, and block 3h + b belongs to node h of the pair, so by the result
+// layout (row l/16 + 4r in element r, column l%16) a lane holds the full states of two ICs at
+// both nodes of one row: norms, force and gravity gradient need no other lane.
+// At 16 padded nodes a pair block would be half padding; there a row is one node, and block
+// 3h + b belongs to the h-th eight of a wave's 16 ICs.
+//
+// LDS layout of F: [row][group of ICs][b 3][i 16][h 2], i = 8 (component half) + IC of the
+// group's eight, place i XOR-ed with row % 16.  One ds_read_b128 gives a lane the operands of
+// both h; the 16 lanes of a k row read 256 consecutive bytes, and the 16 lanes that publish
+// one IC at 16 rows write 16 different 16-byte places (without the XOR all would fall on the
+// same banks, a row being a multiple of 256 bytes).
+template <int PAIRS, int NP>
+struct PcShape {
+    static constexpr int NT = PAIRS / 4;
+    static constexpr int W = NT / 64;
+    static constexpr int T = PAIRS / NP;
+    static constexpr bool PAR = NP >= 32;
+    static constexpr int KR = PAR ? NP / 2 : NP;   // rows of F
+    static constexpr int NQ = KR / 4;              // k steps of the 16x16x4 product
+    static constexpr int STRIPS = KR / 16;
+    static constexpr int COLS = PAR ? 8 : 16;      // ICs of one wave (a group)
+    static constexpr int GN = T / COLS;            // groups
+    static constexpr int ROW = GN * 96;            // doubles per row of F
+    static constexpr int E = PAR ? 2 : 4;          // ICs a lane holds points of
+    static_assert(T >= 8 && T <= PAIRS / 16 && W == STRIPS * GN, "unsupported job shape");
+};
+
+struct PcLane {
+    int lane, wave, strip, grp;
+    int g, c;        // lane / 16, lane % 16
+    int row;         // the lane's row of F
+    int jn[2];       // its nodes (past the last row: those of the last one)
+    bool ok;         // the row holds nodes
+    bool two;        // the row's nodes differ (not the middle node of an odd count, nor one-node rows)
+    int nq;          // k steps the products run: up to the last block of 16 rows that holds nodes
+};
+
+// The fragments of the operators are zero past the last row, so the products stop after the
+// last 16-row block holding one (4 k steps each; at least two blocks when the padded count
+// has them, which the k loop's prologue needs).
+// Waves of one group are consecutive: a job with few ICs keeps one wave per SIMD busy.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_lane_place(PcLane& L, int N)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    const int M = Sh::PAR ? (N + 1) >> 1 : N;
+    L.g = L.lane >> 4;
+    L.c = L.lane & 15;
+    L.row = L.strip * 16 + L.c;
+    L.ok = L.row < M;
+    const int i = L.ok ? L.row : M - 1;
+    L.jn[0] = i;
+    L.jn[1] = Sh::PAR ? N - 1 - i : i;
+    L.two = Sh::PAR && L.jn[1] != L.jn[0];
+}
+template <int PAIRS, int NP>
+static __device__ __forceinline__ PcLane pc_lane_geometry(int tid, int N)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    PcLane L;
+    const int M = Sh::PAR ? (N + 1) >> 1 : N;
+    L.nq = Sh::NQ > 4 ? min(Sh::NQ, max(8, ((M + 15) >> 4) << 2)) : Sh::NQ;
+    L.lane = tid & 63;
+    L.wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // one value per wave: scalar registers and branches
+    L.strip = L.wave % Sh::STRIPS;
+    L.grp = L.wave / Sh::STRIPS;
+    pc_lane_place<PAIRS, NP>(L, N);
+    return L;
+}
+// The same lane, its places computed again from here on: a sweep loop then forms its LDS
+// addresses where it uses them (a few integer instructions) instead of holding each across the
+// loop, which spilled them to scratch.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ PcLane pc_lane_again(const PcLane& L, int N)
+{
+    PcLane R = L;
+    asm volatile("" : "+v"(R.lane));
+    pc_lane_place<PAIRS, NP>(R, N);
+    return R;
+}
+
+// Column (IC within the group) of the lane's e-th IC, and the IC (within the job) of its point
+// (h, r).
+template <int PAIRS, int NP>
+static __device__ __forceinline__ int pc_col(const PcLane& L, int e)
+{
+    return PcShape<PAIRS, NP>::PAR ? L.g + 4 * e : 8 * (e >> 1) + L.g + 4 * (e & 1);
+}
+template <int PAIRS, int NP>
+static __device__ __forceinline__ int pc_ic(const PcLane& L, int h, int r)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    return L.grp * Sh::COLS + (Sh::PAR ? 0 : 8 * h) + L.g + 4 * r;
+}
+
+// Place of (row, group, b, i) in F, in pairs of values.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ int pc_unit(int row, int grp, int b, int i)
+{
+    return row * (PcShape<PAIRS, NP>::ROW / 2) + grp * 48 + b * 16 + (i ^ (row & 15));
+}
+
 // Shared-memory arena of one workgroup (sized for the largest job shape).
+// REC: ephemeris kept in LDS, 8 perturbers at the shape's largest node count.  Past the 6T
+// doubles in use, Y0 holds the weights of the job's rows (pc_weights).
 template <int PAIRS>
 struct PcSmem {
-    static constexpr int REC = PAIRS >= 2048 ? 7040 : 3072;   // doubles of ephemeris kept in LDS
-    double F[6 * PAIRS];          // [node][F comp 6][IC]: velocity (0..2), acceleration (3..5)
-    double Rec[REC];              // [node][body 0..P][3]: perturber positions, then the indirect term
+    static constexpr int REC = PAIRS >= 2048 ? 7040 : 3456;
+    alignas(16) double F[6 * PAIRS];
+    alignas(16) double Rec[REC];  // [node][body 0..P][3]: perturber positions, then the indirect term
     double Y0[6 * (PAIRS / 16)];  // [comp][IC] initial state of the current segment
-    double Mu[3 * PC_MAX_PERT_DEV];   // perturber mu, then 3 mu / 2, then 15 mu / 8 (pc_mu_r3)
+    alignas(16) double Mu[4 * PC_MAX_PERT_DEV];   // per perturber mu, 3 mu / 2, 15 mu / 8 (pc_mu_r3), 0
     int Flag[(PAIRS / 256) * 16]; // per wave, per IC: bit 0 not converged, bit 1 non-finite, bit 2 large change
     int Keep[PAIRS / 256];        // per wave: an iterating IC still changes by more than the FP32 switch
     int Go[PAIRS / 256];          // per wave (or IC group): some IC still iterates after this sweep
     int Active[PAIRS / 16];
     int Dead[PAIRS / 16];
 };
+
+template <int PAIRS, int NP>
+static __device__ __forceinline__ double* pc_weights(PcSmem<PAIRS>& sm)
+{
+    return sm.Y0 + 6 * PcShape<PAIRS, NP>::T;
+}
+
+// The rows' weights into LDS, once per job: w (even part of the last node's integral) and w2
+// (odd part of its double integral, second-order sweeps).
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_stage_weights(PcSmem<PAIRS>& sm, const double* wts)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    if constexpr (Sh::PAR) {
+        for (int i = threadIdx.x; i < 2 * Sh::KR; i += Sh::NT) pc_weights<PAIRS, NP>(sm)[i] = pc_gcd(wts)[i];
+    }
+}
 
 // After the stopping rule (taken by threads tid < T on their IC's status word), the waves
 // that hold status words note whether some IC still iterates; the barrier that ends the
@@ -413,173 +553,138 @@ static __device__ __forceinline__ bool pc_any_active(const PcSmem<PAIRS>& sm)
     return a != 0;
 }
 
-// The same for R points at one node j (the transposed job layout): the bodies go in
-// chunks of four whose records are read together, so the wave waits on LDS once per chunk;
-// past the last body the indirect-term record (always present) stands in with zero mass.
-template <int R>
-static __device__ __forceinline__ void pc_force_lds_node(const double (&x)[R], const double (&y)[R],
-                                                         const double (&z)[R], int j, int P, double mu_sun,
-                                                         const double* srec, const double* smu,
-                                                         double (&ax)[R], double (&ay)[R], double (&az)[R])
+// ---------------------------------------------------------------------------
+// Force, gravity gradient and Hessian products at a lane's four points: point p = 2h + r is
+// IC r at node jn[h].
+// ---------------------------------------------------------------------------
+// Accelerations with the records in LDS (compact [node][body][3], masses [body][4]): two
+// bodies at a time, so that a wave waits on LDS once per eight body-point pairs.
+static __device__ __forceinline__ void pc_force_lds(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                    const int (&jn)[2], int P, double mu_sun, const double* srec,
+                                                    const double* smu, double (&ax)[4], double (&ay)[4],
+                                                    double (&az)[4])
 {
-    const double* rec = srec + j * 3 * (P + 1);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double s = pc_mu_r3(x[r] * x[r] + y[r] * y[r] + z[r] * z[r], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun);
-        ax[r] = -s * x[r];
-        ay[r] = -s * y[r];
-        az[r] = -s * z[r];
+    for (int p = 0; p < 4; ++p) {
+        ax[p] = ay[p] = az[p] = 0.0;
+        pc_pull(x[p], y[p], z[p], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun, ax[p], ay[p], az[p]);
     }
-    for (int b0 = 0; b0 < P; b0 += 4) {
-        double qx[4], qy[4], qz[4], mu[4], mu1[4], mu2[4];
+    const double* rec[2] = {srec + jn[0] * 3 * (P + 1), srec + jn[1] * 3 * (P + 1)};
+    auto bodies = [&](int b, auto nb) __attribute__((always_inline)) {
+        constexpr int NB = decltype(nb)::value;
+        double q[NB][2][3], mu[NB][3];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int b = b0 + k < P ? b0 + k : P;
-            const int bm = b0 + k < P ? b0 + k : 0;
-            mu[k] = b0 + k < P ? smu[bm] : 0.0;
-            mu1[k] = b0 + k < P ? smu[PC_MAX_PERT_DEV + bm] : 0.0;
-            mu2[k] = b0 + k < P ? smu[2 * PC_MAX_PERT_DEV + bm] : 0.0;
-            qx[k] = rec[3 * b];
-            qy[k] = rec[3 * b + 1];
-            qz[k] = rec[3 * b + 2];
-        }
+        for (int k = 0; k < NB; ++k) {
+            const pc_d2v m01 = *reinterpret_cast<const pc_d2v*>(smu + 4 * (b + k));
+            mu[k][0] = m01.x;
+            mu[k][1] = m01.y;
+            mu[k][2] = smu[4 * (b + k) + 2];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+            for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double dx = x[r] - qx[k], dy = y[r] - qy[k], dz = z[r] - qz[k];
-                const double sd = pc_mu_r3(dx * dx + dy * dy + dz * dz, mu[k], mu1[k], mu2[k]);
-                ax[r] -= sd * dx;
-                ay[r] -= sd * dy;
-                az[r] -= sd * dz;
+                for (int c = 0; c < 3; ++c) q[k][h][c] = rec[h][3 * (b + k) + c];
             }
         }
-    }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        ax[r] -= rec[3 * P];
-        ay[r] -= rec[3 * P + 1];
-        az[r] -= rec[3 * P + 2];
-    }
-}
-
-// Accelerations at R points whose perturber records sit in LDS (compact [node][body][3]).
-template <int R>
-static __device__ __forceinline__ void pc_force_lds(const double (&x)[R], const double (&y)[R],
-                                                    const double (&z)[R], const int (&jr)[R], int P,
-                                                    double mu_sun, const double* srec, const double* smu,
-                                                    double (&ax)[R], double (&ay)[R], double (&az)[R])
-{
-    const int stride = 3 * (P + 1);
+        for (int k = 0; k < NB; ++k) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double s = pc_mu_r3(x[r] * x[r] + y[r] * y[r] + z[r] * z[r], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun);
-        ax[r] = -s * x[r];
-        ay[r] = -s * y[r];
-        az[r] = -s * z[r];
-    }
-    for (int b = 0; b < P; ++b) {
-        const double mu = smu[b], mu1 = smu[PC_MAX_PERT_DEV + b], mu2 = smu[2 * PC_MAX_PERT_DEV + b];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double* q = srec + jr[r] * stride + 3 * b;
-            const double dx = x[r] - q[0], dy = y[r] - q[1], dz = z[r] - q[2];
-            const double sd = pc_mu_r3(dx * dx + dy * dy + dz * dz, mu, mu1, mu2);
-            ax[r] -= sd * dx;
-            ay[r] -= sd * dy;
-            az[r] -= sd * dz;
+            for (int p = 0; p < 4; ++p)
+                pc_pull(x[p] - q[k][p >> 1][0], y[p] - q[k][p >> 1][1], z[p] - q[k][p >> 1][2], mu[k][0], mu[k][1],
+                        mu[k][2], ax[p], ay[p], az[p]);
         }
-    }
+    };
+    int b = 0;
+    for (; b + 2 <= P; b += 2) bodies(b, std::integral_constant<int, 2>{});
+    if (b < P) bodies(b, std::integral_constant<int, 1>{});
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double* q = srec + jr[r] * stride + 3 * P;
-        ax[r] -= q[0];
-        ay[r] -= q[1];
-        az[r] -= q[2];
+    for (int p = 0; p < 4; ++p) {
+        ax[p] -= rec[p >> 1][3 * P];
+        ay[p] -= rec[p >> 1][3 * P + 1];
+        az[p] -= rec[p >> 1][3 * P + 2];
     }
 }
 
 // FP32 variant for the early sweeps of the precision schedule: the differences to the
 // perturbers are formed in FP64, everything after them in FP32.
-template <int R>
-static __device__ __forceinline__ void pc_force_lds32(const double (&x)[R], const double (&y)[R],
-                                                      const double (&z)[R], const int (&jr)[R], int P,
-                                                      double mu_sun, const double* srec, const double* smu,
-                                                      double (&ax)[R], double (&ay)[R], double (&az)[R])
+static __device__ __forceinline__ void pc_force_lds32(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                      const int (&jn)[2], int P, double mu_sun, const double* srec,
+                                                      const double* smu, double (&ax)[4], double (&ay)[4],
+                                                      double (&az)[4])
 {
-    const int stride = 3 * (P + 1);
-    float fx[R], fy[R], fz[R];
+    float fx[4], fy[4], fz[4];
+    auto add = [&](int p, float dx, float dy, float dz, float mu) __attribute__((always_inline)) {
+        const float id = rsqrtf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+        const float s = mu * (id * id * id);
+        fx[p] = fmaf(-s, dx, fx[p]);
+        fy[p] = fmaf(-s, dy, fy[p]);
+        fz[p] = fmaf(-s, dz, fz[p]);
+    };
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const float xf = (float)x[r], yf = (float)y[r], zf = (float)z[r];
-        const float ir = rsqrtf(xf * xf + yf * yf + zf * zf);
-        const float s = (float)mu_sun * (ir * ir * ir);
-        fx[r] = -s * xf;
-        fy[r] = -s * yf;
-        fz[r] = -s * zf;
+    for (int p = 0; p < 4; ++p) {
+        fx[p] = fy[p] = fz[p] = 0.0f;
+        add(p, (float)x[p], (float)y[p], (float)z[p], (float)mu_sun);
     }
+    const double* rec[2] = {srec + jn[0] * 3 * (P + 1), srec + jn[1] * 3 * (P + 1)};
     for (int b = 0; b < P; ++b) {
-        const float mu = (float)smu[b];
+        const float mu = (float)smu[4 * b];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double* q = srec + jr[r] * stride + 3 * b;
-            const float dx = (float)(x[r] - q[0]), dy = (float)(y[r] - q[1]), dz = (float)(z[r] - q[2]);
-            const float id = rsqrtf(dx * dx + dy * dy + dz * dz);
-            const float sd = mu * (id * id * id);
-            fx[r] -= sd * dx;
-            fy[r] -= sd * dy;
-            fz[r] -= sd * dz;
+        for (int p = 0; p < 4; ++p) {
+            const double* q = rec[p >> 1] + 3 * b;
+            add(p, (float)(x[p] - q[0]), (float)(y[p] - q[1]), (float)(z[p] - q[2]), mu);
         }
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double* q = srec + jr[r] * stride + 3 * P;
-        ax[r] = (double)(fx[r] - (float)q[0]);
-        ay[r] = (double)(fy[r] - (float)q[1]);
-        az[r] = (double)(fz[r] - (float)q[2]);
+    for (int p = 0; p < 4; ++p) {
+        const double* q = rec[p >> 1] + 3 * P;
+        ax[p] = (double)(fx[p] - (float)q[0]);
+        ay[p] = (double)(fy[p] - (float)q[1]);
+        az[p] = (double)(fz[p] - (float)q[2]);
     }
 }
 
-// Same with the records read from global memory ((x, y, z, mu) per body, then the indirect term).
-template <int R>
-static __device__ __forceinline__ void pc_force_glb(const double (&x)[R], const double (&y)[R],
-                                                    const double (&z)[R], const int (&jr)[R], int P,
-                                                    double mu_sun, const double4* grec,
-                                                    double (&ax)[R], double (&ay)[R], double (&az)[R])
+// Same as pc_force_lds with the records read from global memory ((x, y, z, mu) per body, then
+// the indirect term), each where it is used: the other wave on the SIMD covers the wait.
+static __device__ __forceinline__ void pc_force_glb(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                    const int (&jn)[2], int P, double mu_sun, const double4* grec,
+                                                    double (&ax)[4], double (&ay)[4], double (&az)[4])
 {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double s = pc_mu_r3(x[r] * x[r] + y[r] * y[r] + z[r] * z[r], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun);
-        ax[r] = -s * x[r];
-        ay[r] = -s * y[r];
-        az[r] = -s * z[r];
+    for (int p = 0; p < 4; ++p) {
+        ax[p] = ay[p] = az[p] = 0.0;
+        pc_pull(x[p], y[p], z[p], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun, ax[p], ay[p], az[p]);
     }
-    // each body's records are loaded where they are used: the other wave on the SIMD
-    // covers the wait, while holding the next body's records too raises the register
-    // pressure of the 256-node bodies into spills (6 % slower with one buffer, 19 % with two)
     const gconst_cp base = pc_wave_base(grec);
-    uint32_t vo[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) vo[r] = (uint32_t)jr[r] * (uint32_t)(P + 1) * 32u;
+    const uint32_t vo[2] = {(uint32_t)jn[0] * (uint32_t)(P + 1) * 32u, (uint32_t)jn[1] * (uint32_t)(P + 1) * 32u};
     for (int b = 0; b < P; ++b) {
-        double4 q[R];
+        double4 q[2];
 #pragma unroll
-        for (int r = 0; r < R; ++r) q[r] = pc_load_d4((base + (size_t)b * 32) + vo[r]);
+        for (int h = 0; h < 2; ++h) q[h] = pc_load_d4((base + (size_t)b * 32) + vo[h]);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double dx = x[r] - q[r].x, dy = y[r] - q[r].y, dz = z[r] - q[r].z;
-            const double sd = pc_mu_r3(dx * dx + dy * dy + dz * dz, q[r].w, 1.5 * q[r].w, 1.875 * q[r].w);
-            ax[r] -= sd * dx;
-            ay[r] -= sd * dy;
-            az[r] -= sd * dz;
+        for (int p = 0; p < 4; ++p) {
+            const double4& k = q[p >> 1];
+            pc_pull(x[p] - k.x, y[p] - k.y, z[p] - k.z, k.w, 1.5 * k.w, 1.875 * k.w, ax[p], ay[p], az[p]);
         }
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const double4 q = pc_load_d4((base + (size_t)P * 32) + vo[r]);
-        ax[r] -= q.x;
-        ay[r] -= q.y;
-        az[r] -= q.z;
+    for (int p = 0; p < 4; ++p) {
+        const double4 q = pc_load_d4((base + (size_t)P * 32) + vo[p >> 1]);
+        ax[p] -= q.x;
+        ay[p] -= q.y;
+        az[p] -= q.z;
+    }
+}
+
+// Record of body b at the lane's node h: from LDS (compact [node][body][3], masses in smu) or
+// from global memory (double4 (x, y, z, mu)).
+template <bool LDSREC>
+static __device__ __forceinline__ double4 pc_record(const double* srec, const double* smu, const double4* grec, int P,
+                                                    int j, int b)
+{
+    if constexpr (LDSREC) {
+        const double* q = srec + j * 3 * (P + 1) + 3 * b;
+        return make_double4(q[0], q[1], q[2], smu[4 * b]);
+    } else {
+        return pc_load_d4((pc_wave_base(grec) + (size_t)b * 32) + (uint32_t)j * (uint32_t)(P + 1) * 32u);
     }
 }
 
@@ -590,999 +695,59 @@ static __device__ __forceinline__ void pc_hess_term(double dx, double dy, double
                                                     double wz, double mu, double mu1, double mu2, double& hx,
                                                     double& hy, double& hz)
 {
-    const double x = dx * dx + dy * dy + dz * dz;
+    const double x = pc_norm2(dx, dy, dz);
     const double y = __builtin_amdgcn_rsq(x);
     const double t = y * y;
     const double e = fma(-x, t, 1.0);
     const double A = (y * t) * fma(e, fma(mu2, e, mu1), mu);
     const double i2 = fma(t, fma(e, e, e), t);
-    const double c = (A * i2) * (3.0 * (dx * wx + dy * wy + dz * wz));
+    const double c = (A * i2) * (3.0 * fma(dz, wz, fma(dy, wy, dx * wx)));
     hx = fma(c, dx, fma(-A, wx, hx));
     hy = fma(c, dy, fma(-A, wy, hy));
     hz = fma(c, dz, fma(-A, wz, hz));
 }
 
-// H w for the symmetric force Jacobian H = da/dr at R points: every attracting body with
-// parameter mu at offset d contributes -mu (w/|d|^3 - 3 d (d.w)/|d|^5); the indirect term
-// does not depend on r.  Records as in pc_force_lds (LDS) or pc_force_glb (global).
-template <int R, bool LDSREC>
-static __device__ __forceinline__ void pc_hess_apply(const double (&x)[R], const double (&y)[R],
-                                                     const double (&z)[R], const double (&wx)[R],
-                                                     const double (&wy)[R], const double (&wz)[R],
-                                                     const int (&jr)[R], int P, double mu_sun,
+// H w for the symmetric force Jacobian H = da/dr at the lane's points: every attracting body
+// with parameter mu at offset d contributes -mu (w/|d|^3 - 3 d (d.w)/|d|^5); the indirect term
+// does not depend on r.
+template <bool LDSREC>
+static __device__ __forceinline__ void pc_hess_apply(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                     const double (&wx)[4], const double (&wy)[4],
+                                                     const double (&wz)[4], const int (&jn)[2], int P, double mu_sun,
                                                      const double* srec, const double* smu, const double4* grec,
-                                                     double (&hx)[R], double (&hy)[R], double (&hz)[R])
+                                                     double (&hx)[4], double (&hy)[4], double (&hz)[4])
 {
-    const double ms1 = 1.5 * mu_sun, ms2 = 1.875 * mu_sun;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        hx[r] = hy[r] = hz[r] = 0.0;
-        pc_hess_term(x[r], y[r], z[r], wx[r], wy[r], wz[r], mu_sun, ms1, ms2, hx[r], hy[r], hz[r]);
+    for (int p = 0; p < 4; ++p) {
+        hx[p] = hy[p] = hz[p] = 0.0;
+        pc_hess_term(x[p], y[p], z[p], wx[p], wy[p], wz[p], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun, hx[p], hy[p], hz[p]);
     }
-    const int stride = 3 * (P + 1);
     for (int b = 0; b < P; ++b) {
+        double4 q[2];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            double qx, qy, qz, mu, mu1, mu2;
-            if constexpr (LDSREC) {
-                const double* q = srec + jr[r] * stride + 3 * b;
-                qx = q[0]; qy = q[1]; qz = q[2];
-                mu = smu[b];
-                mu1 = smu[PC_MAX_PERT_DEV + b];
-                mu2 = smu[2 * PC_MAX_PERT_DEV + b];
-            } else {
-                const double4 q = grec[(size_t)jr[r] * (P + 1) + b];
-                qx = q.x; qy = q.y; qz = q.z;
-                mu = q.w;
-                mu1 = 1.5 * q.w;
-                mu2 = 1.875 * q.w;
-            }
-            pc_hess_term(x[r] - qx, y[r] - qy, z[r] - qz, wx[r], wy[r], wz[r], mu, mu1, mu2, hx[r], hy[r], hz[r]);
+        for (int h = 0; h < 2; ++h) q[h] = pc_record<LDSREC>(srec, smu, grec, P, jn[h], b);
+        const double mu1 = LDSREC ? smu[4 * b + 1] : 1.5 * q[0].w, mu2 = LDSREC ? smu[4 * b + 2] : 1.875 * q[0].w;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const double4& k = q[p >> 1];
+            pc_hess_term(x[p] - k.x, y[p] - k.y, z[p] - k.z, wx[p], wy[p], wz[p], k.w, mu1, mu2, hx[p], hy[p], hz[p]);
         }
     }
 }
 
-// Shape of a job: PAIRS = NP x T (node, IC) pairs, NT threads in W waves; every wave owns
-// six 16x16 blocks of the iterate.  WIDE (T >= 16): one 16-node strip x the six component
-// blocks of one 16-IC group, computed transposed (IC rows, node columns), so that lane l
-// holds node l%16 of the strip for ICs l/16 + 4r, r = 0..3 (one node per lane: the force
-// reads each perturber record once for its four points).  Otherwise (T == 8): two strips
-// x three blocks of two components x 8 ICs, node rows; lane l holds nodes l/16 + 4r and
-// components hi, 2+hi, 4+hi of IC l%8 (hi = bit 3 of l).
-template <int PAIRS, int NP>
-struct PcShape {
-    static constexpr int NT = PAIRS / 4;
-    static constexpr int W = NT / 64;
-    static constexpr int T = PAIRS / NP;
-    static constexpr int ROW = 6 * T;      // doubles per node row of F
-    static constexpr int NQ = NP / 4;      // k-steps of the 16x16x4 product
-    static constexpr bool WIDE = T >= 16;
-    static constexpr int G16 = WIDE ? T / 16 : 1;
-    static constexpr int H = WIDE ? 1 : 2; // strips per wave
-    static_assert(T >= 8 && T <= PAIRS / 16, "unsupported job shape");
-};
-
-struct PcLane {
-    int lane, wave, strip0, grp, hi;
-    int wide;
-    int ic_base, ic_step;   // the lane's element r belongs to IC ic_base + ic_step r of the job
-    int nq;                 // k steps the products run: the 16-node blocks that hold a node < N
-};
-
-// nq: K_N's fragments are zero in every column at or past N, so the products stop after
-// the last 16-node block holding a node (4 k steps each; at least two blocks when the
-// padded count has them, which the k loop's prologue needs)
-template <int PAIRS, int NP>
-static __device__ __forceinline__ PcLane pc_lane_geometry(int tid, int N)
+// Linear change of the point-mass acceleration over a position change at the lane's points:
+// g = (da/dr)(r) dr, the Hessian product with w = dr.
+static __device__ __forceinline__ void pc_grad_dot(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                   const double (&dx)[4], const double (&dy)[4], const double (&dz)[4],
+                                                   const int (&jn)[2], int P, double mu_sun, bool rec_lds,
+                                                   const double* srec, const double* smu, const double4* grec,
+                                                   double (&gx)[4], double (&gy)[4], double (&gz)[4])
 {
-    using Sh = PcShape<PAIRS, NP>;
-    PcLane L;
-    L.nq = Sh::NQ > 4 ? min(Sh::NQ, max(8, ((N + 15) >> 4) << 2)) : Sh::NQ;
-    L.lane = tid & 63;
-    L.wave = tid >> 6;
-    L.strip0 = Sh::WIDE ? L.wave / Sh::G16 : 2 * L.wave;
-    L.grp = Sh::WIDE ? L.wave - L.strip0 * Sh::G16 : 0;
-    L.hi = Sh::WIDE ? 0 : (L.lane >> 3) & 1;
-    L.wide = Sh::WIDE;
-    L.ic_base = Sh::WIDE ? L.grp * 16 + (L.lane >> 4) : (L.lane & 7);
-    L.ic_step = Sh::WIDE ? 4 : 0;
-    return L;
+    if (rec_lds) pc_hess_apply<true>(x, y, z, dx, dy, dz, jn, P, mu_sun, srec, smu, grec, gx, gy, gz);
+    else pc_hess_apply<false>(x, y, z, dx, dy, dz, jn, P, mu_sun, srec, smu, grec, gx, gy, gz);
 }
 
-// node of the lane's element r in strip h (MFMA f64 result layout: D[l/16 + 4r][l%16];
-// WIDE blocks are transposed, so their node is the column l%16)
-static __device__ __forceinline__ int pc_node(const PcLane& L, int h, int r)
-{
-    return L.wide ? L.strip0 * 16 + (L.lane & 15) : (L.strip0 + h) * 16 + (L.lane >> 4) + 4 * r;
-}
-
-// IC (index within the job) of the lane's element r
-static __device__ __forceinline__ int pc_ic(const PcLane& L, int r)
-{
-    return L.ic_base + L.ic_step * r;
-}
-
-// IC whose stopping-rule flag lane l < 16 returns from pc_product: grp * 16 + l (WIDE),
-// l % 8 (T == 8)
-template <int PAIRS, int NP>
-static __device__ __forceinline__ int pc_flag_ic(const PcLane& L)
-{
-    return PcShape<PAIRS, NP>::WIDE ? L.grp * 16 + (L.lane & 15) : (L.lane & 7);
-}
-
-// Column of IC m in node row j of the LDS force array F[node][comp][IC].  WIDE jobs XOR
-// the IC's place in its 16-IC group with j % 16: a row is 6T doubles, a multiple of the
-// bank count, so without it the 16 lanes of a row group (one node each, same IC) would
-// all hit one bank.  Readers of a 16-column group still see a permutation of it.
-template <int PAIRS, int NP>
-static __device__ __forceinline__ int pc_fcol(int j, int m)
-{
-    return PcShape<PAIRS, NP>::WIDE ? (m ^ (j & 15)) : m;
-}
-
-// Software-pipelined k loop of a 16x16x4 product over nq steps (a multiple of 4, at most
-// NQ, at least 8 when NQ is; NQ fixes the layout of the operands).  The A operand of step q
-// (a K_N fragment, read from L2) is loaded DK steps ahead into a ring of DK registers, the
-// B operands (LDS) one step ahead into two buffers, and the loop body is unrolled DK
-// times, so both rings rotate by register renaming.  A register move out of a ring would
-// make the wave wait for the load it copies right after issuing it.
-// loadB(q, q % 4, buffer) gets the phase as a compile-time constant after unrolling;
-// loadA0(u) supplies the first DK A operands (registers kept across calls, or loads).
-// SG_DS / SG_MFMA / SG_VMEM > 0 pin the order of one step in the steady-state loop for
-// the scheduler: the B reads of the next step, this step's MFMAs, then the A read DK
-// steps ahead (left to itself, the scheduler sinks the reads below the MFMAs that free
-// their registers, and the wave then waits on each read right after issuing it).
-template <int NQ, int NB, class AT, class BT, int SG_DS = 0, int SG_MFMA = 0, int SG_VMEM = 0, class LA0,
-          class LA, class LB, class MM>
-static __device__ __forceinline__ void pc_kloop(int nq, LA0 loadA0, LA loadA, LB loadB, MM mma)
-{
-    constexpr int DK = 4;
-    static_assert(NQ % DK == 0, "k steps must be a multiple of the A ring depth");
-    AT ka[DK];
-    BT bb[2][NB];
-#pragma unroll
-    for (int u = 0; u < DK; ++u) ka[u] = loadA0(u);
-    loadB(0, 0, bb[0]);
-    auto steps = [&](int q0) {
-#pragma unroll
-        for (int u = 0; u < DK; ++u) {
-            loadB(q0 + u + 1, (u + 1) & 3, bb[(u + 1) & 1]);
-            mma(ka[u], bb[u & 1]);
-            ka[u] = loadA(q0 + u + DK);
-            if constexpr (SG_MFMA > 0) {
-                __builtin_amdgcn_sched_group_barrier(0x100, SG_DS, 0);     // DS reads
-                __builtin_amdgcn_sched_group_barrier(0x008, SG_MFMA, 0);   // MFMA
-                __builtin_amdgcn_sched_group_barrier(0x020, SG_VMEM, 0);   // VMEM reads
-            }
-        }
-    };
-    // the first DK steps outside the loop: their products start from the caller's
-    // accumulators directly (a zero start becomes the MFMA's inline constant instead of
-    // register moves on every sweep)
-    if constexpr (NQ > DK) steps(0);
-    auto rest = [&](int n) __attribute__((always_inline)) {
-#pragma unroll 1
-        for (int q0 = DK; q0 < n - DK; q0 += DK) steps(q0);
-#pragma unroll
-        for (int u = 0; u < DK; ++u) {   // the last DK steps load nothing past the end
-            if (u + 1 < DK) loadB(n - DK + u + 1, (u + 1) & 3, bb[(u + 1) & 1]);
-            mma(ka[u], bb[u & 1]);
-        }
-    };
-    // a job whose nodes fill every k step keeps the compile-time bound (constant B
-    // offsets in the last steps); a shorter one runs to its own bound, one value per wave
-    // (a scalar, which keeps the loop and the B addresses off the vector registers)
-    if constexpr (NQ > 2 * DK) {
-        if (nq < NQ) {
-            rest(__builtin_amdgcn_readfirstlane(nq));
-            return;
-        }
-    }
-    rest(NQ);
-}
-
-struct PcPairD {
-    double a0, a1;
-};
-
-// The first four FP64 A operands of the lane's strip (and, for 8-IC jobs, of its second
-// strip), loaded once per job: every product then starts without waiting on L2.
-template <int PAIRS, int NP>
-static __device__ __forceinline__ void pc_kpre_load(gconst_dp kp0, double (&kpre)[8])
-{
-    constexpr int NQ = NP / 4;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        kpre[u] = kp0[u * 64];
-        kpre[4 + u] = PcShape<PAIRS, NP>::WIDE ? 0.0 : kp0[(NQ + u) * 64];
-    }
-}
-struct PcPairF {
-    float a0, a1;
-};
-
-// Stopping-rule thresholds in fma form, fixed per segment: a squared change d2 passes
-// against the squared norm y2 when d2 < a y2 + b, with (a, b) = (tol^2, 0) for the relative
-// rule and (0, tol^2) for the absolute one (the same comparisons as d2 < tol^2 y2 and
-// d2 < tol^2 for finite norms, with no branch on the mode).  (sa, sb): the same for the
-// precision switch.
-struct PcTol {
-    double ta, tb, sa, sb;
-};
-static __device__ __forceinline__ PcTol pc_tol(int tol_mode, double t2, double sw2)
-{
-    return tol_mode == 0 ? PcTol{t2, 0.0, sw2, 0.0} : PcTol{0.0, t2, 0.0, sw2};
-}
-
-// Epilogue of a transposed (WIDE) product: acc <- base + w2 acc, where base is y0 (a Picard
-// sweep, INCR false) or the previous iterate itself (an increment sweep, INCR true); the
-// stopping-rule flags of Sec. 2.2 against the previous iterate yc, OR-ed over the strip's
-// nodes, returned by lane i < 16 for local IC i.  SW: evaluate the switch test (bit 2).
-template <int PAIRS, int NP, bool INCR, bool SW = true>
-static __device__ __forceinline__ int pc_wide_epilogue(const double* sY0, const double (&yc)[6][4],
-                                                       f64x4 (&acc)[6], double w2, const PcTol& tl, int N,
-                                                       const PcLane& L)
-{
-    constexpr int T = PcShape<PAIRS, NP>::T;
-    const bool node_ok = pc_node(L, 0, 0) < N;
-    int fr = 0;   // element r's flags in bits 4r..4r+2
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = pc_ic(L, r);
-        double pd = 0.0, py = 0.0, vd = 0.0, vy = 0.0;
-#pragma unroll
-        for (int b = 0; b < 6; ++b) {
-            const double yn = (INCR ? yc[b][r] : sY0[b * T + m]) + w2 * acc[b][r];
-            acc[b][r] = yn;
-            const double d = yn - yc[b][r];
-            if (b < 3) { pd += d * d; py += yn * yn; }
-            else { vd += d * d; vy += yn * yn; }
-        }
-        const bool ok = pd < fma(tl.ta, py, tl.tb) && vd < fma(tl.ta, vy, tl.tb);
-        const bool lo = !SW || (pd < fma(tl.sa, py, tl.sb) && vd < fma(tl.sa, vy, tl.sb));
-        // the previous iterate is finite, so a non-finite change shows in the new norms
-        const bool nf = !isfinite(py + vy);
-        fr |= ((ok ? 0 : 1) | (nf ? 2 : 0) | (lo ? 0 : 4)) << (4 * r);
-    }
-    if (!node_ok) fr = 0;
-    // OR over the strip's 16 nodes (the lanes of one row group)
-    fr = pc_row_or16(fr);
-    // lane i < 16 returns the flag of local IC i = (i & 3) + 4 (i >> 2), held by the lanes
-    // of row group i & 3 in element i >> 2
-    return (__shfl(fr, 16 * (L.lane & 3)) >> (4 * ((L.lane >> 2) & 3))) & 7;
-}
-
-// Epilogue of an 8-IC job's product (node-row layout: element (3h + cb, r) is comp 2cb + hi
-// of node pc_node(L, h, r) of IC l % 8): y_new = y0 + w2 acc (INCR: yc + w2 acc), the
-// position and velocity
-// change norms summed over the lane pair (l, l ^ 8) that shares the IC's components, and
-// the stopping-rule flags OR-ed over the lane's nodes and its partner's.  The caller ORs
-// the four row groups.
-template <int PAIRS, int NP, bool SW, bool INCR = false>
-static __device__ __forceinline__ int pc_row_epilogue(const double* sY0, const double (&yc)[6][4],
-                                                      f64x4 (&acc)[6], double w2, const PcTol& tl, int N,
-                                                      const PcLane& L)
-{
-    constexpr int T = PcShape<PAIRS, NP>::T;
-    const int hi = L.hi;
-    const int my_m = pc_ic(L, 0);
-    int flag = 0;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, h, r);
-            double dd[3], yy[3];
-#pragma unroll
-            for (int cb = 0; cb < 3; ++cb) {
-                const double base = INCR ? yc[3 * h + cb][r] : sY0[(2 * cb + hi) * T + my_m];
-                const double yn = base + w2 * acc[3 * h + cb][r];
-                acc[3 * h + cb][r] = yn;
-                const double d = yn - yc[3 * h + cb][r];
-                dd[cb] = d * d;
-                yy[cb] = yn * yn;
-            }
-            double pd = dd[0] + (hi ? 0.0 : dd[1]);
-            double py = yy[0] + (hi ? 0.0 : yy[1]);
-            double vd = (hi ? dd[1] : 0.0) + dd[2];
-            double vy = (hi ? yy[1] : 0.0) + yy[2];
-            pd += pc_dpp<0x128>(pd);   // lane ^ 8
-            py += pc_dpp<0x128>(py);
-            vd += pc_dpp<0x128>(vd);
-            vy += pc_dpp<0x128>(vy);
-            if (j < N) {
-                const bool ok = pd < fma(tl.ta, py, tl.tb) && vd < fma(tl.ta, vy, tl.tb);
-                const bool lo = !SW || (pd < fma(tl.sa, py, tl.sb) && vd < fma(tl.sa, vy, tl.sb));
-                const bool nf = !isfinite(py + vy);
-                flag |= (ok ? 0 : 1) | (nf ? 2 : 0) | (lo ? 0 : 4);
-            }
-        }
-    }
-    flag |= pc_dpp<0x128>(flag);
-    return flag;
-}
-
-// Increment sweep of the precision schedule: Y_new = Y + w2 K_N dF with
-// dF, the change of F (pc_publish_chord), held in LDS as FP32 (sD, [node][comp 6][IC]
-// with the column swizzle of pc_fcol) and multiplied on the FP32 matrix cores; the sum
-// into Y stays FP64.  The FP32 rounding is relative to the increment, so it shrinks as the
-// sweeps converge instead of leaving a floor at the FP32 precision of Y.  Returns the
-// flags as pc_product.
-template <int PAIRS, int NP>
-static __device__ __forceinline__ int pc_product_incr(const float* sD, gconst_fp kp0f, const double (&yc)[6][4],
-                                                      f64x4 (&acc)[6], double w2, const PcTol& tl, int N,
-                                                      const PcLane& L)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
-    const int lane = L.lane;
-    f32x4 accf[6];
-#pragma unroll
-    for (int b = 0; b < 6; ++b) accf[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (!Sh::WIDE) {
-        // 8-IC jobs: the node-row FP32 product of pc_product (K_N rows permuted in kp0f so
-        // that the f32 result layout matches the f64 one) on dF, added to the iterate
-        gconst_fp kp1f = kp0f + (size_t)NQ * 64;
-        const float* bp = sD + (lane >> 4) * ROW + (lane & 15);
-        pc_kloop<NQ, 3, PcPairF, float>(L.nq, 
-            [&](int q) { return PcPairF{kp0f[q * 64], kp1f[q * 64]}; },
-            [&](int q) { return PcPairF{kp0f[q * 64], kp1f[q * 64]}; },
-            [&](int q, int, float (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) bq[c] = bp[q * 4 * ROW + 16 * c];
-            },
-            [&](const PcPairF& ka, const float (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) accf[c] = mfma16f(ka.a0, bq[c], accf[c]);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) accf[3 + c] = mfma16f(ka.a1, bq[c], accf[3 + c]);
-            });
-#pragma unroll
-        for (int b = 0; b < 6; ++b) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[b][r] = (double)accf[b][r];
-        }
-        int flag = pc_row_epilogue<PAIRS, NP, true, true>(nullptr, yc, acc, w2, tl, N, L);
-        flag |= __shfl_xor(flag, 16);
-        flag |= __shfl_xor(flag, 32);
-        return flag;
-    }
-    // IC rows read in the order perm(i) = i/4 + 4 (i%4), so the f32 result layout puts IC
-    // l/16 + 4r in element r as the f64 one does
-    const int i = lane & 15, pi = (i >> 2) + 4 * (i & 3);
-    const float* bp[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-        bp[u] = sD + (lane >> 4) * ROW + L.grp * 16 + (pi ^ ((4 * u + (lane >> 4)) & 15));
-    pc_kloop<NQ, 6, float, float, 3, 6, 1>(L.nq, 
-        [&](int q) { return kp0f[q * 64]; }, [&](int q) { return kp0f[q * 64]; },
-        [&](int q, int u, float (&bq)[6]) {
-#pragma unroll
-            for (int b = 0; b < 6; ++b) bq[b] = bp[u][q * 4 * ROW + b * T];
-        },
-        [&](float ka, const float (&bq)[6]) {
-#pragma unroll
-            for (int b = 0; b < 6; ++b) accf[b] = mfma16f(bq[b], ka, accf[b]);
-        });
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[b][r] = (double)accf[b][r];
-    }
-    return pc_wide_epilogue<PAIRS, NP, true>(nullptr, yc, acc, w2, tl, N, L);
-}
-
-// y_new = y0 + w2 K_N F on the matrix cores (Sec. 2.2 with A, C and S folded into K_N) for
-// the lane's six blocks, FP64 or (FP32) FP32 products accumulated into FP64; acc receives
-// y_new.  Also evaluates the stopping rule of Sec. 2.2 against the previous iterate yc in
-// squared form (|dr|^2 < tol^2 |r|^2 and the same for v, or without the norms in absolute
-// mode) and returns in lanes 0..15 the flags of IC pc_flag_ic, OR-ed over its nodes:
-// bit 0 = some node not converged, bit 1 = non-finite, bit 2 = some node changed by more
-// than sqrt(sw2) (relative).  WIDE blocks are computed as (K_N F)^T = F^T K_N^T: the F
-// slice is the A operand and the K_N fragment the B operand.  SW: evaluate bit 2.
-template <int PAIRS, int NP, bool FP32 = false, bool SW = true>
-static __device__ __forceinline__ int pc_product(const double* sF, const double* sY0, gconst_dp kp0,
-                                                  const double (&kpre)[8], gconst_fp kp0f,
-                                                  const double (&yc)[6][4], f64x4 (&acc)[6],
-                                                  double w2, const PcTol& tl, int N,
-                                                  const PcLane& L)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
-    const int lane = L.lane;
-#pragma unroll
-    for (int b = 0; b < 6; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-    int flag = 0;
-    if constexpr (FP32) {
-        // FP32 sweep: FP32 fragments of K_N (rows permuted so the f32 result layout matches
-        // the f64 one), FP32 copies of the B operands, FP64 accumulation into y0 below
-        f32x4 accf[6];
-#pragma unroll
-        for (int b = 0; b < 6; ++b) accf[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (Sh::WIDE) {
-            // the f32 result holds A row 4(l/16) + r in element r: reading IC row i from
-            // column perm(i) = i/4 + 4 (i%4) puts IC l/16 + 4r there, as in the f64 layout
-            const int i = lane & 15, pi = (i >> 2) + 4 * (i & 3);
-            const double* bp[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                bp[u] = sF + (lane >> 4) * ROW + L.grp * 16 + (pi ^ ((4 * u + (lane >> 4)) & 15));
-            pc_kloop<NQ, 6, float, float>(L.nq, 
-                [&](int q) { return kp0f[q * 64]; }, [&](int q) { return kp0f[q * 64]; },
-                [&](int q, int u, float (&bq)[6]) {
-#pragma unroll
-                    for (int b = 0; b < 6; ++b) bq[b] = (float)bp[u][q * 4 * ROW + b * T];
-                },
-                [&](float ka, const float (&bq)[6]) {
-#pragma unroll
-                    for (int b = 0; b < 6; ++b) accf[b] = mfma16f(bq[b], ka, accf[b]);
-                });
-        } else {
-            gconst_fp kp1f = kp0f + (size_t)NQ * 64;
-            const double* bp = sF + (lane >> 4) * ROW + (lane & 15);
-            pc_kloop<NQ, 3, PcPairF, float>(L.nq, 
-                [&](int q) { return PcPairF{kp0f[q * 64], kp1f[q * 64]}; },
-                [&](int q) { return PcPairF{kp0f[q * 64], kp1f[q * 64]}; },
-                [&](int q, int, float (&bq)[3]) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) bq[c] = (float)bp[q * 4 * ROW + 16 * c];
-                },
-                [&](const PcPairF& ka, const float (&bq)[3]) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) accf[c] = mfma16f(ka.a0, bq[c], accf[c]);
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) accf[3 + c] = mfma16f(ka.a1, bq[c], accf[3 + c]);
-                });
-        }
-#pragma unroll
-        for (int b = 0; b < 6; ++b) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[b][r] = (double)accf[b][r];
-        }
-    }
-    if constexpr (Sh::WIDE) {
-        // K_N strip streamed from L2 four k-steps ahead; B operands one k-step ahead
-        if constexpr (!FP32) {
-            // row 4q + l/16 of F: its column for IC l%16 depends on q % 4 through the swizzle
-            const double* bp[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                bp[u] = sF + (lane >> 4) * ROW + L.grp * 16 + ((lane & 15) ^ ((4 * u + (lane >> 4)) & 15));
-            pc_kloop<NQ, 6, double, double, 3, 6, 1>(L.nq, 
-                [&](int u) { return kpre[u]; }, [&](int q) { return kp0[q * 64]; },
-                [&](int q, int u, double (&bq)[6]) {
-#pragma unroll
-                    for (int b = 0; b < 6; ++b) bq[b] = bp[u][q * 4 * ROW + b * T];
-                },
-                [&](double ka, const double (&bq)[6]) {
-#pragma unroll
-                    for (int b = 0; b < 6; ++b) acc[b] = mfma16(bq[b], ka, acc[b]);
-                });
-        }
-        return pc_wide_epilogue<PAIRS, NP, false, SW>(sY0, yc, acc, w2, tl, N, L);
-    } else {
-        if constexpr (!FP32) {
-            gconst_dp kp1 = kp0 + (size_t)NQ * 64;
-            const double* bp = sF + (lane >> 4) * ROW + (lane & 15);
-            pc_kloop<NQ, 3, PcPairD, double>(L.nq, 
-                [&](int u) { return PcPairD{kpre[u], kpre[4 + u]}; },
-                [&](int q) { return PcPairD{kp0[q * 64], kp1[q * 64]}; },
-                [&](int q, int, double (&bq)[3]) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) bq[c] = bp[q * 4 * ROW + 16 * c];
-                },
-                [&](const PcPairD& ka, const double (&bq)[3]) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) acc[c] = mfma16(ka.a0, bq[c], acc[c]);
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) acc[3 + c] = mfma16(ka.a1, bq[c], acc[3 + c]);
-                });
-        }
-        flag = pc_row_epilogue<PAIRS, NP, SW>(sY0, yc, acc, w2, tl, N, L);
-    }
-    flag |= __shfl_xor(flag, 16);
-    flag |= __shfl_xor(flag, 32);
-    return flag;
-}
-
-struct PcQuadD {
-    double k0, k1, q0, q1;   // K_N and K2_N fragments of the wave's two strips
-};
-
-// Second-order sweep: the velocity and the position both come from the acceleration
-// columns of F (comps 3..5), v_new = v0 + w2 K_N a and
-// x_new = x0 + w2 v0 (tau_j + 1) + w2^2 K2_N a, with K2_N the double-integration operator
-// (the degree N-2 fit integrated twice, zero value and slope at tau = -1).
-// WIDE shapes: per k step a lane loads the two operators' fragments (kp1: K_N, kp2: K2_N)
-// and three F values, and issues six MFMAs, as the first-order product does.
-// 8-IC jobs (node-row layout, a column block holding comps 2cb and 2cb + 1 of the 8 ICs):
-// block 0 (x, y) is K2_N times (a_x, a_y) and block 2 (v_y, v_z) K_N times (a_y, a_z), but
-// block 1 (z, v_x) needs K2_N for its low half and K_N for its high half, so it takes two
-// MFMAs whose B operands are zero in the other half (read from F's velocity columns, which
-// second-order sweeps keep at zero): four MFMAs per strip and k step against three.
-// tp = tau_j + 1 of the lane's nodes (WIDE: tp[0]; 8-IC jobs: tp[4h + r]).  Flags as
-// pc_product.
-template <int PAIRS, int NP>
-static __device__ __forceinline__ int pc_product2(const double* sF, const double* sY0, gconst_dp kp1,
-                                                   gconst_dp kp2, const double (&kpre)[8],
-                                                   const double (&yc)[6][4], f64x4 (&acc)[6], double w2,
-                                                   const double (&tp)[8], const PcTol& tl, int N, const PcLane& L)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
-    const int lane = L.lane;
-#pragma unroll
-    for (int b = 0; b < 6; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-    if constexpr (!Sh::WIDE) {
-        const int hi = L.hi, m = lane & 7;
-        // per-lane F columns of the four B operands (comp * T + IC; comp 0 is zero)
-        const double* row = sF + (lane >> 4) * ROW;
-        const double* b0 = row + (hi ? 4 : 3) * T + m;   // a_x | a_y
-        const double* b1 = row + (hi ? 0 : 5) * T + m;   // a_z | 0
-        const double* b2 = row + (hi ? 3 : 0) * T + m;   // 0   | a_x
-        const double* b3 = row + (hi ? 5 : 4) * T + m;   // a_y | a_z
-        gconst_dp kp1b = kp1 + (size_t)NQ * 64, kp2b = kp2 + (size_t)NQ * 64;
-        pc_kloop<NQ, 4, PcQuadD, double>(L.nq, 
-            [&](int q) { return PcQuadD{kp1[q * 64], kp1b[q * 64], kp2[q * 64], kp2b[q * 64]}; },
-            [&](int q) { return PcQuadD{kp1[q * 64], kp1b[q * 64], kp2[q * 64], kp2b[q * 64]}; },
-            [&](int q, int, double (&bq)[4]) {
-                const int o = q * 4 * ROW;
-                bq[0] = b0[o];
-                bq[1] = b1[o];
-                bq[2] = b2[o];
-                bq[3] = b3[o];
-            },
-            [&](const PcQuadD& ka, const double (&bq)[4]) {
-                // the two MFMAs into block 1 of a strip are five MFMAs apart
-                acc[0] = mfma16(ka.q0, bq[0], acc[0]);
-                acc[1] = mfma16(ka.q0, bq[1], acc[1]);
-                acc[2] = mfma16(ka.k0, bq[3], acc[2]);
-                acc[3] = mfma16(ka.q1, bq[0], acc[3]);
-                acc[4] = mfma16(ka.q1, bq[1], acc[4]);
-                acc[5] = mfma16(ka.k1, bq[3], acc[5]);
-                acc[1] = mfma16(ka.k0, bq[2], acc[1]);
-                acc[4] = mfma16(ka.k1, bq[2], acc[4]);
-            });
-        // position elements (block 0, and block 1 in the low lane): w2 acc + v0 (tau + 1),
-        // so the common epilogue's y0 + w2 acc gives x0 + w2 v0 (tau + 1) + w2^2 K2_N a
-        const double v0a = sY0[(3 + hi) * T + m], v0z = sY0[5 * T + m];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double t = tp[4 * h + r];
-                acc[3 * h][r] = fma(w2, acc[3 * h][r], t * v0a);
-                acc[3 * h + 1][r] = hi ? acc[3 * h + 1][r] : fma(w2, acc[3 * h + 1][r], t * v0z);
-            }
-        }
-        int flag = pc_row_epilogue<PAIRS, NP, false>(sY0, yc, acc, w2, tl, N, L);
-        flag |= __shfl_xor(flag, 16);
-        flag |= __shfl_xor(flag, 32);
-        return flag;
-    } else {
-        const double tp1 = tp[0];
-        const double* bp[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            bp[u] = sF + (lane >> 4) * ROW + L.grp * 16 + ((lane & 15) ^ ((4 * u + (lane >> 4)) & 15));
-        pc_kloop<NQ, 3, PcPairD, double, 3, 6, 2>(L.nq, 
-            [&](int u) { return PcPairD{kpre[u], kpre[4 + u]}; },
-            [&](int q) { return PcPairD{kp1[q * 64], kp2[q * 64]}; },
-            [&](int q, int u, double (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) bq[c] = bp[u][q * 4 * ROW + (3 + c) * T];
-            },
-            [&](const PcPairD& ka, const double (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[c] = mfma16(bq[c], ka.a1, acc[c]);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[3 + c] = mfma16(bq[c], ka.a0, acc[3 + c]);
-            });
-        // position: x0 + w2 v0 (tau + 1) + w2^2 acc; the common epilogue adds w2 * acc to
-        // its base, so the position blocks become w2 acc + v0 (tau + 1) first
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = pc_ic(L, r);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc[c][r] = fma(w2, acc[c][r], tp1 * sY0[(3 + c) * T + m]);
-        }
-        return pc_wide_epilogue<PAIRS, NP, false, false>(sY0, yc, acc, w2, tl, N, L);
-    }
-}
-
-// Linear change of the point-mass acceleration over a position change, at R points of
-// node j: g = (da/dr)(r) dr = sum over the Sun (at the origin) and the perturbers of
-// mu (3 d (d . dr) / |d|^5 - dr / |d|^3), d the point's offset from the mass (the indirect
-// term does not depend on the position).  mu/|d|^3 as pc_mu_r3, and 1/|d|^2 from the same
-// estimate t of 1/|d|^2 as t (1 + e + e^2), e = 1 - |d|^2 t.  Records in LDS (compact
-// [node][body][3], masses in smu) or, when they do not fit there, double4 (x, y, z, mu)
-// in global memory.
-template <int R, bool ONE_NODE = true>
-static __device__ __forceinline__ void pc_grad_dot_node(const double (&x)[R], const double (&y)[R],
-                                                        const double (&z)[R], const double (&dx)[R],
-                                                        const double (&dy)[R], const double (&dz)[R],
-                                                        const int (&jr)[R], int P, double mu_sun, bool rec_lds,
-                                                        const double* srec, const double* smu, const double4* grec,
-                                                        double (&gx)[R], double (&gy)[R], double (&gz)[R])
-{
-    auto add = [&](int r, double ox, double oy, double oz, double mu) {
-        const double qx = x[r] - ox, qy = y[r] - oy, qz = z[r] - oz;
-        const double q2 = qx * qx + qy * qy + qz * qz;
-        const double yv = __builtin_amdgcn_rsq(q2);
-        const double t = yv * yv;
-        const double e = fma(-q2, t, 1.0);
-        const double inv2 = fma(t, fma(e, e, e), t);
-        const double sd = mu * (yv * t) * fma(e, fma(1.875, e, 1.5), 1.0);
-        const double k = 3.0 * sd * inv2 * (qx * dx[r] + qy * dy[r] + qz * dz[r]);
-        gx[r] += fma(k, qx, -sd * dx[r]);
-        gy[r] += fma(k, qy, -sd * dy[r]);
-        gz[r] += fma(k, qz, -sd * dz[r]);
-    };
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        gx[r] = gy[r] = gz[r] = 0.0;
-        add(r, 0.0, 0.0, 0.0, mu_sun);
-    }
-    // body b's record at node j (ONE_NODE: every point at node jr[0], one read for all)
-    auto rec = [&](int j, int b, double& ox, double& oy, double& oz, double& mu) {
-        if (rec_lds) {
-            const double* q = srec + j * 3 * (P + 1) + 3 * b;
-            ox = q[0];
-            oy = q[1];
-            oz = q[2];
-            mu = smu[b];
-        } else {
-            const double4 q = grec[(size_t)j * (P + 1) + b];
-            ox = q.x;
-            oy = q.y;
-            oz = q.z;
-            mu = q.w;
-        }
-    };
-    for (int b = 0; b < P; ++b) {
-        if constexpr (ONE_NODE) {
-            double ox, oy, oz, mu;
-            rec(jr[0], b, ox, oy, oz, mu);
-#pragma unroll
-            for (int r = 0; r < R; ++r) add(r, ox, oy, oz, mu);
-        } else {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                double ox, oy, oz, mu;
-                rec(jr[r], b, ox, oy, oz, mu);
-                add(r, ox, oy, oz, mu);
-            }
-        }
-    }
-}
-
-// Second-order sweep with integral error feedback.  The sweep's accelerations
-// were taken at the previous position iterate; the position it predicts,
-// x = x0 + w2 v0 (tau_j + 1) + w2^2 K2_N a, changes that iterate by dx, and the linear change
-// of the acceleration over dx, da = (da/dr) dx at the previous iterate, is integrated like
-// the accelerations and added: v_new = v0 + w2 K_N (a + da), x_new = x0 + w2 v0 (tau_j + 1) +
-// w2^2 K2_N (a + da).  da is published in the velocity columns of F, which second-order
-// products do not read, and its product accumulates onto the first one (one barrier in
-// between).  At the fixed point dx vanishes, so the converged iterate is the second-order
-// one.  Flags as pc_product.
-// 8-IC jobs (node-row layout, as pc_product2): the velocity columns hold da, so both
-// products take the zero halves of their mixed operands by select instead of from those
-// columns; each lane forms da at the four points of strip hi, taking the position and
-// change components it lacks from its partner (l ^ 8).
-template <int PAIRS, int NP>
-static __device__ __forceinline__ int pc_product2_fb(double* sF, const double* sY0, gconst_dp kp1, gconst_dp kp2,
-                                                      const double (&kpre)[8], const double (&yc)[6][4],
-                                                      f64x4 (&acc)[6], double w2, const double (&tp)[8],
-                                                      const PcTol& tl, int N, const PcLane& L, int P, double mu_sun,
-                                                      bool rec_lds, const double* sRec, const double* sMu,
-                                                      const double4* grec)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
-    const int lane = L.lane;
-#pragma unroll
-    for (int b = 0; b < 6; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-    if constexpr (!Sh::WIDE) {
-        const int hi = L.hi, m = lane & 7;
-        const double* row = sF + (lane >> 4) * ROW;
-        gconst_dp kp1b = kp1 + (size_t)NQ * 64, kp2b = kp2 + (size_t)NQ * 64;
-        // K2_N and K_N products of the columns c0 = base, c1, c2 (accelerations: base 3;
-        // da: base 0) into the position and velocity blocks, as pc_product2
-        auto product = [&](int base) {
-            const double* b0 = row + (base + hi) * T + m;       // c0 | c1
-            const double* b1 = row + (base + 2) * T + m;        // c2 | 0
-            const double* b2 = row + base * T + m;              // 0  | c0
-            const double* b3 = row + (base + 1 + hi) * T + m;   // c1 | c2
-            pc_kloop<NQ, 4, PcQuadD, double>(L.nq,
-                [&](int q) { return PcQuadD{kp1[q * 64], kp1b[q * 64], kp2[q * 64], kp2b[q * 64]}; },
-                [&](int q) { return PcQuadD{kp1[q * 64], kp1b[q * 64], kp2[q * 64], kp2b[q * 64]}; },
-                [&](int q, int, double (&bq)[4]) {
-                    const int o = q * 4 * ROW;
-                    const double v1 = b1[o], v2 = b2[o];
-                    bq[0] = b0[o];
-                    bq[1] = hi ? 0.0 : v1;
-                    bq[2] = hi ? v2 : 0.0;
-                    bq[3] = b3[o];
-                },
-                [&](const PcQuadD& ka, const double (&bq)[4]) {
-                    acc[0] = mfma16(ka.q0, bq[0], acc[0]);
-                    acc[1] = mfma16(ka.q0, bq[1], acc[1]);
-                    acc[2] = mfma16(ka.k0, bq[3], acc[2]);
-                    acc[3] = mfma16(ka.q1, bq[0], acc[3]);
-                    acc[4] = mfma16(ka.q1, bq[1], acc[4]);
-                    acc[5] = mfma16(ka.k1, bq[3], acc[5]);
-                    acc[1] = mfma16(ka.k0, bq[2], acc[1]);
-                    acc[4] = mfma16(ka.k1, bq[2], acc[4]);
-                });
-        };
-        product(3);
-        // predicted position and its change from the previous iterate: block 3h holds
-        // comp hi of strip h, block 3h + 1 comp 2 in the low lane
-        const double x0a = sY0[hi * T + m], x0z = sY0[2 * T + m];
-        const double v0a = sY0[(3 + hi) * T + m], v0z = sY0[5 * T + m];
-        double xs[4], ys[4], zs[4], ddx[4], ddy[4], ddz[4], gx[4], gy[4], gz[4];
-        int jr[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            double d0[2], d1[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const double t = tp[4 * h + r];
-                d0[h] = (x0a + w2 * fma(w2, acc[3 * h][r], t * v0a)) - yc[3 * h][r];
-                d1[h] = (x0z + w2 * fma(w2, acc[3 * h + 1][r], t * v0z)) - yc[3 * h + 1][r];
-            }
-            // the lane's points are those of strip hi
-            const double s1 = pc_dpp<0x128>(hi ? yc[0][r] : yc[3][r]);   // lo: y(0); hi: x(1)
-            const double s2 = pc_dpp<0x128>(yc[4][r]);                   // hi: z(1)
-            const double g1 = pc_dpp<0x128>(hi ? d0[0] : d0[1]);         // lo: dy(0); hi: dx(1)
-            const double g2 = pc_dpp<0x128>(d1[1]);                      // hi: dz(1)
-            xs[r] = hi ? s1 : yc[0][r];
-            ys[r] = hi ? yc[3][r] : s1;
-            zs[r] = hi ? s2 : yc[1][r];
-            ddx[r] = hi ? g1 : d0[0];
-            ddy[r] = hi ? d0[1] : g1;
-            ddz[r] = hi ? g2 : d1[0];
-            const int j = pc_node(L, hi, r);
-            jr[r] = j < N ? j : N - 1;
-        }
-        pc_grad_dot_node<4, false>(xs, ys, zs, ddx, ddy, ddz, jr, P, mu_sun, rec_lds, sRec, sMu, grec, gx, gy,
-                                   gz);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, hi, r);
-            if (j < N) {
-                double* f = sF + j * ROW + m;
-                f[0 * T] = gx[r];
-                f[1 * T] = gy[r];
-                f[2 * T] = gz[r];
-            }
-        }
-        __syncthreads();   // every node's da published
-        product(0);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double t = tp[4 * h + r];
-                acc[3 * h][r] = fma(w2, acc[3 * h][r], t * v0a);
-                acc[3 * h + 1][r] = hi ? acc[3 * h + 1][r] : fma(w2, acc[3 * h + 1][r], t * v0z);
-            }
-        }
-        int flag = pc_row_epilogue<PAIRS, NP, false>(sY0, yc, acc, w2, tl, N, L);
-        flag |= __shfl_xor(flag, 16);
-        flag |= __shfl_xor(flag, 32);
-        return flag;
-    }
-    const double tp1 = tp[0];
-    const double* bp[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-        bp[u] = sF + (lane >> 4) * ROW + L.grp * 16 + ((lane & 15) ^ ((4 * u + (lane >> 4)) & 15));
-    auto product = [&](int c0) {
-        pc_kloop<NQ, 3, PcPairD, double, 3, 6, 2>(L.nq, 
-            [&](int u) { return PcPairD{kpre[u], kpre[4 + u]}; },
-            [&](int q) { return PcPairD{kp1[q * 64], kp2[q * 64]}; },
-            [&](int q, int u, double (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) bq[c] = bp[u][q * 4 * ROW + (c0 + c) * T];
-            },
-            [&](const PcPairD& ka, const double (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[c] = mfma16(bq[c], ka.a1, acc[c]);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[3 + c] = mfma16(bq[c], ka.a0, acc[3 + c]);
-            });
-    };
-    product(3);
-    // the predicted position, its change from the previous iterate, and da there
-    const int j = pc_node(L, 0, 0);
-    double ddx[4], ddy[4], ddz[4], gx[4], gy[4], gz[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = pc_ic(L, r);
-        double d[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            d[c] = (sY0[c * T + m] + w2 * fma(w2, acc[c][r], tp1 * sY0[(3 + c) * T + m])) - yc[c][r];
-        ddx[r] = d[0];
-        ddy[r] = d[1];
-        ddz[r] = d[2];
-    }
-    const int jj = j < N ? j : N - 1;
-    const int jr[4] = {jj, jj, jj, jj};
-    pc_grad_dot_node<4>(yc[0], yc[1], yc[2], ddx, ddy, ddz, jr, P, mu_sun, rec_lds, sRec, sMu, grec, gx, gy, gz);
-    if (j < N) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            double* f = sF + j * ROW + pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
-            f[0 * T] = gx[r];
-            f[1 * T] = gy[r];
-            f[2 * T] = gz[r];
-        }
-    }
-    __syncthreads();   // every node's da published
-    product(0);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = pc_ic(L, r);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[c][r] = fma(w2, acc[c][r], tp1 * sY0[(3 + c) * T + m]);
-    }
-    return pc_wide_epilogue<PAIRS, NP, false, false>(sY0, yc, acc, w2, tl, N, L);
-}
-
-// acc = K_N^T mu for the lane's six blocks (WIDE shapes, transposed like pc_product): the
-// adjoint product, mu published in sF as [node][comp 6][IC] and kpT the lane's strip of
-// K_N^T fragments.
-template <int PAIRS, int NP>
-static __device__ __forceinline__ void pc_product_adj(const double* sF, gconst_dp kpT, f64x4 (&acc)[6],
-                                                      const PcLane& L)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
-    const int lane = L.lane;
-#pragma unroll
-    for (int b = 0; b < 6; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-    if constexpr (Sh::WIDE) {
-        const double* bp[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            bp[u] = sF + (lane >> 4) * ROW + L.grp * 16 + ((lane & 15) ^ ((4 * u + (lane >> 4)) & 15));
-        pc_kloop<NQ, 6, double, double, 3, 6, 1>(L.nq, 
-            [&](int q) { return kpT[q * 64]; }, [&](int q) { return kpT[q * 64]; },
-            [&](int q, int u, double (&bq)[6]) {
-#pragma unroll
-                for (int b = 0; b < 6; ++b) bq[b] = bp[u][q * 4 * ROW + b * T];
-            },
-            [&](double ka, const double (&bq)[6]) {
-#pragma unroll
-                for (int b = 0; b < 6; ++b) acc[b] = mfma16(bq[b], ka, acc[b]);
-            });
-    } else {
-        // 8-IC jobs: the forward product's node-row form with the K_N^T strips of the
-        // wave's two row blocks; acc[3h + c] is column block c of strip h
-        gconst_dp kpT1 = kpT + (size_t)NQ * 64;
-        const double* bp = sF + (lane >> 4) * ROW + (lane & 15);
-        pc_kloop<NQ, 3, PcPairD, double>(L.nq, 
-            [&](int q) { return PcPairD{kpT[q * 64], kpT1[q * 64]}; },
-            [&](int q) { return PcPairD{kpT[q * 64], kpT1[q * 64]}; },
-            [&](int q, int, double (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) bq[c] = bp[q * 4 * ROW + 16 * c];
-            },
-            [&](const PcPairD& ka, const double (&bq)[3]) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[c] = mfma16(ka.a0, bq[c], acc[c]);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[3 + c] = mfma16(ka.a1, bq[c], acc[3 + c]);
-            });
-    }
-}
-
-// OR of the per-wave flags of IC m (written as Flag[wave][lane] by lanes < 16).
-template <int PAIRS, int NP>
-static __device__ __forceinline__ int pc_gather_flags(const int* sFlag, int m)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    int f = 0;
-    if constexpr (Sh::WIDE) {
-        for (int w = m >> 4; w < Sh::W; w += Sh::G16) f |= sFlag[w * 16 + (m & 15)];
-    } else {
-        for (int w = 0; w < Sh::W; ++w) f |= sFlag[w * 16 + m];
-    }
-    return f;
-}
-
-// Dynamics of the lane's (node, IC) pairs from its registers, published with the
-// velocities as the force matrix F = (v, a) of Sec. 2.2 into sF[node][comp'][IC].
-// sRec/sMu: the segment's records in LDS (when rec_lds), grec: the same in global memory.
-// VEL = false (second-order sweeps, which read the accelerations only): the velocity
-// columns are not written (they stay zero from the segment's start, and the 8-IC
-// second-order product reads them as zero B operands).
-template <int PAIRS, int NP, bool FP32 = false, bool VEL = true>
-static __device__ __forceinline__ void pc_publish(double* sF, const double (&yc)[6][4], const PcLane& L,
-                                                  int N, int P, double mu_sun, bool rec_lds,
-                                                  const double* sRec, const double* sMu, const double4* grec)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW;
-    const int hi = L.hi;
-    if constexpr (Sh::WIDE) {
-        // one node, four ICs: the same record index for every point
-        double ax[4], ay[4], az[4];
-        const int j = pc_node(L, 0, 0);
-        const int jj = j < N ? j : N - 1;
-        const int jr[4] = {jj, jj, jj, jj};
-        if (rec_lds && FP32) pc_force_lds32<4>(yc[0], yc[1], yc[2], jr, P, mu_sun, sRec, sMu, ax, ay, az);
-        else if (rec_lds) pc_force_lds_node<4>(yc[0], yc[1], yc[2], jj, P, mu_sun, sRec, sMu, ax, ay, az);
-        else pc_force_glb<4>(yc[0], yc[1], yc[2], jr, P, mu_sun, grec, ax, ay, az);
-        if (j < N) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                double* f = sF + j * ROW + pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
-                if constexpr (VEL) {
-                    f[0 * T] = yc[3][r];
-                    f[1 * T] = yc[4][r];
-                    f[2 * T] = yc[5][r];
-                }
-                f[3 * T] = ax[r];
-                f[4 * T] = ay[r];
-                f[5 * T] = az[r];
-            }
-        }
-    } else {
-        const int my_m = pc_ic(L, 0);
-        // Lane pairs (l, l ^ 8) share the points of one IC: the low lane holds x and z, the
-        // high lane y.  Each lane of the pair takes the force of one strip (hd = hi), so
-        // both do half the work: the low lane gets y of strip 0 from its partner, the high
-        // lane gets x and z of strip 1.
-        double xs[4], ys[4], zs[4], ax[4], ay[4], az[4];
-        int jr[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double s1 = pc_dpp<0x128>(hi ? yc[0][r] : yc[3][r]);   // lane ^ 8
-            const double s2 = pc_dpp<0x128>(yc[4][r]);
-            xs[r] = hi ? s1 : yc[0][r];
-            ys[r] = hi ? yc[3][r] : s1;
-            zs[r] = hi ? s2 : yc[1][r];
-            const int j = pc_node(L, hi, r);
-            jr[r] = j < N ? j : N - 1;
-        }
-        if (rec_lds && FP32) pc_force_lds32<4>(xs, ys, zs, jr, P, mu_sun, sRec, sMu, ax, ay, az);
-        else if (rec_lds) pc_force_lds<4>(xs, ys, zs, jr, P, mu_sun, sRec, sMu, ax, ay, az);
-        else pc_force_glb<4>(xs, ys, zs, jr, P, mu_sun, grec, ax, ay, az);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, hi, r);
-            if (j < N) {
-                double* f = sF + j * ROW + my_m;
-                f[3 * T] = ax[r];
-                f[4 * T] = ay[r];
-                f[5 * T] = az[r];
-            }
-        }
-        if constexpr (VEL) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = pc_node(L, h, r);
-                    if (j < N) {
-                        double* f = sF + j * ROW + my_m;
-                        if (hi) {
-                            f[0 * T] = yc[3 * h + 1][r];   // vx (comp 3)
-                            f[2 * T] = yc[3 * h + 2][r];   // vz (comp 5)
-                        } else {
-                            f[1 * T] = yc[3 * h + 2][r];   // vy (comp 4)
-                        }
-                    }
-                }
-            }
-        }
-    }
-}
-
-// Gravity gradient da/dr of the force model at R points of node j, in FP32, as the six
+// Gravity gradient da/dr of the force model at the lane's points, in FP32, as the six
 // entries (xx, yy, zz, xy, xz, yz) of the symmetric 3x3 matrix: every point mass (the Sun
 // at the origin, the perturbers at their record positions) adds mu (3 d d^T / |d|^5 -
 // I / |d|^3), d the offset of the point from the mass; the indirect term does not depend
@@ -1590,41 +755,36 @@ static __device__ __forceinline__ void pc_publish(double* sF, const double (&yc)
 // the error of G times the distance of the anchor from the solution: d is formed in FP64
 // and then rounded (near a close approach, rounding the positions first would leave an
 // error of 1e-5 in G and of about 1e-12 in the result), the rest is FP32.
-template <int R, bool ONE_NODE = true>
-static __device__ __forceinline__ void pc_grad_lds_node32(const double (&x)[R], const double (&y)[R],
-                                                          const double (&z)[R], const int (&jr)[R], int P,
-                                                          double mu_sun, const double* srec, const double* smu,
-                                                          float (&G)[6][R])
+static __device__ __forceinline__ void pc_grad_lds32(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                     const int (&jn)[2], int P, double mu_sun, const double* srec,
+                                                     const double* smu, float (&G)[6][4])
 {
-    // ONE_NODE: the R points share node jr[0] (WIDE); else point r is at node jr[r]
-    auto rec = [&](int r) { return srec + (ONE_NODE ? jr[0] : jr[r]) * 3 * (P + 1); };
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
+    for (int p = 0; p < 4; ++p) {
 #pragma unroll
-        for (int e = 0; e < 6; ++e) G[e][r] = 0.0f;
+        for (int e = 0; e < 6; ++e) G[e][p] = 0.0f;
     }
-    auto add = [&](int r, float dx, float dy, float dz, float mu) {
-        const float q = __builtin_amdgcn_rsqf(dx * dx + dy * dy + dz * dz);
+    auto add = [&](int p, float dx, float dy, float dz, float mu) __attribute__((always_inline)) {
+        const float q = __builtin_amdgcn_rsqf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
         const float q2 = q * q;
         const float m3 = mu * q * q2;          // mu / |d|^3
         const float m5 = 3.0f * m3 * q2;       // 3 mu / |d|^5
         const float tx = m5 * dx, ty = m5 * dy, tz = m5 * dz;
-        G[0][r] += fmaf(tx, dx, -m3);
-        G[1][r] += fmaf(ty, dy, -m3);
-        G[2][r] += fmaf(tz, dz, -m3);
-        G[3][r] = fmaf(tx, dy, G[3][r]);
-        G[4][r] = fmaf(tx, dz, G[4][r]);
-        G[5][r] = fmaf(ty, dz, G[5][r]);
+        G[0][p] += fmaf(tx, dx, -m3);
+        G[1][p] += fmaf(ty, dy, -m3);
+        G[2][p] += fmaf(tz, dz, -m3);
+        G[3][p] = fmaf(tx, dy, G[3][p]);
+        G[4][p] = fmaf(tx, dz, G[4][p]);
+        G[5][p] = fmaf(ty, dz, G[5][p]);
     };
-    const float ms = (float)mu_sun;
 #pragma unroll
-    for (int r = 0; r < R; ++r) add(r, (float)x[r], (float)y[r], (float)z[r], ms);
+    for (int p = 0; p < 4; ++p) add(p, (float)x[p], (float)y[p], (float)z[p], (float)mu_sun);
     for (int b = 0; b < P; ++b) {
-        const float mu = (float)smu[b];
+        const float mu = (float)smu[4 * b];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double* q = rec(r) + 3 * b;
-            add(r, (float)(x[r] - q[0]), (float)(y[r] - q[1]), (float)(z[r] - q[2]), mu);
+        for (int p = 0; p < 4; ++p) {
+            const double* q = srec + jn[p >> 1] * 3 * (P + 1) + 3 * b;
+            add(p, (float)(x[p] - q[0]), (float)(y[p] - q[1]), (float)(z[p] - q[2]), mu);
         }
     }
 }
@@ -1667,21 +827,18 @@ static __device__ __forceinline__ double4 pc_eih_load(const PcEihRecs& E, int k,
 // minus the Newtonian indirect term.  The term in Phi is 4 Phi / c^2 sum_b mu_b d / rho^3,
 // so one pass over the bodies accumulates Phi, that sum and the rest, and the term is
 // added at the end (the same sum in another order).  e: the segment's records, slot k of
-// node j at e[k ns + j]; point r sits at node jr[r] (ONE_NODE: all at jr[0], one load
-// per record for the R points).
-template <int R, bool ONE_NODE>
+// node j at e[k ns + j].
+template <int R>
 static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const double (&y)[R],
                                                     const double (&z)[R], const double (&vx)[R],
                                                     const double (&vy)[R], const double (&vz)[R],
-                                                    const double4* __restrict__ e, const int (&jr)[R], int ns,
-                                                    int P, double inv_c2, double (&ax)[R], double (&ay)[R],
-                                                    double (&az)[R])
+                                                    const double4* __restrict__ e, int j, int ns, int P, double inv_c2,
+                                                    double (&ax)[R], double (&ay)[R], double (&az)[R])
 {
+#pragma clang fp contract(fast)
     const PcEihRecs E = pc_eih_recs(e, ns);
-    uint32_t vo[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) vo[r] = (uint32_t)jr[ONE_NODE ? 0 : r] * 32u;
-    auto rec = [&](int k, int r) -> double4 { return pc_eih_load(E, k, vo[r]); };
+    const uint32_t vo = (uint32_t)j * 32u;
+    auto rec = [&](int k) -> double4 { return pc_eih_load(E, k, vo); };
     const double c35 = 3.5 * inv_c2;
     double phi[R], v2[R], nx[R], ny[R], nz[R];
 #pragma unroll
@@ -1692,21 +849,16 @@ static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const 
         nx[r] = ny[r] = nz[r] = 0.0;
     }
     // the next body's records are loaded while this one's terms are formed
-    double4 qn = rec(0, 0), wn = rec(1, 0), gn = rec(2, 0);
+    double4 qn = rec(0), wn = rec(1), gn = rec(2);
     for (int b = 0; b <= P; ++b) {
-        double4 q = qn, w = wn, g = gn;
+        const double4 q = qn, w = wn, g = gn;
         if (b < P) {
-            qn = rec(3 * b + 3, 0);
-            wn = rec(3 * b + 4, 0);
-            gn = rec(3 * b + 5, 0);
+            qn = rec(3 * b + 3);
+            wn = rec(3 * b + 4);
+            gn = rec(3 * b + 5);
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (!ONE_NODE && r > 0) {
-                q = rec(3 * b, r);
-                w = rec(3 * b + 1, r);
-                g = rec(3 * b + 2, r);
-            }
             const double mu = w.w;
             const double dx = x[r] - q.x, dy = y[r] - q.y, dz = z[r] - q.z;
             const double i1 = pc_rsqrt_full(dx * dx + dy * dy + dz * dz);
@@ -1730,9 +882,9 @@ static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const 
             az[r] += k1 * dz + k2 * (vz[r] - w.z) + k3 * g.z;
         }
     }
+    const double4 ind = rec(3 * (P + 1));
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const double4 ind = rec(3 * (P + 1), r);
         const double f = 4.0 * inv_c2 * phi[r];
         ax[r] = fma(f, nx[r], ax[r]) - ind.x;
         ay[r] = fma(f, ny[r], ay[r]) - ind.y;
@@ -1740,7 +892,7 @@ static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const 
     }
 }
 
-// Vector-Jacobian product of the relativistic acceleration of pc_force_eih at R points:
+// Vector-Jacobian product of the relativistic acceleration of pc_force_eih at the lane's points:
 // with s = u . a, gr = ds/dr = (da/dr)^T u and gv = ds/dv = (da/dv)^T u (the adjoint's
 // J^T w with u = w_v).  Per body, with d, rho, m3 = mu/rho^3, m5 = 3 mu/rho^5,
 // S = U_b - v^2 - 2 v_b^2 + 4 v.v_b + 3/2 (d.v_b/rho)^2 + 1/2 d.a_b, q = 4 v - 3 v_b and
@@ -1752,21 +904,21 @@ static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const 
 // and the terms through Phi = sum_b mu_b/rho_b, whose gradient is -N with
 // N = sum_b m3 d: gr += -4 e Phi H - 4 e (u.N) N, H = sum_b (m5 (u.d) d - m3 u).  At
 // e = 0 this is the point-mass Hessian product (symmetric in r).  The indirect term does
-// not depend on the state.  Records and node indices as pc_force_eih.
-template <int R, bool ONE_NODE>
-static __device__ __forceinline__ void pc_eih_vjp(const double (&x)[R], const double (&y)[R],
-                                                  const double (&z)[R], const double (&vx)[R],
-                                                  const double (&vy)[R], const double (&vz)[R],
-                                                  const double (&ux)[R], const double (&uy)[R],
-                                                  const double (&uz)[R], const double4* __restrict__ e,
-                                                  const int (&jr)[R], int ns, int P, double inv_c2,
-                                                  double (&grx)[R], double (&gry)[R], double (&grz)[R],
-                                                  double (&gvx)[R], double (&gvy)[R], double (&gvz)[R])
+// not depend on the state.  Records as pc_force_eih, point p at node jn[p / 2].
+static __device__ __forceinline__ void pc_eih_vjp(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                  const double (&vx)[4], const double (&vy)[4],
+                                                  const double (&vz)[4], const double (&ux)[4],
+                                                  const double (&uy)[4], const double (&uz)[4],
+                                                  const double4* __restrict__ e, const int (&jn)[2], int ns, int P,
+                                                  double inv_c2, double (&grx)[4], double (&gry)[4],
+                                                  double (&grz)[4], double (&gvx)[4], double (&gvy)[4],
+                                                  double (&gvz)[4])
 {
+#pragma clang fp contract(fast)
     const PcEihRecs E = pc_eih_recs(e, ns);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t vo = (uint32_t)jr[ONE_NODE ? 0 : r] * 32u;
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t vo = (uint32_t)jn[r >> 1] * 32u;
         auto rec = [&](int k, int) -> double4 { return pc_eih_load(E, k, vo); };
         double phi = 0.0, v2 = vx[r] * vx[r] + vy[r] * vy[r] + vz[r] * vz[r];
         double nx = 0.0, ny = 0.0, nz = 0.0, hx = 0.0, hy = 0.0, hz = 0.0;
@@ -1822,232 +974,712 @@ static __device__ __forceinline__ void pc_eih_vjp(const double (&x)[R], const do
         gvz[r] = inv_c2 * bz;
     }
 }
-
-// Publish F = (v, a) with the relativistic acceleration.  erec: the segment's records,
-// pc_eih_rec(P) slots of N double4.  WIDE shapes: a lane's four points share node j.
-// 8-column shapes: as in pc_publish, lane pairs (l, l ^ 8) hold the points of one IC (the
-// low lane x, z, vy, the high lane y, vx, vz) and each lane evaluates one strip (hd = hi),
-// taking the three components it lacks from its partner.
-template <int PAIRS, int NP>
-static __device__ __forceinline__ void pc_publish_eih(double* sF, const double (&yc)[6][4], const PcLane& L,
-                                                      int N, int P, const double4* erec, double inv_c2)
+// Software-pipelined k loop of a 16x16x4 product over nq steps (a multiple of 4, at most
+// NQ, at least 8 when NQ is; NQ fixes the layout of the operands).  The A operand of step q
+// (a K_N fragment, read from L2) is loaded DK steps ahead into a ring of DK registers, the
+// B operands (LDS) one step ahead into two buffers, and the loop body is unrolled DK
+// times, so both rings rotate by register renaming.  A register move out of a ring would
+// make the wave wait for the load it copies right after issuing it.
+// loadB(q, q % 4, buffer) gets the phase as a compile-time constant after unrolling;
+// loadA0(u) supplies the first DK A operands (registers kept across calls, or loads).
+// SG_DS / SG_MFMA / SG_VMEM > 0 pin the order of one step in the steady-state loop for
+// the scheduler: the B reads of the next step, this step's MFMAs, then the A read DK
+// steps ahead (left to itself, the scheduler sinks the reads below the MFMAs that free
+// their registers, and the wave then waits on each read right after issuing it).
+template <int NQ, class AT, class BT, int SG_DS = 0, int SG_MFMA = 0, int SG_VMEM = 0, class LA0,
+          class LA, class LB, class MM>
+static __device__ __forceinline__ void pc_kloop(int nq, LA0 loadA0, LA loadA, LB loadB, MM mma)
 {
-    using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW;
-    if constexpr (Sh::WIDE) {
-        const int j = pc_node(L, 0, 0);
-        if (j >= N) return;
-        const int jr[4] = {j, j, j, j};
-        double ax[4], ay[4], az[4];
-        pc_force_eih<4, true>(yc[0], yc[1], yc[2], yc[3], yc[4], yc[5], erec, jr, N, P, inv_c2, ax, ay, az);
+    constexpr int DK = 4;
+    static_assert(NQ % DK == 0, "k steps must be a multiple of the A ring depth");
+    AT ka[DK];
+    BT bb[2];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            double* f = sF + j * ROW + pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
-            f[0 * T] = yc[3][r];
-            f[1 * T] = yc[4][r];
-            f[2 * T] = yc[5][r];
-            f[3 * T] = ax[r];
-            f[4 * T] = ay[r];
-            f[5 * T] = az[r];
-        }
-    } else {
-        const int hi = L.hi;
-        const int my_m = pc_ic(L, 0);
-        double xs[4], ys[4], zs[4], us[4], vs[4], ws[4], ax[4], ay[4], az[4];
-        int jr[4];
+    for (int u = 0; u < DK; ++u) ka[u] = loadA0(u);
+    loadB(0, 0, bb[0]);
+    auto steps = [&](int q0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double e1 = pc_dpp<0x128>(hi ? yc[0][r] : yc[3][r]);   // lane ^ 8
-            const double e2 = pc_dpp<0x128>(hi ? yc[1][r] : yc[4][r]);
-            const double e3 = pc_dpp<0x128>(hi ? yc[2][r] : yc[5][r]);
-            xs[r] = hi ? e1 : yc[0][r];
-            ys[r] = hi ? yc[3][r] : e1;
-            zs[r] = hi ? e2 : yc[1][r];
-            us[r] = hi ? yc[4][r] : e2;
-            vs[r] = hi ? e3 : yc[2][r];
-            ws[r] = hi ? yc[5][r] : e3;
-            const int j = pc_node(L, hi, r);
-            jr[r] = j < N ? j : N - 1;
-        }
-        pc_force_eih<4, false>(xs, ys, zs, us, vs, ws, erec, jr, N, P, inv_c2, ax, ay, az);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, hi, r);
-            if (j < N) {
-                double* f = sF + j * ROW + my_m;
-                f[3 * T] = ax[r];
-                f[4 * T] = ay[r];
-                f[5 * T] = az[r];
+        for (int u = 0; u < DK; ++u) {
+            loadB(q0 + u + 1, (u + 1) & 3, bb[(u + 1) & 1]);
+            mma(ka[u], bb[u & 1]);
+            ka[u] = loadA(q0 + u + DK);
+            if constexpr (SG_MFMA > 0) {
+                __builtin_amdgcn_sched_group_barrier(0x100, SG_DS, 0);     // DS reads
+                __builtin_amdgcn_sched_group_barrier(0x008, SG_MFMA, 0);   // MFMA
+                __builtin_amdgcn_sched_group_barrier(0x020, SG_VMEM, 0);   // VMEM reads
             }
         }
+    };
+    // the first DK steps outside the loop: their products start from the caller's
+    // accumulators directly (a zero start becomes the MFMA's inline constant instead of
+    // register moves on every sweep)
+    if constexpr (NQ > DK) steps(0);
+    auto rest = [&](int n) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int q0 = DK; q0 < n - DK; q0 += DK) steps(q0);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int u = 0; u < DK; ++u) {   // the last DK steps load nothing past the end
+            if (u + 1 < DK) loadB(n - DK + u + 1, (u + 1) & 3, bb[(u + 1) & 1]);
+            mma(ka[u], bb[u & 1]);
+        }
+    };
+    // a job whose nodes fill every k step keeps the compile-time bound (constant B
+    // offsets in the last steps); a shorter one runs to its own bound, one value per wave
+    // (a scalar, which keeps the loop and the B addresses off the vector registers)
+    if constexpr (NQ > 2 * DK) {
+        if (nq < NQ) {
+            rest(__builtin_amdgcn_readfirstlane(nq));
+            return;
+        }
+    }
+    rest(NQ);
+}
+// ---------------------------------------------------------------------------
+// Products
+// ---------------------------------------------------------------------------
+// Integration from -1 of a function sampled at the mirrored nodes of a pair (l: node i, r: node
+// N-1-i): with s = F_l + F_r and d = F_l - F_r the even and the odd part of F,
+//   y_l = y0 + w2 (U s + O d),   y_r = y0 + w2 (W + O d - U s),
+// where U and O hold (K[i][p] +- K[i][N-1-p]) / 2 and W = sum_p w_p s_p, the integral over the
+// whole segment (w: U's row of the last node; the middle node of an odd count is its own
+// mirror: F_l = F_r, its column of U and w is halved and its column of O zero).  Two products of
+// half the size in each direction: half the MFMAs of y0 + w2 K_N F, which is what bounds a
+// sweep (v_mfma_f64_16x16x4 takes 64 cycles of a SIMD, an FP64 VALU instruction between 4 and
+// 5, and nothing else issues beside the MFMA).  Whole products before and this after: 4096
+// Venus ICs (128 nodes, 8 segments) 2.07 -> 1.51 ms, the uneven 65536-IC batch 157.8 -> 107.1
+// ms, 13509 relativistic ICs of 200 nodes 11.7 -> 7.3 ms, gradients of 16384 ICs 17.9 -> 13.4 ms.
+// W comes from the same operands: each lane adds w_p s_p over its k rows (one VALU multiply-add
+// per block and k step), and one MFMA against ones adds the four k rows and leaves the sum in
+// the result layout.  Taking W from the strip that holds the last node instead would need a
+// barrier between the product and the epilogue.
+
+typedef float pc_f2v __attribute__((ext_vector_type(2)));
+
+// A strip's fragments of one operator: the strip's address is one value per wave (scalar
+// registers) and a load adds only the lane's byte offset.  With one 64-bit address per k step
+// in vector registers those addresses were spilled, and every reload from scratch waited for
+// the fragments still in flight.
+template <class V>
+struct PcFrag {
+    gconst_cp base;
+    uint32_t vo;
+    __device__ __forceinline__ V operator[](int q) const
+    {
+        gconst_cp p = base + (size_t)q * (64 * sizeof(V));
+        asm volatile("" : "+s"(p));   // the scalar sum stays one: base + vo is not formed per lane
+        return *(const __attribute__((address_space(1))) V*)(p + vo);
+    }
+};
+typedef PcFrag<pc_d2v> PcFragD;
+typedef PcFrag<pc_f2v> PcFragF;
+template <int PAIRS, int NP, class F>
+static __device__ __forceinline__ F pc_frag(const void* op, const PcLane& L)
+{
+    constexpr uint32_t V = sizeof(F{}[0]) * 64;
+    return F{pc_wave_base(static_cast<const char*>(op) + (size_t)L.strip * PcShape<PAIRS, NP>::NQ * V),
+             (uint32_t)L.lane * (V / 64)};
+}
+
+// The first four FP64 operator fragments of the lane's strip, loaded before the barrier that
+// precedes the product, which then starts without waiting on L2.
+static __device__ __forceinline__ void pc_kpre_load(const PcFragD& kp, pc_d2v (&kpre)[4])
+{
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = pc_node(L, h, r);
-                if (j < N) {
-                    double* f = sF + j * ROW + my_m;
-                    if (hi) {
-                        f[0 * T] = yc[3 * h + 1][r];   // vx (comp 3)
-                        f[2 * T] = yc[3 * h + 2][r];   // vz (comp 5)
-                    } else {
-                        f[1 * T] = yc[3 * h + 2][r];   // vy (comp 4)
-                    }
-                }
+    for (int u = 0; u < 4; ++u) kpre[u] = kp[u];
+}
+
+// Stopping-rule thresholds in fma form, fixed per segment: a squared change d2 passes
+// against the squared norm y2 when d2 < a y2 + b, with (a, b) = (tol^2, 0) for the relative
+// rule and (0, tol^2) for the absolute one (the same comparisons as d2 < tol^2 y2 and
+// d2 < tol^2 for finite norms, with no branch on the mode).  (sa, sb): the same for the
+// precision switch.
+struct PcTol {
+    double ta, tb, sa, sb;
+};
+static __device__ __forceinline__ PcTol pc_tol(int tol_mode, double t2, double sw2)
+{
+    return tol_mode == 0 ? PcTol{t2, 0.0, sw2, 0.0} : PcTol{0.0, t2, 0.0, sw2};
+}
+
+// Stopping-rule flags (Sec. 2.2) of the lane's ICs, new iterate y against the previous one yc,
+// OR-ed over the strip's nodes: bits 4e..4e+2 belong to the lane's e-th IC (bit 0 some node not
+// converged, bit 1 non-finite, bit 2 some node changed by more than the switch, SW only).
+template <int PAIRS, int NP, bool SW>
+static __device__ __forceinline__ int pc_flags(const double (&yc)[6][4], const f64x4 (&y)[6], const PcTol& tl,
+                                               const PcLane& L)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    int fr = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            double pd = 0.0, py = 0.0, vd = 0.0, vy = 0.0;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const double p = y[3 * h + b][r], v = y[3 * h + b][2 + r];
+                const double dp = p - yc[3 * h + b][r], dv = v - yc[3 * h + b][2 + r];
+                pd = b == 0 ? dp * dp : fma(dp, dp, pd);
+                py = b == 0 ? p * p : fma(p, p, py);
+                vd = b == 0 ? dv * dv : fma(dv, dv, vd);
+                vy = b == 0 ? v * v : fma(v, v, vy);
+            }
+            const bool ok = pd < fma(tl.ta, py, tl.tb) && vd < fma(tl.ta, vy, tl.tb);
+            const bool lo = !SW || (pd < fma(tl.sa, py, tl.sb) && vd < fma(tl.sa, vy, tl.sb));
+            // the previous iterate is finite, so a non-finite change shows in the new norms
+            const bool nf = !isfinite(py + vy);
+            fr |= ((ok ? 0 : 1) | (nf ? 2 : 0) | (lo ? 0 : 4)) << (4 * (Sh::PAR ? r : 2 * h + r));
+        }
+    }
+    if (!L.ok) fr = 0;
+    return pc_row_or16(fr);   // the 16 rows of the strip: the lanes of one row group
+}
+
+// The flags of the wave's columns into sFlag[wave][column].
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_put_flags(int* sFlag, int fr, const PcLane& L)
+{
+    if (L.c < PcShape<PAIRS, NP>::E) sFlag[L.wave * 16 + pc_col<PAIRS, NP>(L, L.c)] = (fr >> (4 * L.c)) & 7;
+}
+
+// OR of the per-wave flags of IC m of the job.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ int pc_gather_flags(const int* sFlag, int m)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    const int* f0 = sFlag + (m / Sh::COLS) * Sh::STRIPS * 16 + m % Sh::COLS;
+    int f = 0;
+#pragma unroll
+    for (int s = 0; s < Sh::STRIPS; ++s) f |= f0[s * 16];
+    return f;
+}
+
+// acc <- base + w2 (the product), acc holding the blocks of U s (h = 0) and O d (h = 1), wd
+// those of W; base: y0 (sY0), or the previous iterate (INCR, an increment sweep).
+template <int PAIRS, int NP, bool INCR>
+static __device__ __forceinline__ void pc_combine(const double* sY0, const double (&yc)[6][4], f64x4 (&acc)[6],
+                                                  const f64x4 (&wd)[3], double w2, const PcLane& L)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    constexpr int T = Sh::T;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = b + 3 * (r >> 1);
+            double bl, br;
+            if constexpr (INCR) {
+                bl = yc[b][r];
+                br = yc[3 + b][r];
+            } else {
+                bl = sY0[c * T + pc_ic<PAIRS, NP>(L, 0, r & 1)];
+                br = Sh::PAR ? bl : sY0[c * T + pc_ic<PAIRS, NP>(L, 1, r & 1)];
+            }
+            const double u = acc[b][r], o = acc[3 + b][r];
+            if constexpr (Sh::PAR) {
+                acc[b][r] = fma(w2, u, fma(w2, o, bl));
+                acc[3 + b][r] = fma(-w2, u, fma(w2, o, fma(w2, wd[b][r], br)));
+            } else {
+                acc[b][r] = fma(w2, u, bl);
+                acc[3 + b][r] = fma(w2, o, br);
             }
         }
     }
+}
+
+// One k step's operands from LDS: F's even and odd parts (or the two eights' values) of the
+// three blocks, and the row's weight.
+struct PcB {
+    pc_d2v f[3];
+    double w;
+};
+struct PcBf {
+    pc_f2v f[3];
+    float w;
+};
+
+// Lane's base of the k rows 4q + u (u = q % 4): the place of its A-operand row i in F, in
+// pairs of values; a k step adds 4 rows, a block 16.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_kbase(const PcLane& L, int i, int (&bp)[4])
+{
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        bp[u] = L.g * (PcShape<PAIRS, NP>::ROW / 2) + L.grp * 48 + (i ^ ((4 * u + L.g) & 15));
+}
+
+// acc <- U s | O d (or K F of the two eights), wd <- W: the FP64 product of the lane's six
+// blocks, F in sF, the strip's fragments kp (kpre: its first four).
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_mm(const double* sF, const double* sWt, const PcFragD& kp,
+                                             const pc_d2v (&kpre)[4], f64x4 (&acc)[6], f64x4 (&wd)[3], const PcLane& L)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    constexpr int STEP = 4 * Sh::ROW / 2;
+    const pc_d2v* f = reinterpret_cast<const pc_d2v*>(sF);
+    int bp[4];
+    pc_kbase<PAIRS, NP>(L, L.c, bp);
+    double ws[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int b = 0; b < 6; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    pc_kloop<Sh::NQ, pc_d2v, PcB, Sh::PAR ? 4 : 3, 6, 1>(
+        L.nq, [&](int u) { return kpre[u]; }, [&](int q) { return kp[q]; },
+        [&](int q, int u, PcB& B) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) B.f[b] = f[bp[u] + q * STEP + 16 * b];
+            if constexpr (Sh::PAR) B.w = sWt[4 * q + L.g];
+        },
+        [&](const pc_d2v& k, const PcB& B) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) acc[b] = mfma16(B.f[b].x, k.x, acc[b]);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) acc[3 + b] = mfma16(B.f[b].y, k.y, acc[3 + b]);
+            if constexpr (Sh::PAR) {
+#pragma unroll
+                for (int b = 0; b < 3; ++b) ws[b] = fma(B.w, B.f[b].x, ws[b]);
+            }
+        });
+    if constexpr (Sh::PAR) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b) wd[b] = mfma16(ws[b], 1.0, f64x4{0.0, 0.0, 0.0, 0.0});
+    }
+}
+
+// The same on the FP32 matrix cores, from FP32 values (increment sweeps: the change of F) or
+// from FP64 ones rounded here (FP32 Picard sweeps).  The f32 result holds A row 4(l/16) + r in
+// element r, the f64 one row l/16 + 4r: reading IC row i from row i/4 + 4 (i%4) puts the same
+// IC in the same lane and element.
+template <int PAIRS, int NP, class V>
+static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, const PcFragF& kp, f64x4 (&acc)[6],
+                                               f64x4 (&wd)[3], const PcLane& L)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    constexpr int STEP = 4 * Sh::ROW / 2;
+    typedef V v2 __attribute__((ext_vector_type(2)));
+    const v2* f = reinterpret_cast<const v2*>(sF);
+    int bp[4];
+    pc_kbase<PAIRS, NP>(L, (L.c >> 2) + 4 * (L.c & 3), bp);
+    float ws[3] = {0.0f, 0.0f, 0.0f};
+    f32x4 a[6];
+#pragma unroll
+    for (int b = 0; b < 6; ++b) a[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    pc_kloop<Sh::NQ, pc_f2v, PcBf, Sh::PAR ? 4 : 3, 6, 1>(
+        L.nq, [&](int q) { return kp[q]; }, [&](int q) { return kp[q]; },
+        [&](int q, int u, PcBf& B) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const v2 t = f[bp[u] + q * STEP + 16 * b];
+                B.f[b] = pc_f2v{(float)t.x, (float)t.y};
+            }
+            if constexpr (Sh::PAR) B.w = (float)sWt[4 * q + L.g];
+        },
+        [&](const pc_f2v& k, const PcBf& B) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) a[b] = mfma16f(B.f[b].x, k.x, a[b]);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) a[3 + b] = mfma16f(B.f[b].y, k.y, a[3 + b]);
+            if constexpr (Sh::PAR) {
+#pragma unroll
+                for (int b = 0; b < 3; ++b) ws[b] = fmaf(B.w, B.f[b].x, ws[b]);
+            }
+        });
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[b][r] = (double)a[b][r];
+    }
+    if constexpr (Sh::PAR) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const f32x4 t = mfma16f(ws[b], 1.0f, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+#pragma unroll
+            for (int r = 0; r < 4; ++r) wd[b][r] = (double)t[r];
+        }
+    }
+}
+
+// One sweep's product: acc receives y0 + w2 K_N F, FP64; returns the flags (pc_flags).
+template <int PAIRS, int NP, bool SW>
+static __device__ __forceinline__ int pc_product(const double* sF, const double* sY0, const double* sWt, const PcFragD& kp,
+                                                 const pc_d2v (&kpre)[4], const double (&yc)[6][4], f64x4 (&acc)[6],
+                                                 double w2, const PcTol& tl, const PcLane& L)
+{
+    f64x4 wd[3];
+    pc_mm<PAIRS, NP>(sF, sWt, kp, kpre, acc, wd, L);
+    pc_combine<PAIRS, NP, false>(sY0, yc, acc, wd, w2, L);
+    return pc_flags<PAIRS, NP, SW>(yc, acc, tl, L);
+}
+
+// FP32 sweeps of the precision schedule, accumulated into FP64: a Picard sweep (from the FP64
+// F) or an increment sweep, Y_new = Y + w2 K_N dF with dF, the change of F
+// (pc_publish_chord), held in LDS as FP32 in F's layout.  An increment's FP32 rounding is
+// relative to it, so it shrinks as the sweeps converge instead of leaving a floor at the FP32
+// precision of Y.
+template <int PAIRS, int NP, bool INCR>
+static __device__ __forceinline__ int pc_product32(const double* sF, const double* sY0, const double* sWt,
+                                                   const PcFragF& kp, const double (&yc)[6][4], f64x4 (&acc)[6], double w2,
+                                                   const PcTol& tl, const PcLane& L)
+{
+    f64x4 wd[3];
+    if constexpr (INCR) pc_mm32<PAIRS, NP>(reinterpret_cast<const float*>(sF), sWt, kp, acc, wd, L);
+    else pc_mm32<PAIRS, NP>(sF, sWt, kp, acc, wd, L);
+    pc_combine<PAIRS, NP, INCR>(sY0, yc, acc, wd, w2, L);
+    return pc_flags<PAIRS, NP, true>(yc, acc, tl, L);
+}
+
+// Second-order sweep: velocity and position both from the accelerations,
+// v = v0 + w2 K_N a and x = x0 + w2 v0 (tau + 1) + w2^2 K2_N a, with K2_N the double-integration
+// operator (the degree N-2 fit integrated twice, zero value and slope at tau = -1).  With the
+// same even and odd parts s and d of a, and U2, O2, w2 those of K2_N,
+//   x_l = x0 + w2 v0 (1 + tau_l) + w2^2 (U2 s + O2 d),
+//   x_r = x0 + w2 v0 (1 - tau_l) + w2^2 (U2 s - tau_l W + C - O2 d),   C = sum_p w2_p d_p.
+// F's blocks hold (a_x | a_y), (a_z | 0) and (0 | a_z) in their low and high eights: a_z's
+// position needs K2_N and its velocity K_N in one block, so it takes two MFMAs with half an
+// operand zero, eight per k step against the first-order sweep's six.
+struct PcQuad {
+    pc_d2v k, q;   // K_N and K2_N fragments
+};
+struct PcB2 {
+    pc_d2v f[3];
+    double w, c;
+};
+struct PcSo {
+    f64x4 k[2], q[2], z[2];   // per h: K_N (a_x | a_y), K2_N (a_x | a_y), (K2_N a_z | K_N a_z)
+    f64x4 w[2], c[2];         // W and C of blocks 0 and 1
+};
+
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_mm2(const double* sF, const double* sWt, const PcFragD& kp1, const PcFragD& kp2,
+                                              PcSo& A, const PcLane& L)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    constexpr int STEP = 4 * Sh::ROW / 2;
+    const pc_d2v* f = reinterpret_cast<const pc_d2v*>(sF);
+    int bp[4];
+    pc_kbase<PAIRS, NP>(L, L.c, bp);
+    double ws[2] = {0.0, 0.0}, cs[2] = {0.0, 0.0};
+    pc_kloop<Sh::NQ, PcQuad, PcB2>(
+        L.nq, [&](int q) { return PcQuad{kp1[q], kp2[q]}; },
+        [&](int q) { return PcQuad{kp1[q], kp2[q]}; },
+        [&](int q, int u, PcB2& B) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) B.f[b] = f[bp[u] + q * STEP + 16 * b];
+            if constexpr (Sh::PAR) {
+                B.w = sWt[4 * q + L.g];
+                B.c = sWt[Sh::KR + 4 * q + L.g];
+            }
+        },
+        [&](const PcQuad& k, const PcB2& B) {
+            A.z[0] = mfma16(B.f[1].x, k.q.x, A.z[0]);
+            A.z[1] = mfma16(B.f[1].y, k.q.y, A.z[1]);
+            A.q[0] = mfma16(B.f[0].x, k.q.x, A.q[0]);
+            A.q[1] = mfma16(B.f[0].y, k.q.y, A.q[1]);
+            A.k[0] = mfma16(B.f[0].x, k.k.x, A.k[0]);
+            A.k[1] = mfma16(B.f[0].y, k.k.y, A.k[1]);
+            A.z[0] = mfma16(B.f[2].x, k.k.x, A.z[0]);
+            A.z[1] = mfma16(B.f[2].y, k.k.y, A.z[1]);
+            if constexpr (Sh::PAR) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    ws[b] = fma(B.w, B.f[b].x, ws[b]);
+                    cs[b] = fma(B.c, B.f[b].y, cs[b]);
+                }
+            }
+        });
+    if constexpr (Sh::PAR) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            A.w[b] = mfma16(ws[b], 1.0, A.w[b]);
+            A.c[b] = mfma16(cs[b], 1.0, A.c[b]);
+        }
+    }
+}
+
+// New iterate of a second-order sweep from its products (tp = tau + 1 of the lane's node 0).
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_combine2(const double* sY0, const PcSo& A, f64x4 (&y)[6], double w2, double tp,
+                                                   const PcLane& L)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    constexpr int T = Sh::T;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            // comp b of IC r: (a_x | a_y) blocks hold comp 1 in their high eight
+            const int k = b == 1 ? 2 + r : r;
+            const double e = b < 2 ? A.q[0][k] : A.z[0][r], o2 = b < 2 ? A.q[1][k] : A.z[1][r];
+            const double u = b < 2 ? A.k[0][k] : A.z[0][2 + r], o = b < 2 ? A.k[1][k] : A.z[1][2 + r];
+            const int m0 = pc_ic<PAIRS, NP>(L, 0, r), m1 = pc_ic<PAIRS, NP>(L, 1, r);
+            const double x0 = sY0[b * T + m0], v0 = sY0[(3 + b) * T + m0];
+            if constexpr (Sh::PAR) {
+                const double W = b < 2 ? A.w[0][k] : A.w[1][r], C = b < 2 ? A.c[0][k] : A.c[1][r];
+                y[b][r] = fma(w2, fma(w2, e + o2, tp * v0), x0);
+                y[3 + b][r] = fma(w2, fma(w2, fma(1.0 - tp, W, e + C) - o2, (2.0 - tp) * v0), x0);
+                y[b][2 + r] = fma(w2, u, fma(w2, o, v0));
+                y[3 + b][2 + r] = fma(-w2, u, fma(w2, o, fma(w2, W, v0)));
+            } else {
+                const double x1 = sY0[b * T + m1], v1 = sY0[(3 + b) * T + m1];
+                y[b][r] = fma(w2, fma(w2, e, tp * v0), x0);
+                y[3 + b][r] = fma(w2, fma(w2, o2, tp * v1), x1);
+                y[b][2 + r] = fma(w2, u, v0);
+                y[3 + b][2 + r] = fma(w2, o, v1);
+            }
+        }
+    }
+}
+
+// Publish a change or value (two halves h) of the accelerations in the second-order layout.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_put2(double* sF, const double (&ax)[4], const double (&ay)[4],
+                                               const double (&az)[4], const PcLane& L);
+
+template <int PAIRS, int NP>
+static __device__ __forceinline__ int pc_product2(const double* sF, const double* sY0, const double* sWt,
+                                                  const PcFragD& kp1, const PcFragD& kp2, const double (&yc)[6][4],
+                                                  f64x4 (&acc)[6], double w2, double tp, const PcTol& tl,
+                                                  const PcLane& L)
+{
+    PcSo A = {};
+    pc_mm2<PAIRS, NP>(sF, sWt, kp1, kp2, A, L);
+    pc_combine2<PAIRS, NP>(sY0, A, acc, w2, tp, L);
+    return pc_flags<PAIRS, NP, false>(yc, acc, tl, L);
+}
+
+// Second-order sweep with integral error feedback.  The sweep's accelerations were taken at
+// the previous position iterate; the position it predicts changes that iterate by dx, and the
+// linear change of the acceleration over dx, da = (da/dr) dx at the previous iterate, is
+// integrated like the accelerations and added: v_new = v0 + w2 K_N (a + da),
+// x_new = x0 + w2 v0 (tau + 1) + w2^2 K2_N (a + da).  da takes a's place in F once every wave
+// has read it, and its product accumulates onto the first one.  At the fixed point dx vanishes,
+// so the converged iterate is the second-order one.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ int pc_product2_fb(double* sF, const double* sY0, const double* sWt, const PcFragD& kp1,
+                                                     const PcFragD& kp2, const double (&yc)[6][4], f64x4 (&acc)[6],
+                                                     double w2, double tp, const PcTol& tl, const PcLane& L, int P,
+                                                     double mu_sun, bool rec_lds, const double* sRec,
+                                                     const double* sMu, const double4* grec)
+{
+    PcSo A = {};
+    pc_mm2<PAIRS, NP>(sF, sWt, kp1, kp2, A, L);
+    pc_combine2<PAIRS, NP>(sY0, A, acc, w2, tp, L);
+    double x[3][4], dx[3][4], gx[4], gy[4], gz[4];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            x[b][p] = yc[3 * (p >> 1) + b][p & 1];
+            dx[b][p] = acc[3 * (p >> 1) + b][p & 1] - x[b][p];
+        }
+    }
+    pc_grad_dot(x[0], x[1], x[2], dx[0], dx[1], dx[2], L.jn, P, mu_sun, rec_lds, sRec, sMu, grec, gx, gy, gz);
+    __syncthreads();   // every wave is done reading the accelerations
+    if (L.ok) pc_put2<PAIRS, NP>(sF, gx, gy, gz, L);
+    __syncthreads();   // every node's da published
+    pc_mm2<PAIRS, NP>(sF, sWt, kp1, kp2, A, L);
+    pc_combine2<PAIRS, NP>(sY0, A, acc, w2, tp, L);
+    return pc_flags<PAIRS, NP, false>(yc, acc, tl, L);
+}
+
+// w = K_N^T mu at the lane's nodes: with the published pairs (mu_l - mu_r, mu_l + mu_r) and
+// the transposed operators, g_s = U^T (mu_l - mu_r) + w R, R = sum over the rows of mu_r, and
+// g_d = O^T (mu_l + mu_r), w_l = g_s + g_d and w_r = g_s - g_d (at a middle node w_l is g_s:
+// its columns are whole here, and its mu_r is zero).  wr: half the row weight w of the lane's
+// own row; R's sum over the k rows is formed like pc_mm's W and enters by one MFMA per block.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_product_adj(const double* sF, const PcFragD& kpT, double wr, f64x4 (&acc)[6],
+                                                      const PcLane& L)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    constexpr int STEP = 4 * Sh::ROW / 2;
+    const pc_d2v* f = reinterpret_cast<const pc_d2v*>(sF);
+    int bp[4];
+    pc_kbase<PAIRS, NP>(L, L.c, bp);
+    double rs[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int b = 0; b < 6; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    pc_kloop<Sh::NQ, pc_d2v, PcB, 3, 6, 1>(
+        L.nq, [&](int q) { return kpT[q]; }, [&](int q) { return kpT[q]; },
+        [&](int q, int u, PcB& B) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) B.f[b] = f[bp[u] + q * STEP + 16 * b];
+        },
+        [&](const pc_d2v& k, const PcB& B) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b) acc[b] = mfma16(B.f[b].x, k.x, acc[b]);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) acc[3 + b] = mfma16(B.f[b].y, k.y, acc[3 + b]);
+            if constexpr (Sh::PAR) {
+#pragma unroll
+                for (int b = 0; b < 3; ++b) rs[b] += B.f[b].y - B.f[b].x;   // 2 mu_r
+            }
+        });
+    if constexpr (Sh::PAR) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const f64x4 s = mfma16(rs[b], wr, acc[b]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double d = acc[3 + b][r];
+                acc[b][r] = s[r] + d;
+                acc[3 + b][r] = s[r] - d;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Publishing
+// ---------------------------------------------------------------------------
+// One component of the lane's points into F's block b, eight `half`: the even and odd parts of
+// the pair (or the two eights' values).
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_put(double* sF, int b, int half, int r, double vl, double vr, const PcLane& L)
+{
+    const int i = 8 * half + L.g + 4 * r;
+    pc_d2v* f = reinterpret_cast<pc_d2v*>(sF) + pc_unit<PAIRS, NP>(L.row, L.grp, b, i);
+    *f = PcShape<PAIRS, NP>::PAR ? pc_d2v{vl + vr, vl - vr} : pc_d2v{vl, vr};
+}
+
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_put2(double* sF, const double (&ax)[4], const double (&ay)[4],
+                                               const double (&az)[4], const PcLane& L)
+{
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        pc_put<PAIRS, NP>(sF, 0, 0, r, ax[r], ax[2 + r], L);
+        pc_put<PAIRS, NP>(sF, 0, 1, r, ay[r], ay[2 + r], L);
+        pc_put<PAIRS, NP>(sF, 1, 0, r, az[r], az[2 + r], L);
+        pc_put<PAIRS, NP>(sF, 2, 1, r, az[r], az[2 + r], L);
+    }
+}
+
+// F = (v, a) of the lane's points into sF.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_put_f(double* sF, const double (&yc)[6][4], const double (&ax)[4],
+                                                const double (&ay)[4], const double (&az)[4], const PcLane& L)
+{
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+#pragma unroll
+        for (int b = 0; b < 3; ++b) pc_put<PAIRS, NP>(sF, b, 0, r, yc[b][2 + r], yc[3 + b][2 + r], L);
+        pc_put<PAIRS, NP>(sF, 0, 1, r, ax[r], ax[2 + r], L);
+        pc_put<PAIRS, NP>(sF, 1, 1, r, ay[r], ay[2 + r], L);
+        pc_put<PAIRS, NP>(sF, 2, 1, r, az[r], az[2 + r], L);
+    }
+}
+
+// Position component b of the lane's points from the iterate.
+static __device__ __forceinline__ void pc_points(const double (&yc)[6][4], int b, double (&x)[4])
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p) x[p] = yc[3 * (p >> 1) + b][p & 1];
+}
+
+// Dynamics of the lane's (node, IC) pairs from its registers, published as the force matrix
+// F = (v, a) of Sec. 2.2.  sRec/sMu: the segment's records in LDS (when rec_lds), grec: the
+// same in global memory.  SO: second-order sweeps, the accelerations only, in their layout.
+template <int PAIRS, int NP, bool FP32 = false, bool SO = false>
+static __device__ __forceinline__ void pc_publish(double* sF, const double (&yc)[6][4], const PcLane& L, int P,
+                                                  double mu_sun, bool rec_lds, const double* sRec, const double* sMu,
+                                                  const double4* grec)
+{
+    double x[4], y[4], z[4], ax[4], ay[4], az[4];
+    pc_points(yc, 0, x);
+    pc_points(yc, 1, y);
+    pc_points(yc, 2, z);
+    if (rec_lds && FP32) pc_force_lds32(x, y, z, L.jn, P, mu_sun, sRec, sMu, ax, ay, az);
+    else if (rec_lds) pc_force_lds(x, y, z, L.jn, P, mu_sun, sRec, sMu, ax, ay, az);
+    else pc_force_glb(x, y, z, L.jn, P, mu_sun, grec, ax, ay, az);
+    if (!L.ok) return;
+    if constexpr (SO) pc_put2<PAIRS, NP>(sF, ax, ay, az, L);
+    else pc_put_f<PAIRS, NP>(sF, yc, ax, ay, az, L);
+}
+
+// The same with the relativistic acceleration.  erec: the segment's records, pc_eih_rec(P)
+// slots of N double4; one pass over the bodies per node of the lane.
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_publish_eih(double* sF, const double (&yc)[6][4], const PcLane& L, int N,
+                                                      int P, const double4* erec, double inv_c2)
+{
+    double ax[4], ay[4], az[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const double x[2] = {yc[3 * h][0], yc[3 * h][1]}, y[2] = {yc[3 * h + 1][0], yc[3 * h + 1][1]},
+                     z[2] = {yc[3 * h + 2][0], yc[3 * h + 2][1]}, u[2] = {yc[3 * h][2], yc[3 * h][3]},
+                     v[2] = {yc[3 * h + 1][2], yc[3 * h + 1][3]}, w[2] = {yc[3 * h + 2][2], yc[3 * h + 2][3]};
+        double a0[2], a1[2], a2[2];
+        pc_force_eih<2>(x, y, z, u, v, w, erec, L.jn[h], N, P, inv_c2, a0, a1, a2);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            ax[2 * h + r] = a0[r];
+            ay[2 * h + r] = a1[r];
+            az[2 * h + r] = a2[r];
+        }
+    }
+    if (L.ok) pc_put_f<PAIRS, NP>(sF, yc, ax, ay, az, L);
 }
 
 // Publish for an increment sweep.  The increment of F = (v, a) from the last
 // change dy of the iterate, to first order: dF = (dv, G dr), with G the gravity gradient
-// at the anchor, the iterate after the last FP64 sweep (ANCHOR: evaluated here at yc and
-// kept in sG, [node][6][IC] FP32, read back only by the same lane; else read from sG).
-// dF goes to sD rounded to FP32.  act[r]: the lane's IC r iterates (others publish zero,
-// so that no stale or non-finite value reaches the product).
+// at the anchor, the iterate after the last FP64 sweep (anchor: evaluated here at yc and
+// kept in sG, [entry 6][point 4][thread] FP32; else read from sG).
+// dF goes to sD rounded to FP32, in F's layout.  act[p]: the IC of the lane's point p iterates
+// (others publish zero, so that no stale or non-finite value reaches the product; dy is zero
+// for them).
 template <int PAIRS, int NP>
 static __device__ __forceinline__ void pc_publish_chord(float* sD, float* sG, const double (&yc)[6][4],
-                                                        const float (&dy)[6][4], const int (&act)[4],
-                                                        bool anchor, const PcLane& L, int N, int P,
-                                                        double mu_sun, const double* sRec, const double* sMu)
+                                                        const float (&dy)[6][4], const int (&act)[4], bool anchor,
+                                                        const PcLane& L, int P, double mu_sun, const double* sRec,
+                                                        const double* sMu)
 {
     using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, ROW = Sh::ROW;
-    if constexpr (!Sh::WIDE) {
-        // 8-IC jobs (node-row layout, lane pairs sharing an IC's components): each lane
-        // stores dv for its own velocity components at its eight nodes, and forms G dr at
-        // the four points of strip hi (G from the anchor's position, kept in sG by the same
-        // lane), taking the components it lacks from its partner as pc_publish does
-        const int hi = L.hi, m = pc_ic(L, 0);
-        const bool on = act[0];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = pc_node(L, h, r);
-                float* d = sD + j * ROW + m;
-                const bool ok = j < N;   // rows past N stay zero (they meet zero operator columns)
-#pragma unroll
-                for (int cb = 0; cb < 3; ++cb) {
-                    const int c = 2 * cb + hi;
-                    if (c >= 3) d[(c - 3) * T] = ok ? dy[3 * h + cb][r] : 0.0f;
-                }
-            }
-        }
-        double xs[4], ys[4], zs[4];
-        float rx[4], ry[4], rz[4];
-        int jr[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double e1 = pc_dpp<0x128>(hi ? yc[0][r] : yc[3][r]);   // lo: y(0); hi: x(1)
-            const double e2 = pc_dpp<0x128>(yc[4][r]);                   // hi: z(1)
-            const float f1 = pc_dpp<0x128>(hi ? dy[0][r] : dy[3][r]);    // lo: dy(0); hi: dx(1)
-            const float f2 = pc_dpp<0x128>(dy[4][r]);                    // hi: dz(1)
-            xs[r] = hi ? e1 : yc[0][r];
-            ys[r] = hi ? yc[3][r] : e1;
-            zs[r] = hi ? e2 : yc[1][r];
-            rx[r] = hi ? f1 : dy[0][r];
-            ry[r] = hi ? dy[3][r] : f1;
-            rz[r] = hi ? f2 : dy[1][r];
-            const int j = pc_node(L, hi, r);
-            jr[r] = j < N ? j : N - 1;
-        }
-        float G[6][4];
-        if (anchor) {
-            pc_grad_lds_node32<4, false>(xs, ys, zs, jr, P, mu_sun, sRec, sMu, G);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float* g = sG + pc_node(L, hi, r) * 6 * T + m;
-#pragma unroll
-                for (int e = 0; e < 6; ++e) {
-                    G[e][r] = on ? G[e][r] : 0.0f;
-                    g[e * T] = G[e][r];
-                }
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float* g = sG + pc_node(L, hi, r) * 6 * T + m;
-#pragma unroll
-                for (int e = 0; e < 6; ++e) G[e][r] = g[e * T];
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, hi, r);
-            const bool ok = j < N;
-            float* d = sD + j * ROW + m;
-            d[3 * T] = ok ? fmaf(G[0][r], rx[r], fmaf(G[3][r], ry[r], G[4][r] * rz[r])) : 0.0f;
-            d[4 * T] = ok ? fmaf(G[3][r], rx[r], fmaf(G[1][r], ry[r], G[5][r] * rz[r])) : 0.0f;
-            d[5 * T] = ok ? fmaf(G[4][r], rx[r], fmaf(G[5][r], ry[r], G[2][r] * rz[r])) : 0.0f;
-        }
-        return;
-    }
-    const int j = pc_node(L, 0, 0);
-    if (j >= N) {   // rows past N meet zero operator columns: keep them zero (no stale NaN bits)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float* d = sD + j * ROW + pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
-#pragma unroll
-            for (int c = 0; c < 6; ++c) d[c * T] = 0.0f;
-        }
-        return;
-    }
+    pc_f2v* d = reinterpret_cast<pc_f2v*>(sD);
     float G[6][4];
+    float* g = sG + L.wave * 64 + L.lane;
     if (anchor) {
-        pc_grad_lds_node32<4>(yc[0], yc[1], yc[2], {j, j, j, j}, P, mu_sun, sRec, sMu, G);
+        double x[4], y[4], z[4];
+        pc_points(yc, 0, x);
+        pc_points(yc, 1, y);
+        pc_points(yc, 2, z);
+        pc_grad_lds32(x, y, z, L.jn, P, mu_sun, sRec, sMu, G);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float* g = sG + j * 6 * T + pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
+        for (int e = 0; e < 6; ++e) {
 #pragma unroll
-            for (int e = 0; e < 6; ++e) {
-                G[e][r] = act[r] ? G[e][r] : 0.0f;
-                g[e * T] = G[e][r];
+            for (int p = 0; p < 4; ++p) {
+                G[e][p] = act[p] ? G[e][p] : 0.0f;
+                g[(4 * e + p) * Sh::NT] = G[e][p];
             }
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float* g = sG + j * 6 * T + pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
+        for (int e = 0; e < 6; ++e) {
 #pragma unroll
-            for (int e = 0; e < 6; ++e) G[e][r] = g[e * T];
+            for (int p = 0; p < 4; ++p) G[e][p] = g[(4 * e + p) * Sh::NT];
         }
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        float* d = sD + j * ROW + pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
-        const float rx = dy[0][r], ry = dy[1][r], rz = dy[2][r];
-        d[0 * T] = dy[3][r];
-        d[1 * T] = dy[4][r];
-        d[2 * T] = dy[5][r];
-        d[3 * T] = fmaf(G[0][r], rx, fmaf(G[3][r], ry, G[4][r] * rz));
-        d[4 * T] = fmaf(G[3][r], rx, fmaf(G[1][r], ry, G[5][r] * rz));
-        d[5 * T] = fmaf(G[4][r], rx, fmaf(G[5][r], ry, G[2][r] * rz));
+    for (int r = 0; r < 2; ++r) {
+        float F[6][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int p = 2 * h + r;
+            const float rx = dy[3 * h][r], ry = dy[3 * h + 1][r], rz = dy[3 * h + 2][r];
+            F[0][h] = dy[3 * h][2 + r];
+            F[1][h] = dy[3 * h + 1][2 + r];
+            F[2][h] = dy[3 * h + 2][2 + r];
+            F[3][h] = fmaf(G[0][p], rx, fmaf(G[3][p], ry, G[4][p] * rz));
+            F[4][h] = fmaf(G[3][p], rx, fmaf(G[1][p], ry, G[5][p] * rz));
+            F[5][h] = fmaf(G[4][p], rx, fmaf(G[5][p], ry, G[2][p] * rz));
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            // rows past the last one meet zero operator columns: zero, not stale bits
+            const float l = L.ok ? F[c][0] : 0.0f, q = L.ok ? F[c][1] : 0.0f;
+            d[pc_unit<PAIRS, NP>(L.row, L.grp, c % 3, 8 * (c / 3) + L.g + 4 * r)] =
+                Sh::PAR ? pc_f2v{l + q, l - q} : pc_f2v{l, q};
+        }
     }
 }
 
-// Load the lane's share of a [node][comp][IC] array with row stride `row` and comp stride
-// `cs` (WIDE: yc[c][r]; T == 8: yc[3h + cb][r] = comp 2cb + hi); SWZ: an LDS array with
-// the column swizzle of pc_fcol.
-template <int PAIRS, int NP, bool SWZ = false, class Ptr>
-static __device__ __forceinline__ void pc_load_share(Ptr base, size_t row, size_t cs, double (&yc)[6][4],
-                                                     const PcLane& L, int N)
-{
-    using Sh = PcShape<PAIRS, NP>;
-#pragma unroll
-    for (int h = 0; h < Sh::H; ++h) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, h, r);
-            const int jj = j < N ? j : N - 1;
-            const int m = SWZ ? pc_fcol<PAIRS, NP>(jj, pc_ic(L, r)) : pc_ic(L, r);
-            if constexpr (Sh::WIDE) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c) yc[c][r] = base[jj * row + c * cs + m];
-            } else {
-#pragma unroll
-                for (int cb = 0; cb < 3; ++cb) yc[3 * h + cb][r] = base[jj * row + (2 * cb + L.hi) * cs + m];
-            }
-        }
-    }
-}
+#pragma clang fp contract(fast)

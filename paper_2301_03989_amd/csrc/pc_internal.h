@@ -3,14 +3,13 @@
 // Layout conventions (all FP64):
 //  * A "job" is one workgroup's share of one group: T consecutive ICs of the group,
 //    all NP (padded) nodes, all segments.  NP * T == PAIRS, PAIRS in {1024, 2048}.
-//  * Inside a workgroup the state of a job lives in LDS as [node j][comp 9][IC m]:
-//    comps 0..5 = x y z vx vy vz of the current iterate, comps 6..8 = the
-//    acceleration at the nodes.  Comps 3..8 are the force matrix F of Sec. 2.2
-//    (velocity and acceleration), so y_new = y0 + w2 * K_N F is one product with
-//    a contiguous right-hand side per node row.
-//  * K_N is stored as MFMA A-operand fragments: kfrag[strip][q][lane] =
-//    K_N[16*strip + lane%16][4*q + lane/16], zero-padded to NP x NP, so one wave
-//    reads a 16x4 slice with one coalesced 512-byte load.
+//  * A job's F = (v, a) lives in LDS by rows (PcShape in pc_device.h): from 32 padded nodes on
+//    a row is the pair of mirrored nodes i and N-1-i and holds the even and the odd part of F,
+//    at 16 it is one node.  KR = NP / 2 (16) rows.
+//  * The operators are stored as MFMA fragments of two values, [KR/16][KR/4][64 lanes][2] for
+//    entry (16 strip + lane%16, 4q + lane/16): the even and odd halves of K_N (pc_product),
+//    zero-padded, or K_N twice at 16 padded nodes.  One wave reads a k step's 16x4 slices of
+//    both with one coalesced 1 KiB load.
 //  * Ephemeris records: for every (group, segment, node) the positions and
 //    parameters of the perturbers, rec[p] = (x, y, z, mu_p), followed by the
 //    indirect term rec[P] = (sum_p mu_p r_p/|r_p|^3, 0).
@@ -25,11 +24,11 @@ struct PcGroupDev {
     double t0, h, tol;         // segment s spans [t0 + (s0 + s) h, t0 + (s0 + s + 1) h]
     int64_t ic_offset, n_ic;
     int64_t rec_offset;        // first ephemeris record of the group (S * N records)
-    const double* kfrag;       // [NP/16][NP/4][64]
-    const float* kfrag32;      // FP32 copy in the same fragment order
-    const float* kfrag32p;     // FP32 copy, rows permuted for the f32 MFMA result layout
-    const double* kfragT;      // fragments of K_N^T (adjoint)
-    const double* kfrag2;      // fragments of the double-integration operator K2_N (second order)
+    const double* kpair;       // K_N
+    const float* kpair32;      // FP32 copy
+    const double* kpairT;      // K_N^T (adjoint)
+    const double* kpair2;      // the double-integration operator K2_N (second order)
+    const double* wts;         // [3][KR] row weights: w, w2 (pc_product, pc_mm2), half of the adjoint's w
     const double* tau;         // [NP] CGL nodes, zero past N
     int32_t N, NP, T, S;
     int32_t s0;                // first segment of the group on the t0 + k h grid (a call that
@@ -72,7 +71,7 @@ struct PcParams {
     int32_t precision;          // 0 FP64; 1 FP32 sweeps, then FP64
     int32_t max_fp32;           // cap on FP32 sweeps per segment
     int32_t conv;               // PC_CONV_PER_IC or PC_CONV_GROUP_MAX (plain path only)
-    int32_t order;              // 1: first-order sweeps; 2: second-order sweeps (WIDE shapes)
+    int32_t order;              // 1: first-order sweeps; 2: second-order sweeps
     int32_t feedback;           // order 2: integral error feedback
     double switch2;             // squared relative change below which a job leaves FP32
     int32_t* counters;          // [0] ICs with a not-converged segment, [1] non-finite ICs

@@ -161,11 +161,10 @@ int pc_launch_copy_runs(const PcCopyDev* list, int64_t n, void* stream)
 
 // One job: T = PAIRS/NP ICs of one group, all segments.
 //
-// Ownership: every wave owns six 16x16 blocks of the iterate (node rows x component
-// columns) for the whole job.  It keeps its blocks of the current iterate in registers
-// (in the MFMA result layout), computes the dynamics for the (node, IC) pairs it owns
-// straight from them, and publishes only the force matrix F = (v, a) to LDS, where the
-// product y_new = y0 + w2 K_N F reads it as the B operand.
+// Ownership: every wave owns six 16x16 blocks of the iterate (PcShape) for the whole job.  It
+// keeps its blocks of the current iterate in registers (in the MFMA result layout), computes
+// the dynamics for the (node, IC) pairs it owns straight from them, and publishes only the
+// force matrix F = (v, a) to LDS, where the product y_new = y0 + w2 K_N F reads it.
 // The workgroup's LDS arena, one per job shape (file scope, so that the non-inlined job
 // bodies below address it as LDS).
 __shared__ PcSmem<2048> g_smem2048;
@@ -189,9 +188,26 @@ static __device__ __forceinline__ void pc_stage_records(const double4* grec, int
         sm.Rec[3 * i + 1] = q.y;
         sm.Rec[3 * i + 2] = q.z;
         if (i < P) {
-            sm.Mu[i] = q.w;
-            sm.Mu[PC_MAX_PERT_DEV + i] = 1.5 * q.w;
-            sm.Mu[2 * PC_MAX_PERT_DEV + i] = 1.875 * q.w;
+            sm.Mu[4 * i] = q.w;
+            sm.Mu[4 * i + 1] = 1.5 * q.w;
+            sm.Mu[4 * i + 2] = 1.875 * q.w;
+        }
+    }
+}
+
+// The rows of F past the last one holding nodes are zero (they meet zero operator columns,
+// which a stale NaN would survive), and so are the unused halves of the second-order blocks.
+template <int PAIRS, int NP, bool SO>
+static __device__ __forceinline__ void pc_clear_rows(double* sF, int N)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    const int M = Sh::PAR ? (N + 1) >> 1 : N;
+    for (int i = M * Sh::ROW + (int)threadIdx.x; i < Sh::KR * Sh::ROW; i += Sh::NT) sF[i] = 0.0;
+    if constexpr (SO) {
+        for (int k = threadIdx.x; k < M * Sh::GN * 16; k += Sh::NT) {
+            const int i = k & 15, q = k >> 4;
+            const int u = pc_unit<PAIRS, NP>(q / Sh::GN, q % Sh::GN, i < 8 ? 2 : 1, i);
+            reinterpret_cast<pc_d2v*>(sF)[u] = pc_d2v{0.0, 0.0};
         }
     }
 }
@@ -204,14 +220,15 @@ static __device__ __forceinline__ void pc_stage_records(const double4* grec, int
 // jobs carry none of its registers).
 template <int PAIRS, int NP, bool MIXED = false, bool EIH = false, int SO = 0>
 static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const PcGroupDev& g, int n, int64_t ic0,
-                                                        int s, PcSmem<PAIRS>& sm, const PcLane& L, gconst_dp kp0,
+                                                        int s, PcSmem<PAIRS>& sm, PcLane L, const PcFragD& kp,
                                                         double (&yc)[6][4], gi32p iters_out, int& had_notconv,
                                                         int rec_cap = PcSmem<PAIRS>::REC)
 {
     using Sh = PcShape<PAIRS, NP>;
-    constexpr int NT = Sh::NT, T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
+    constexpr int NT = Sh::NT, T = Sh::T;
     double* sF = sm.F;
     double* sY0 = sm.Y0;
+    const double* sWt = pc_weights<PAIRS, NP>(sm);
     const int tid = threadIdx.x;
     const int N = g.N;
     const int P = p.n_pert;
@@ -228,47 +245,41 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
     const double4* grec = reinterpret_cast<const double4*>(p.recs) +
                           (size_t)(g.rec_offset + (int64_t)s * N) * (P + 1);
     if (rec_lds) pc_stage_records<PAIRS>(grec, N, P, sm);
-    // initial guess at every (node, IC) pair: warm (Kepler) or cold start, Sec. 2.1,
-    // staged through the F area as [node][comp 6][IC]
-    {
-        const int pm = tid % T;
-        double y0[6];
-#pragma unroll
-        for (int c = 0; c < 6; ++c) y0[c] = sY0[c * T + pm];
-        const bool warm = p.init == 0 && !sm.Dead[pm];
-        const bool hot = p.init == 2 && !sm.Dead[pm] && pm < n;   // the caller's node states
+    // initial guess at the lane's points: warm (Kepler) or cold start, Sec. 2.1, each staged in
+    // the lane's own part of the F area (one call site, no private array)
 #pragma unroll 1
-        for (int pr = tid; pr < PAIRS; pr += NT) {
-            const int j = pr / T;
-            double y[6];
-            bool have = false;
-            if (hot && j < N) {
-                const double* gp = p.guess + (((size_t)(ic0 + pm) * p.iters_stride + s) * p.nodes_stride + j) * 6;
-                bool fin = true;
+    for (int q = 0; q < 4; ++q) {
+        const int j = q < 2 ? L.jn[0] : L.jn[1];
+        const int m = pc_ic<PAIRS, NP>(L, q >> 1, q & 1);
+        double y0[6], y[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) y0[c] = sY0[c * T + m];
+        bool have = false;
+        if (!sm.Dead[m]) {
+            if (p.init == 2 && m < n) {   // the caller's node states
+                const gconst_dp gp =
+                    pc_gcd(p.guess) + (((size_t)(ic0 + m) * p.iters_stride + s) * p.nodes_stride + j) * 6;
+                have = true;
 #pragma unroll
                 for (int c = 0; c < 6; ++c) {
                     y[c] = gp[c];
-                    fin = fin && isfinite(y[c]);
+                    have = have && isfinite(y[c]);
                 }
-                have = fin;
-            } else if (j < N && warm) {
+            } else if (p.init == 0) {
                 have = pc_kepler(y0, w2 * (pc_gcd(g.tau)[j] + 1.0), y);
             }
-            if (!have) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c) y[c] = y0[c];
-            }
-            double* dst = sF + j * ROW + pc_fcol<PAIRS, NP>(j, pm);
-#pragma unroll
-            for (int c = 0; c < 6; ++c) dst[c * T] = y[c];
         }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) sF[(q * 6 + c) * NT + tid] = have ? y[c] : y0[c];
     }
-    __syncthreads();
-    pc_load_share<PAIRS, NP, true>(static_cast<const double*>(sF), ROW, T, yc, L, N);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) yc[3 * (q >> 1) + c % 3][(q & 1) + 2 * (c / 3)] = sF[(q * 6 + c) * NT + tid];
+    }
     if (tid < T) sm.Active[tid] = (tid < n) && !sm.Dead[tid];
-    __syncthreads();   // staging read before F is rebuilt
-    for (int i = tid; i < 6 * PAIRS; i += NT) sF[i] = 0.0;
-    __syncthreads();
+    __syncthreads();   // staging read before F is built
+    pc_clear_rows<PAIRS, NP, SO != 0>(sF, N);
     // precision schedule (uniform per job): an FP32 phase first when asked, then FP64
     // sweeps.  Sweep kinds: 0 FP64 Picard sweep, 1 FP32 Picard sweep (jobs whose records do
     // not fit in LDS), 2 FP32 increment sweep (after one FP64 sweep; records in LDS).
@@ -301,72 +312,65 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
     int stage = (MIXED && incr) ? -1 : 0;
     float* sD = reinterpret_cast<float*>(sF);                // increment sweeps: dF, FP32
     float* sG = reinterpret_cast<float*>(sF + 3 * PAIRS);    // increment sweeps: G at the anchor
-    int act[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) act[r] = sm.Active[pc_ic(L, r)];
     // relativistic model: the segment's records of the major bodies
     const double4* erec = nullptr;
     if constexpr (EIH)
         erec = reinterpret_cast<const double4*>(p.recs_eih) + (size_t)(g.rec_offset + (int64_t)s * N) * pc_eih_rec(P);
-    if (act[0] | act[1] | act[2] | act[3]) {
+    // which of the lane's ICs iterate (point p = 2h + r), and whether any of the wave's group
+    // does: the waves of a group without an IC (few ICs, or all stopped) only keep the barriers
+    int act[4];
+    auto read_active = [&]() -> bool {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) act[q] = sm.Active[pc_ic<PAIRS, NP>(L, q >> 1, q & 1)];
+        return __any(act[0] | act[1] | act[2] | act[3]);
+    };
+    bool busy = read_active();
+    if (busy) {
         if constexpr (EIH) pc_publish_eih<PAIRS, NP>(sF, yc, L, N, P, erec, p.inv_c2);
-        else if (MIXED && mode == 1) pc_publish<PAIRS, NP, MIXED>(sF, yc, L, N, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
-        else pc_publish<PAIRS, NP, false, SO == 0>(sF, yc, L, N, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+        else if (MIXED && mode == 1)
+            pc_publish<PAIRS, NP, MIXED>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+        else pc_publish<PAIRS, NP, false, SO != 0>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
     }
     __syncthreads();
 
-    // FP32 fragments: natural order for the transposed WIDE product, row-permuted otherwise
-    gconst_fp kp0f = (gconst_fp)(Sh::WIDE ? g.kfrag32 : g.kfrag32p) + (size_t)L.strip0 * NQ * 64 + L.lane;
+    const PcFragF kp32 = pc_frag<PAIRS, NP, PcFragF>(g.kpair32, L);
     const int n_it = fixed_iters > 0 ? fixed_iters : max_iter;
-    double kpre[8];
-    pc_kpre_load<PAIRS, NP>(kp0, kpre);
-    // second-order sweeps: the K2_N strip and its first fragments next to K_N's, and the
-    // lane's node offset tau_j + 1 for the x0 + w2 v0 (tau_j + 1) term
-    gconst_dp kp2 = nullptr;
-    double tp[8] = {};
+    // the next product's first fragments, on their way while the waves wait at the barrier
+    pc_d2v kpre[4];
+    if constexpr (SO == 0) pc_kpre_load(kp, kpre);
+    // second-order sweeps: the K2_N strip, and the lane's node offset tau + 1 for the
+    // x0 + w2 v0 (tau + 1) term
+    PcFragD kp2 = {};
+    double tp = 0.0;
     if constexpr (SO) {
-        kp2 = (gconst_dp)g.kfrag2 + (size_t)L.strip0 * NQ * 64 + L.lane;
-        if constexpr (Sh::WIDE) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) kpre[4 + u] = kp2[u * 64];
-            tp[0] = pc_gcd(g.tau)[pc_node(L, 0, 0)] + 1.0;
-        } else {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) tp[4 * h + r] = pc_gcd(g.tau)[pc_node(L, h, r)] + 1.0;
-            }
-        }
+        kp2 = pc_frag<PAIRS, NP, PcFragD>(g.kpair2, L);
+        tp = pc_gcd(g.tau)[L.jn[0]] + 1.0;
     }
     for (int it = 1; it <= n_it; ++it) {
+        L = pc_lane_again<PAIRS, NP>(L, N);
         // (1)-(2) product and stopping-rule flags
         f64x4 acc[6];
-        int flag;
-        if constexpr (MIXED && Sh::WIDE) {
-            if (mode == 2)
-                flag = pc_product_incr<PAIRS, NP>(sD, kp0f, yc, acc, w2, tl, N, L);
-            else
-                flag = pc_product<PAIRS, NP, false>(sF, sY0, kp0, kpre, kp0f, yc, acc, w2, tl, N, L);
-        } else if constexpr (MIXED) {
-            if (mode == 2)
-                flag = pc_product_incr<PAIRS, NP>(sD, kp0f, yc, acc, w2, tl, N, L);
-            else
-                flag = mode == 1 ? pc_product<PAIRS, NP, true>(sF, sY0, kp0, kpre, kp0f, yc, acc, w2, tl, N, L)
-                                 : pc_product<PAIRS, NP, false>(sF, sY0, kp0, kpre, kp0f, yc, acc, w2, tl, N, L);
-        } else if constexpr (SO == 2) {
-            flag = pc_product2_fb<PAIRS, NP>(sF, sY0, kp0, kp2, kpre, yc, acc, w2, tp, tl, N, L, P, mu_sun,
-                                             rec_lds, sm.Rec, sm.Mu, grec);
-        } else if constexpr (SO) {
-            flag = pc_product2<PAIRS, NP>(sF, sY0, kp0, kp2, kpre, yc, acc, w2, tp, tl, N, L);
-        } else {
-            flag = pc_product<PAIRS, NP, false, false>(sF, sY0, kp0, kpre, kp0f, yc, acc, w2, tl, N, L);
+        int flag = 0;
+        if constexpr (SO == 2) {   // holds barriers: every wave
+            flag = pc_product2_fb<PAIRS, NP>(sF, sY0, sWt, kp, kp2, yc, acc, w2, tp, tl, L, P, mu_sun, rec_lds, sm.Rec,
+                                             sm.Mu, grec);
+        } else if (busy) {
+            if constexpr (MIXED) {
+                if (mode == 2) flag = pc_product32<PAIRS, NP, true>(sF, sY0, sWt, kp32, yc, acc, w2, tl, L);
+                else if (mode == 1) flag = pc_product32<PAIRS, NP, false>(sF, sY0, sWt, kp32, yc, acc, w2, tl, L);
+                else flag = pc_product<PAIRS, NP, true>(sF, sY0, sWt, kp, kpre, yc, acc, w2, tl, L);
+            } else if constexpr (SO) {
+                flag = pc_product2<PAIRS, NP>(sF, sY0, sWt, kp, kp2, yc, acc, w2, tp, tl, L);
+            } else {
+                flag = pc_product<PAIRS, NP, false>(sF, sY0, sWt, kp, kpre, yc, acc, w2, tl, L);
+            }
         }
-        if (L.lane < 16) sm.Flag[L.wave * 16 + L.lane] = flag;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) act[r] = sm.Active[pc_ic(L, r)];
+        pc_put_flags<PAIRS, NP>(sm.Flag, flag, L);
+        busy = read_active();
         if constexpr (MIXED) {
             const unsigned long long keep =
-                __ballot(L.lane < 16 && sm.Active[pc_flag_ic<PAIRS, NP>(L)] && (flag & 4));
+                __ballot(L.c < Sh::E && sm.Active[L.grp * Sh::COLS + pc_col<PAIRS, NP>(L, L.c & (Sh::E - 1))] &&
+                         ((flag >> (4 * (L.c & (Sh::E - 1)))) & 4));
             if (L.lane == 0) sm.Keep[L.wave] = keep != 0ull;
         }
         __syncthreads();   // every wave is done reading F; flags complete
@@ -420,46 +424,46 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
         //     increment sweep, the change of F)
         if constexpr (MIXED) {
             if (next_mode == 2 && it < n_it) {
-                float dy[6][4];
+                if (busy) {
+                    float dy[6][4];
 #pragma unroll
-                for (int b = 0; b < 6; ++b) {
+                    for (int b = 0; b < 6; ++b) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        dy[b][r] = act[r] ? (float)(acc[b][r] - yc[b][r]) : 0.0f;
-                        yc[b][r] = act[r] ? acc[b][r] : yc[b][r];
+                        for (int r = 0; r < 4; ++r) {
+                            const int on = act[2 * (b / 3) + (r & 1)];
+                            dy[b][r] = on ? (float)(acc[b][r] - yc[b][r]) : 0.0f;
+                            yc[b][r] = on ? acc[b][r] : yc[b][r];
+                        }
                     }
+                    // after an FP64 sweep the new iterate is the anchor: G evaluated there
+                    pc_publish_chord<PAIRS, NP>(sD, sG, yc, dy, act, mode != 2, L, P, mu_sun, sm.Rec, sm.Mu);
                 }
-                // after an FP64 sweep the new iterate is the anchor: G evaluated there
-                pc_publish_chord<PAIRS, NP>(sD, sG, yc, dy, act, mode != 2, L, N, P, mu_sun, sm.Rec, sm.Mu);
                 fp32 = next32;
                 mode = next_mode;
                 __syncthreads();   // F complete; the active notes visible
                 if (!pc_any_active<PAIRS, NP>(sm)) break;
                 continue;
             }
-        }
-        if constexpr (MIXED) {
             // back to FP64 after increment sweeps: the FP32 arrays left arbitrary bits in the
-            // rows past N of the FP64 view, which meet zero operator columns; clear them
-            if (mode == 2 && N < NP) {
-                for (int i = N * ROW + tid; i < NP * ROW; i += NT) sF[i] = 0.0;
-            }
+            // rows past the last one of the FP64 view
+            if (mode == 2) pc_clear_rows<PAIRS, NP, false>(sF, N);
         }
-        if (act[0] | act[1] | act[2] | act[3]) {
+        if (busy) {
 #pragma unroll
             for (int b = 0; b < 6; ++b) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) yc[b][r] = act[r] ? acc[b][r] : yc[b][r];
+                for (int r = 0; r < 4; ++r) yc[b][r] = act[2 * (b / 3) + (r & 1)] ? acc[b][r] : yc[b][r];
             }
             if (it < n_it) {
                 if constexpr (EIH) pc_publish_eih<PAIRS, NP>(sF, yc, L, N, P, erec, p.inv_c2);
                 else if (MIXED && next_mode == 1)
-                    pc_publish<PAIRS, NP, MIXED>(sF, yc, L, N, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
-                else pc_publish<PAIRS, NP, false, SO == 0>(sF, yc, L, N, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+                    pc_publish<PAIRS, NP, MIXED>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+                else pc_publish<PAIRS, NP, false, SO != 0>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
             }
         }
         fp32 = next32;
         mode = next_mode;
+        if constexpr (SO == 0) pc_kpre_load(kp, kpre);
         __syncthreads();   // F complete; the active notes visible
         if (!pc_any_active<PAIRS, NP>(sm)) break;
     }
@@ -472,7 +476,7 @@ __device__ __attribute__((noinline)) void pc_job(const PcParams& p, const PcJobD
 {
     PcSmem<PAIRS>& sm = pc_smem<PAIRS>();
     using Sh = PcShape<PAIRS, NP>;
-    constexpr int T = Sh::T, NQ = Sh::NQ;
+    constexpr int T = Sh::T;
 
     double* sY0 = sm.Y0;
     const int tid = threadIdx.x;
@@ -496,7 +500,8 @@ __device__ __attribute__((noinline)) void pc_job(const PcParams& p, const PcJobD
         }
         sm.Dead[tid] = !fin;
     }
-    gconst_dp kp0 = (gconst_dp)g.kfrag + (size_t)L.strip0 * NQ * 64 + L.lane;
+    pc_stage_weights<PAIRS, NP>(sm, g.wts);
+    const PcFragD kp = pc_frag<PAIRS, NP, PcFragD>(g.kpair, L);
     __syncthreads();
 
     double yc[6][4];       // the lane's share of the current iterate
@@ -509,36 +514,26 @@ __device__ __attribute__((noinline)) void pc_job(const PcParams& p, const PcJobD
             }
             if (sm.Dead[tid] && g_iters) g_iters[(size_t)ic * istride + s] = -2;
         }
-        pc_segment_solve<PAIRS, NP, MIXED, EIH, SO>(p, g, n, job.ic0, s, sm, L, kp0, yc, g_iters, had_notconv);
+        pc_segment_solve<PAIRS, NP, MIXED, EIH, SO>(p, g, n, job.ic0, s, sm, L, kp, yc, g_iters, had_notconv);
 
         // converged node states of the segment (optional output), chaining (Sec. 2.2)
 #pragma unroll
-        for (int h = 0; h < Sh::H; ++h) {
+        for (int h = 0; h < 2; ++h) {
+            if (!L.ok || (Sh::PAR && h == 1 && !L.two)) continue;
+            const int j = L.jn[h];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = pc_node(L, h, r);
-                const int m = pc_ic(L, r);
-                const bool dead = sm.Dead[m];
-                if (j >= N) continue;
+            for (int r = 0; r < 2; ++r) {
+                const int m = pc_ic<PAIRS, NP>(L, h, r);
                 if (g_nodes && m < n) {
                     const gdp o = g_nodes + (((size_t)(job.ic0 + m) * istride + s) * nstride + j) * 6;
-                    if constexpr (Sh::WIDE) {
 #pragma unroll
-                        for (int c = 0; c < 6; ++c) o[c] = yc[c][r];
-                    } else {
-#pragma unroll
-                        for (int cb = 0; cb < 3; ++cb) o[2 * cb + L.hi] = yc[3 * h + cb][r];
-                    }
+                    for (int c = 0; c < 6; ++c) o[c] = yc[3 * h + c % 3][r + 2 * (c / 3)];
                 }
                 if (j == N - 1) {
-                    if constexpr (Sh::WIDE) {
+                    const bool dead = sm.Dead[m];
 #pragma unroll
-                        for (int c = 0; c < 6; ++c) sY0[c * T + m] = dead ? (double)NAN : yc[c][r];
-                    } else {
-#pragma unroll
-                        for (int cb = 0; cb < 3; ++cb)
-                            sY0[(2 * cb + L.hi) * T + m] = dead ? (double)NAN : yc[3 * h + cb][r];
-                    }
+                    for (int c = 0; c < 6; ++c)
+                        sY0[c * T + m] = dead ? (double)NAN : yc[3 * h + c % 3][r + 2 * (c / 3)];
                 }
             }
         }
@@ -572,47 +567,43 @@ template <int PAIRS, int NP, int SO = 0>
 __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const PcJobDev& job, const PcGroupDev& g)
 {
     using Sh = PcShape<PAIRS, NP>;
-    constexpr int NT = Sh::NT, T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
-    constexpr int COLS = Sh::WIDE ? 16 : 8;      // columns of one group
-    constexpr int GN = Sh::WIDE ? Sh::G16 : 1;   // groups of the job
-    constexpr int E = Sh::WIDE ? 4 : 1;          // columns a lane holds points of
+    constexpr int NT = Sh::NT, T = Sh::T, COLS = Sh::COLS, GN = Sh::GN, E = Sh::E;
     constexpr unsigned CMASK = (1u << COLS) - 1u;
     PcSmem<PAIRS>& sm = pc_smem<PAIRS>();
     double* sF = sm.F;
     double* sY0 = sm.Y0;
+    const double* sWt = pc_weights<PAIRS, NP>(sm);
     const int tid = threadIdx.x;
-    const PcLane L = pc_lane_geometry<PAIRS, NP>(tid, g.N);
+    PcLane L = pc_lane_geometry<PAIRS, NP>(tid, g.N);
     const int N = g.N, S = g.S, P = p.n_pert;
     const int n = job.n;
-    const int grp = Sh::WIDE ? L.grp : 0;
+    const int grp = L.grp;
     const int n_g = n > grp ? (n - grp + GN - 1) / GN : 0;   // entries of this wave's group
     const bool rec_lds = N * 3 * (P + 1) <= PcSmem<PAIRS>::REC;
     const PcTol tl = pc_tol(p.tol_mode, g.tol * g.tol, 0.0);
-    gconst_dp kp0 = (gconst_dp)g.kfrag + (size_t)L.strip0 * NQ * 64 + L.lane;
-    double kpre[8];
-    pc_kpre_load<PAIRS, NP>(kp0, kpre);
-    // second-order sweeps: the K2_N strip next to K_N's and the nodes' tau + 1
-    gconst_dp kp2 = nullptr;
-    double tp[8] = {};
+    const PcFragD kp = pc_frag<PAIRS, NP, PcFragD>(g.kpair, L);
+    pc_d2v kpre[4];
+    // second-order sweeps: the K2_N strip next to K_N's and the lane's tau + 1
+    PcFragD kp2 = {};
+    double tp = 0.0;
     if constexpr (SO) {
-        kp2 = (gconst_dp)g.kfrag2 + (size_t)L.strip0 * NQ * 64 + L.lane;
-        if constexpr (Sh::WIDE) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) kpre[4 + u] = kp2[u * 64];
-            tp[0] = pc_gcd(g.tau)[pc_node(L, 0, 0)] + 1.0;
-        } else {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) tp[4 * h + r] = pc_gcd(g.tau)[pc_node(L, h, r)] + 1.0;
-            }
-        }
+        kp2 = pc_frag<PAIRS, NP, PcFragD>(g.kpair2, L);
+        tp = pc_gcd(g.tau)[L.jn[0]] + 1.0;
     }
+    pc_stage_weights<PAIRS, NP>(sm, g.wts);
     const bool flane = L.lane < COLS;             // lanes < COLS carry the per-column decisions
     const int fcol = L.lane & (COLS - 1);
-    const bool owner = flane && L.strip0 == 0;    // one wave per group writes per-IC records
+    const bool owner = flane && L.strip == 0;     // one wave per group writes per-IC records
     auto ic_of = [&](int e) -> int64_t { return job.ic0 + grp + (int64_t)GN * e; };
-    auto col_of = [&](int e) -> int { return Sh::WIDE ? pc_ic(L, e) - grp * 16 : (L.lane & 7); };
+    auto col_of = [&](int e) -> int { return pc_col<PAIRS, NP>(L, e); };
+    // the lane's part of a column: its IC r at both nodes of the row (PAR), or IC r of one eight
+    auto has = [&](int e, int h) -> bool { return Sh::PAR || h == (e >> 1); };
+    // the lane's point in a refill pass: point pt of a column (PAR: row pt % 16 at node pt / 16)
+    constexpr int WN = Sh::PAR ? 32 : 16;
+    const int pt = L.lane & (WN - 1), pt_row = L.strip * 16 + (pt & 15);
+    const bool pt_ok = pt_row < (Sh::PAR ? (N + 1) >> 1 : N);
+    const double pt_tau = pc_gcd(g.tau)[!pt_ok ? 0 : Sh::PAR && pt >= 16 ? N - 1 - pt_row : pt_row] + 1.0;
+    double pf[2] = {0.0, 0.0};
     int notconv = 0;
     // the buffers of the call, read once from the parameter block as global pointers
     const gconst_dp g_ics = pc_gcd(p.ics);
@@ -631,87 +622,88 @@ __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const P
         const gconst_dp src = s == 0 ? g_ics : g_states;
         const double4* grec = reinterpret_cast<const double4*>(p.recs) +
                               (size_t)(g.rec_offset + (int64_t)s * N) * (P + 1);
+        // Initial states of the group's entries base .. base + COLS - 1 (those its columns take
+        // next), held across the wave's lanes (entry l % COLS, component l / COLS and, with 16
+        // columns, 4 + l / 16) and loaded as soon as the ones before are taken: a refill then
+        // waits on no memory (it waited about 3000 cycles for the state and the node's tau).
+        auto prefetch = [&](int base) {
+            const int e = base + fcol, c = L.lane / COLS;
+            const gconst_dp y = src + ic_of(e) * 6 + c;
+            pf[0] = e < n_g && c < 6 ? y[0] : 0.0;
+            if constexpr (COLS == 16) pf[1] = e < n_g && c < 2 ? y[4] : 0.0;
+        };
         // Warm (or cold) start, Sec. 2.1, of the group's columns in `rm`, column c taking entry
-        // base + (its rank in rm).  The wave computes the points of its own node rows for
-        // all those columns together (one Kepler solve per lane and pass), stages them in
-        // the columns' F slots (free after the product), and the lanes that hold the points
-        // read them back.
+        // base + (its rank in rm).  The wave computes the points of its own rows for all those
+        // columns together (one Kepler solve per lane and pass), stages them in the columns' F
+        // slots (free after the product; component c of half h in the slot that its F value
+        // will take), and the lanes that hold the points read them back.  The lanes of the
+        // group's first node write y0 (product epilogue) and the checkpoint.
+        auto slot = [&](int row, int col, int c, int h) __attribute__((always_inline)) -> double* {
+            return sF + 2 * pc_unit<PAIRS, NP>(row, grp, c % 3, 8 * (c / 3) + (col & 7)) + h;
+        };
         auto warm_columns = [&](unsigned rm, int base) {
-            constexpr int WN = 16 * Sh::H;               // node rows of this wave
             const int k = __popc(rm);
-            for (int q = L.lane; q < WN * k; q += 64) {
-                const int ci = q / WN, jn = q - ci * WN;
-                unsigned m = rm;
-                for (int t = 0; t < ci; ++t) m &= m - 1u;
-                const int c = __ffs(m) - 1;
-                const int j = L.strip0 * 16 + jn;
-                if (j >= N) continue;
-                const gconst_dp y0p = src + ic_of(base + ci) * 6;
+            for (int q0 = 0; q0 < WN * k; q0 += 64) {
+                const int ci = (q0 + L.lane) / WN;
                 double y0[6];
                 bool fin = true;
 #pragma unroll
                 for (int cc = 0; cc < 6; ++cc) {
-                    y0[cc] = y0p[cc];
+                    const int from = (ci & (COLS - 1)) + COLS * (COLS == 16 ? cc & 3 : cc);
+                    y0[cc] = __shfl(pf[COLS == 16 ? cc >> 2 : 0], from);
                     fin = fin && isfinite(y0[cc]);
                 }
+                if (ci >= k || !pt_ok) continue;
+                unsigned m = rm;
+                for (int t = 0; t < ci; ++t) m &= m - 1u;
+                const int c = __ffs(m) - 1;
+                const int h = Sh::PAR ? pt >> 4 : c >> 3;
                 double y[6];
-                if (!(p.init == 0 && fin && pc_kepler(y0, w2 * (pc_gcd(g.tau)[j] + 1.0), y))) {
+                if (!(p.init == 0 && fin && pc_kepler(y0, w2 * pt_tau, y))) {
 #pragma unroll
                     for (int cc = 0; cc < 6; ++cc) y[cc] = y0[cc];
                 }
-                double* f = sF + j * ROW + pc_fcol<PAIRS, NP>(j, grp * 16 + c);
 #pragma unroll
-                for (int cc = 0; cc < 6; ++cc) f[cc * T] = y[cc];
+                for (int cc = 0; cc < 6; ++cc) *slot(pt_row, c, cc, h) = y[cc];
+                if (pt_row == 0 && pt < 16) {
+#pragma unroll
+                    for (int cc = 0; cc < 6; ++cc) sY0[cc * T + grp * COLS + c] = y0[cc];
+                    if (g_bounds) {
+                        const gdp bo = g_bounds + ((size_t)ic_of(base + ci) * (istride + 1) + s) * 6;
+#pragma unroll
+                        for (int cc = 0; cc < 6; ++cc) bo[cc] = y0[cc];
+                    }
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // staged points visible to the wave
+            if (L.ok) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if (!((rm >> col_of(e)) & 1u)) continue;
+                for (int e = 0; e < E; ++e) {
+                    const int c = col_of(e);
+                    if (!((rm >> c) & 1u)) continue;
 #pragma unroll
-                for (int h = 0; h < Sh::H; ++h) {
+                    for (int h = 0; h < 2; ++h) {
+                        if (!has(e, h)) continue;
 #pragma unroll
-                    for (int r = 0; r < (Sh::WIDE ? 1 : 4); ++r) {
-                        const int j = pc_node(L, h, r);
-                        if (j >= N) continue;
-                        double* f = sF + j * ROW + pc_fcol<PAIRS, NP>(j, Sh::WIDE ? pc_ic(L, e) : (L.lane & 7));
-                        // second-order sweeps keep F's velocity columns at zero: the lane
-                        // that reads a staged velocity clears it
-                        if constexpr (Sh::WIDE) {
-#pragma unroll
-                            for (int cc = 0; cc < 6; ++cc) {
-                                yc[cc][e] = f[cc * T];
-                                if (SO && cc < 3) f[cc * T] = 0.0;
-                            }
-                        } else {
-#pragma unroll
-                            for (int cb = 0; cb < 3; ++cb) {
-                                yc[3 * h + cb][r] = f[(2 * cb + L.hi) * T];
-                                if (SO && 2 * cb + L.hi < 3) f[(2 * cb + L.hi) * T] = 0.0;
-                            }
+                        for (int cc = 0; cc < 6; ++cc) {
+                            double* f = slot(L.row, c, cc, h);
+                            yc[3 * h + cc % 3][(e & 1) + 2 * (cc / 3)] = *f;
+                            // second-order sweeps keep the unused halves of F's blocks at zero
+                            if (SO && (cc == 2 || cc == 4)) *f = 0.0;
                         }
                     }
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // read before the slots are rewritten
         };
-        // the owner lane of a column writes its IC's y0 (product epilogue) and checkpoint
-        auto own_column = [&](int en) {
-            const int64_t icg = ic_of(en);
-            const gconst_dp y0p = src + icg * 6;
-            double v[6];
-#pragma unroll
-            for (int c = 0; c < 6; ++c) v[c] = y0p[c];
-#pragma unroll
-            for (int c = 0; c < 6; ++c) sY0[c * T + grp * 16 + fcol] = v[c];
-            if (g_bounds) {
-                const gdp bo = g_bounds + ((size_t)icg * (istride + 1) + s) * 6;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) bo[c] = v[c];
-            }
-        };
 
         if (rec_lds) pc_stage_records<PAIRS>(grec, N, P, sm);
-        for (int i = tid; i < 6 * PAIRS; i += NT) sF[i] = 0.0;   // rows past N stay zero
+        for (int i = tid; i < 6 * PAIRS; i += NT) sF[i] = 0.0;   // rows past the last stay zero
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) yc[b][r] = 1.0;
+        }
         __syncthreads();   // records staged, F cleared
         // the group's first COLS entries into its columns
         int next = n_g < COLS ? n_g : COLS;                                   // uniform per group
@@ -719,26 +711,31 @@ __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const P
         int ent[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) ent[e] = col_of(e) < next ? col_of(e) : -1;
+        prefetch(0);
         warm_columns(amask, 0);
+        prefetch(next);
         int fent = fcol < next ? fcol : -1;   // flag lane: entry of its column
         int it0 = 0;                          // flag lane: sweep before its IC's first one
-        if (owner && fent >= 0) own_column(fent);
         __syncthreads();   // y0 written
-        if (amask) pc_publish<PAIRS, NP, false, SO == 0>(sF, yc, L, N, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+        if (amask) pc_publish<PAIRS, NP, false, SO != 0>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+        if constexpr (SO == 0) pc_kpre_load(kp, kpre);
         __syncthreads();
 
         for (int it = 1;; ++it) {
+            L = pc_lane_again<PAIRS, NP>(L, N);
             f64x4 acc[6];
-            int flag;
-            if constexpr (SO) flag = pc_product2<PAIRS, NP>(sF, sY0, kp0, kp2, kpre, yc, acc, w2, tp, tl, N, L);
-            else flag = pc_product<PAIRS, NP, false, false>(sF, sY0, kp0, kpre, nullptr, yc, acc, w2, tl, N, L);
-            if (L.lane < 16) sm.Flag[L.wave * 16 + L.lane] = flag;
+            if (amask) {
+                int flag;
+                if constexpr (SO) flag = pc_product2<PAIRS, NP>(sF, sY0, sWt, kp, kp2, yc, acc, w2, tp, tl, L);
+                else flag = pc_product<PAIRS, NP, false>(sF, sY0, sWt, kp, kpre, yc, acc, w2, tl, L);
+                pc_put_flags<PAIRS, NP>(sm.Flag, flag, L);
+            }
             __syncthreads();   // every wave is done reading F; flags complete
 
             // stopping rule per IC (Sec. 2.2), taken identically by every wave of the group
             int rec = 0;
             if (flane && fent >= 0) {
-                const int f = pc_gather_flags<PAIRS, NP>(sm.Flag, grp * 16 + fcol);
+                const int f = pc_gather_flags<PAIRS, NP>(sm.Flag, grp * COLS + fcol);
                 const int k = it - it0;
                 if (f & 2) rec = -2;
                 else if (fixed_iters > 0) rec = (k == fixed_iters) ? k : 0;
@@ -751,16 +748,13 @@ __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const P
                 if (g_iters) g_iters[(size_t)ic_of(fent) * istride + s] = rec;
                 if (rec == -1) ++notconv;
             }
-            // the columns that were iterating take the new iterate
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const bool act = (amask >> col_of(e)) & 1u;
+            // the new iterate (a column whose IC has stopped and was not refilled goes on with
+            // values nobody reads; the product mixes no columns)
+            if (amask) {
 #pragma unroll
                 for (int b = 0; b < 6; ++b) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        if (Sh::WIDE ? r == e : true) yc[b][r] = act ? acc[b][r] : yc[b][r];
-                    }
+                    for (int r = 0; r < 4; ++r) yc[b][r] = acc[b][r];
                 }
             }
             if (smask) {
@@ -769,45 +763,26 @@ __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const P
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     const int c = col_of(e);
-                    if (!((smask >> c) & 1u)) continue;
+                    if (!((smask >> c) & 1u) || !L.ok) continue;
                     const int64_t icg = ic_of(ent[e]);
                     const bool dead = (dmask >> c) & 1u;
 #pragma unroll
-                    for (int h = 0; h < Sh::H; ++h) {
+                    for (int h = 0; h < 2; ++h) {
+                        if (!has(e, h) || (Sh::PAR && h == 1 && !L.two)) continue;
+                        const int j = L.jn[h];
+                        if (g_nodes) {
+                            const gdp nd = g_nodes + (((size_t)icg * istride + s) * nstride + j) * 6;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            if (Sh::WIDE && r != e) continue;
-                            const int j = Sh::WIDE ? pc_node(L, 0, 0) : pc_node(L, h, r);
-                            if (j >= N) continue;
-                            if (g_nodes) {
-                                const gdp nd = g_nodes + (((size_t)icg * istride + s) * nstride + j) * 6;
-                                if constexpr (Sh::WIDE) {
+                            for (int cc = 0; cc < 6; ++cc) nd[cc] = yc[3 * h + cc % 3][(e & 1) + 2 * (cc / 3)];
+                        }
+                        if (j == N - 1) {
+                            const gdp so = g_states + icg * 6;
+                            const gdp bo = g_bounds ? g_bounds + ((size_t)icg * (istride + 1) + s + 1) * 6 : g_bounds;
 #pragma unroll
-                                    for (int cc = 0; cc < 6; ++cc) nd[cc] = yc[cc][e];
-                                } else {
-#pragma unroll
-                                    for (int cb = 0; cb < 3; ++cb) nd[2 * cb + L.hi] = yc[3 * h + cb][r];
-                                }
-                            }
-                            if (j == N - 1) {
-                                const gdp so = g_states + icg * 6;
-                                const gdp bo = g_bounds ? g_bounds + ((size_t)icg * (istride + 1) + s + 1) * 6 : g_bounds;
-                                if constexpr (Sh::WIDE) {
-#pragma unroll
-                                    for (int cc = 0; cc < 6; ++cc) {
-                                        const double v = dead ? (double)NAN : yc[cc][e];
-                                        so[cc] = v;
-                                        if (bo) bo[cc] = v;
-                                    }
-                                } else {
-#pragma unroll
-                                    for (int cb = 0; cb < 3; ++cb) {
-                                        const int cc = 2 * cb + L.hi;
-                                        const double v = dead ? (double)NAN : yc[3 * h + cb][r];
-                                        so[cc] = v;
-                                        if (bo) bo[cc] = v;
-                                    }
-                                }
+                            for (int cc = 0; cc < 6; ++cc) {
+                                const double v = dead ? (double)NAN : yc[3 * h + cc % 3][(e & 1) + 2 * (cc / 3)];
+                                so[cc] = v;
+                                if (bo) bo[cc] = v;
                             }
                         }
                     }
@@ -828,12 +803,14 @@ __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const P
                     if ((rmask >> c) & 1u) ent[e] = next + __popc(rmask & ((1u << c) - 1u));
                     else if ((smask >> c) & 1u) ent[e] = -1;
                 }
-                if (rmask) warm_columns(rmask, next);
+                if (rmask) {
+                    warm_columns(rmask, next);
+                    prefetch(next + take);
+                }
                 if (flane) {
                     if ((rmask >> fcol) & 1u) {
                         fent = next + __popc(rmask & ((1u << fcol) - 1u));
                         it0 = it;
-                        if (owner) own_column(fent);
                     } else if ((smask >> fcol) & 1u) {
                         fent = -1;
                     }
@@ -841,14 +818,15 @@ __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const P
                 next += take;
                 amask = (amask & ~smask) | rmask;
             }
-            if (amask) pc_publish<PAIRS, NP, false, SO == 0>(sF, yc, L, N, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+            if (amask) pc_publish<PAIRS, NP, false, SO != 0>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
             // every wave of an IC group holds the group's column mask: the first strip's waves
             // note it (rewritten only after the next sweep's first barrier)
-            if (L.strip0 == 0 && L.lane == 0) sm.Go[L.grp] = amask != 0u;
+            if (L.strip == 0 && L.lane == 0) sm.Go[grp] = amask != 0u;
+            if constexpr (SO == 0) pc_kpre_load(kp, kpre);
             __syncthreads();   // F complete; the notes visible
             int go = 0;
 #pragma unroll
-            for (int q = 0; q < Sh::G16; ++q) go |= sm.Go[q];
+            for (int q = 0; q < GN; ++q) go |= sm.Go[q];
             if (!go) break;
         }
     }
@@ -864,7 +842,7 @@ __device__ __attribute__((noinline)) void pc_job_list(const PcParams& p, const P
 }
 
 // The job body for node count NP and the call's options: second-order sweeps (with the
-// feedback on WIDE shapes), relativistic, refilled column lists, precision schedule or
+// feedback when asked), relativistic, refilled column lists, precision schedule or
 // plain FP64 one-block jobs.
 template <int PAIRS, int NP>
 static __device__ __forceinline__ void pc_run_job(const PcParams& p, const PcJobDev& job, const PcGroupDev& g,
@@ -913,7 +891,7 @@ __global__ __launch_bounds__(PAIRS / 4, 2) void pc_fused_kernel(const PcParams* 
         const bool mixed = p.precision == 1;
         const bool eih = p.inv_c2 != 0.0;   // relativistic model: one-block jobs
         const bool order2 = p.order == 2;   // second-order sweeps (with the integral error feedback when
-                                            // asked, WIDE shapes): FP64, point masses
+                                            // asked): FP64, point masses
         switch (g.NP) {
         case 16: pc_run_job<PAIRS, 16>(p, job, g, list, mixed, eih, order2); break;
         case 32: pc_run_job<PAIRS, 32>(p, job, g, list, mixed, eih, order2); break;
@@ -961,10 +939,8 @@ int pc_launch_fused(const PcParams& p, const PcParams* p_dev, int pairs, int gri
 //   (J^T w)_r = w2 H w_v,   (J^T w)_v = w2 w_r.
 // Segments are processed from the last: each is first re-solved from its checkpoint (the
 // same forward code, so the same converged states), and its gradient seeds the end node of
-// the previous one.  WIDE job shapes hold one node of four ICs per lane; 8-IC jobs (256
-// nodes) hold the node-row layout of the forward product (a lane pair (l, l ^ 8) shares the
-// components of one IC), and their lanes exchange what the Hessian product and the
-// velocity rows need with their partner.
+// the previous one.  A lane holds its points' states and mu (PcShape), so that J^T w needs no
+// other lane.
 // EIH: the relativistic dynamics, whose force also depends on the velocity: J^T w is
 // ((da/dr)^T w_v, w_r + (da/dv)^T w_v) (pc_eih_vjp) instead of (H w_v, w_r).
 template <int PAIRS, int NP, bool EIH = false>
@@ -972,20 +948,19 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
                                                          const PcGroupDev& g)
 {
     using Sh = PcShape<PAIRS, NP>;
-    constexpr int NT = Sh::NT, T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ, W = Sh::W;
+    constexpr int T = Sh::T, W = Sh::W, COLS = Sh::COLS;
     PcSmem<PAIRS>& sm = pc_smem<PAIRS>();
     const PcParams& p = a.fwd;
     double* sF = sm.F;
     double* sY0 = sm.Y0;
     const int tid = threadIdx.x;
-    // the products run every k step here (the bound NP folds to the compile-time count): a
-    // second, shorter k loop per product costs this body registers at every node count
-    const PcLane L = pc_lane_geometry<PAIRS, NP>(tid, NP);
+    const PcLane L = pc_lane_geometry<PAIRS, NP>(tid, g.N);
     const int N = g.N, S = g.S, P = p.n_pert;
     const int n = job.n;
     const int64_t ic = job.ic0 + tid;
     // adjoint scratch at the top of the record area: seed Lam, estimate LamIt, partial sums
-    constexpr int ADJ = 12 * T + W * 6 * 16;
+    // [wave][comp][column]
+    constexpr int ADJ = 12 * T + W * 6 * COLS;
     constexpr int REC_CAP = PcSmem<PAIRS>::REC - ADJ;
     double* sLam = sm.Rec + REC_CAP;
     double* sLamIt = sLam + 6 * T;
@@ -996,10 +971,18 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
     if (tid < T) {
         for (int c = 0; c < 6; ++c) sLam[c * T + tid] = tid < n ? a.gbar_final[(size_t)ic * 6 + c] : 0.0;
     }
-    gconst_dp kp0 = (gconst_dp)g.kfrag + (size_t)L.strip0 * NQ * 64 + L.lane;
-    gconst_dp kpT = (gconst_dp)g.kfragT + (size_t)L.strip0 * NQ * 64 + L.lane;
+    pc_stage_weights<PAIRS, NP>(sm, g.wts);
+    const PcFragD kp = pc_frag<PAIRS, NP, PcFragD>(g.kpair, L);
+    const PcFragD kpT = pc_frag<PAIRS, NP, PcFragD>(g.kpairT, L);
+    const double wr = Sh::PAR ? pc_gcd(g.wts)[2 * Sh::KR + L.row] : 0.0;
     double yc[6][4];
     int had_notconv = 0, adj_notconv = 0, dead_any = 0;
+    // the lane's mu at IC r (both h): the pair (mu_l - mu_r, mu_l + mu_r), or the two eights'
+    auto put_mu = [&](int c, int r, double vl, double vr) __attribute__((always_inline)) {
+        pc_d2v* f = reinterpret_cast<pc_d2v*>(sF) +
+                    pc_unit<PAIRS, NP>(L.row, L.grp, c % 3, 8 * (c / 3) + L.g + 4 * r);
+        *f = Sh::PAR ? pc_d2v{vl - vr, vl + vr} : pc_d2v{vl, vr};
+    };
     for (int s = S - 1; s >= 0; --s) {
         // segment s's converged iterate: the forward call's node states when given, else a
         // re-solve from its checkpoint
@@ -1022,80 +1005,54 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
         if (a.fwd_nodes) {
             if (!EIH && rec_lds) pc_stage_records<PAIRS>(grec, N, P, sm);
 #pragma unroll
-            for (int h = 0; h < Sh::H; ++h) {
+            for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = pc_node(L, h, r);
-                    const int m = pc_ic(L, r);
+                for (int r = 0; r < 2; ++r) {
+                    const int m = pc_ic<PAIRS, NP>(L, h, r);
                     double v[6];
-                    if (j < N && m < n) {
+                    if (L.ok && m < n) {
                         const gconst_dp y = pc_gcd(a.fwd_nodes) +
-                                            (((size_t)(job.ic0 + m) * a.ckpt_stride + s) * a.nodes_stride + j) * 6;
+                                            (((size_t)(job.ic0 + m) * a.ckpt_stride + s) * a.nodes_stride + L.jn[h]) * 6;
 #pragma unroll
                         for (int c = 0; c < 6; ++c) v[c] = y[c];
-                    } else {   // padding node or column: any finite state (its results are unused)
+                    } else {   // padding row or column: any finite state (its results are unused)
 #pragma unroll
                         for (int c = 0; c < 6; ++c) v[c] = sY0[c * T + m];
                     }
-                    if constexpr (Sh::WIDE) {
 #pragma unroll
-                        for (int c = 0; c < 6; ++c) yc[c][r] = v[c];
-                    } else {
-#pragma unroll
-                        for (int cb = 0; cb < 3; ++cb) yc[3 * h + cb][r] = v[2 * cb + L.hi];
-                    }
+                    for (int c = 0; c < 6; ++c) yc[3 * h + c % 3][r + 2 * (c / 3)] = v[c];
                 }
             }
         } else {
-            pc_segment_solve<PAIRS, NP, false, EIH>(p, g, n, job.ic0, s, sm, L, kp0, yc, nullptr, had_notconv,
+            pc_segment_solve<PAIRS, NP, false, EIH>(p, g, n, job.ic0, s, sm, L, kp, yc, nullptr, had_notconv,
                                                     REC_CAP);
         }
         __syncthreads();
         const double Ts = g.t0 + g.h * s, Te = g.t0 + g.h * (s + 1);
         const double w2 = 0.5 * (Te - Ts);
 
-        // seed of this segment at the lane's nodes: the next segment's gradient at the end
-        // node, plus the node seeds when given (recomputed where needed, not held)
-        // the Hessian's points: WIDE, the lane's node of its four ICs; 8-IC jobs, the four
-        // rows of strip hi (each lane of a pair takes one strip)
-        int jr[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, Sh::WIDE ? 0 : L.hi, r);
-            jr[r] = j < N ? j : N - 1;
-        }
-        auto seed_at = [&](int c, int j, int m) -> double {
-            double v = (j == N - 1) ? sLam[c * T + m] : 0.0;
-            if (a.gbar_nodes && m < n && j < N)
-                v += a.gbar_nodes[(((size_t)(job.ic0 + m) * a.ckpt_stride + s) * a.nodes_stride + j) * 6 + c];
+        // seed of this segment at the lane's point (h, r): the next segment's gradient at the
+        // end node, plus the node seeds when given (recomputed where needed, not held); none at
+        // a middle node's second place
+        auto seed = [&](int c, int h, int r) __attribute__((always_inline)) -> double {
+            const int m = pc_ic<PAIRS, NP>(L, h, r);
+            if (!L.ok || (Sh::PAR && h == 1 && !L.two)) return 0.0;
+            double v = L.jn[h] == N - 1 ? sLam[c * T + m] : 0.0;
+            if (a.gbar_nodes && m < n)
+                v += pc_gcd(a.gbar_nodes)[(((size_t)(job.ic0 + m) * a.ckpt_stride + s) * a.nodes_stride + L.jn[h]) * 6 + c];
             return v;
         };
-        auto seed = [&](int c, int r) -> double { return seed_at(c, pc_node(L, 0, r), pc_ic(L, r)); };
-        for (int i = tid; i < 6 * PAIRS; i += NT) sF[i] = 0.0;
         if (tid < T) {
             sm.Active[tid] = (tid < n) && !sm.Dead[tid];
             for (int c = 0; c < 6; ++c) sLamIt[c * T + tid] = 0.0;
         }
-        __syncthreads();
+        pc_clear_rows<PAIRS, NP, false>(sF, N);
         // mu^(0) = gbar
+        if (L.ok) {
 #pragma unroll
-        for (int h = 0; h < Sh::H; ++h) {
+            for (int c = 0; c < 6; ++c) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = pc_node(L, h, r);
-                const int m = pc_ic(L, r);
-                if (j < N) {
-                    if constexpr (Sh::WIDE) {
-#pragma unroll
-                        for (int c = 0; c < 6; ++c) sF[j * ROW + c * T + pc_fcol<PAIRS, NP>(j, m)] = seed_at(c, j, m);
-                    } else {
-#pragma unroll
-                        for (int cb = 0; cb < 3; ++cb) {
-                            const int c = 2 * cb + L.hi;
-                            sF[j * ROW + c * T + pc_fcol<PAIRS, NP>(j, m)] = seed_at(c, j, m);
-                        }
-                    }
-                }
+                for (int r = 0; r < 2; ++r) put_mu(c, r, seed(c, 0, r), seed(c, 1, r));
             }
         }
         __syncthreads();
@@ -1103,152 +1060,82 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
         int it = 1;
         for (; it <= a.adj_max_iter; ++it) {
             f64x4 acc[6];
-            pc_product_adj<PAIRS, NP>(sF, kpT, acc, L);          // w = K^T mu
-            double hx[4], hy[4], hz[4];
-            if constexpr (Sh::WIDE) {
-                double wx[4], wy[4], wz[4];
+            pc_product_adj<PAIRS, NP>(sF, kpT, wr, acc, L);          // w = K^T mu
+            double x[4], y[4], z[4], wx[4], wy[4], wz[4], hx[4], hy[4], hz[4];
+            pc_points(yc, 0, x);
+            pc_points(yc, 1, y);
+            pc_points(yc, 2, z);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    wx[r] = acc[3][r];
-                    wy[r] = acc[4][r];
-                    wz[r] = acc[5][r];
+            for (int q = 0; q < 4; ++q) {
+                wx[q] = acc[3 * (q >> 1)][2 + (q & 1)];
+                wy[q] = acc[3 * (q >> 1) + 1][2 + (q & 1)];
+                wz[q] = acc[3 * (q >> 1) + 2][2 + (q & 1)];
+            }
+            double gx[4] = {}, gy[4] = {}, gz[4] = {};   // (da/dv)^T w_v (relativistic)
+            if constexpr (EIH) {
+                double vx[4], vy[4], vz[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    vx[q] = yc[3 * (q >> 1)][2 + (q & 1)];
+                    vy[q] = yc[3 * (q >> 1) + 1][2 + (q & 1)];
+                    vz[q] = yc[3 * (q >> 1) + 2][2 + (q & 1)];
                 }
-                double gx[4] = {}, gy[4] = {}, gz[4] = {};   // (da/dv)^T w_v (relativistic)
-                if constexpr (EIH)
-                    pc_eih_vjp<4, true>(yc[0], yc[1], yc[2], yc[3], yc[4], yc[5], wx, wy, wz, erec, jr, N, P, p.inv_c2,
-                                        hx, hy, hz, gx, gy, gz);
-                else if (rec_lds)
-                    pc_hess_apply<4, true>(yc[0], yc[1], yc[2], wx, wy, wz, jr, P, p.mu_sun, sm.Rec, sm.Mu, grec,
-                                           hx, hy, hz);
-                else
-                    pc_hess_apply<4, false>(yc[0], yc[1], yc[2], wx, wy, wz, jr, P, p.mu_sun, sm.Rec, sm.Mu, grec,
-                                            hx, hy, hz);
-                // mu_new = gbar + J^T w, and its sum over the strip's nodes (the 16 lanes of a
-                // row group hold one node each of the same four ICs)
-                const bool node_ok = pc_node(L, 0, 0) < N;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const double nv0 = seed(3, r) + w2 * (acc[0][r] + gx[r]);
-                    const double nv1 = seed(4, r) + w2 * (acc[1][r] + gy[r]);
-                    const double nv2 = seed(5, r) + w2 * (acc[2][r] + gz[r]);
-                    acc[0][r] = seed(0, r) + w2 * hx[r];
-                    acc[1][r] = seed(1, r) + w2 * hy[r];
-                    acc[2][r] = seed(2, r) + w2 * hz[r];
-                    acc[3][r] = nv0;
-                    acc[4][r] = nv1;
-                    acc[5][r] = nv2;
-#pragma unroll
-                    for (int c = 0; c < 6; ++c) {
-                        double part = node_ok ? acc[c][r] : 0.0;
-                        part = pc_row_sum16(part);
-                        if ((L.lane & 15) == 0) sLamPart[(L.wave * 6 + c) * 16 + (L.lane >> 4) + 4 * r] = part;
-                    }
-                }
+                pc_eih_vjp(x, y, z, vx, vy, vz, wx, wy, wz, erec, L.jn, N, P, p.inv_c2, hx, hy, hz, gx, gy, gz);
+            } else if (rec_lds) {
+                pc_hess_apply<true>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
             } else {
-                // node-row layout: element (3h + cb, r) is comp 2cb + hi of node j(h, r); the
-                // low lane of a pair holds comps 0, 2, 4, the high lane 1, 3, 5.  Each lane
-                // forms H w_v at the four points of strip hi (position and w_v = (w3, w4, w5),
-                // taking the three components it lacks from its partner)
-                const int hi = L.hi;
-                const int m = pc_ic(L, 0);
-                double xs[4], ys[4], zs[4], wxs[4], wys[4], wzs[4];
+                pc_hess_apply<false>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
+            }
+            // mu_new = gbar + J^T w, and its sum over the strip's nodes (the 16 lanes of a row
+            // group hold the rows of the same ICs)
+            const bool right = !Sh::PAR || L.two;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const double e1 = pc_dpp<0x128>(hi ? yc[0][r] : yc[3][r]);     // lo: y(0); hi: x(1)
-                    const double e2 = pc_dpp<0x128>(hi ? acc[1][r] : yc[4][r]);    // lo: w3(0); hi: z(1)
-                    const double e3 = pc_dpp<0x128>(hi ? acc[2][r] : acc[5][r]);   // lo: w5(0); hi: w4(1)
-                    xs[r] = hi ? e1 : yc[0][r];
-                    ys[r] = hi ? yc[3][r] : e1;
-                    zs[r] = hi ? e2 : yc[1][r];
-                    wxs[r] = hi ? acc[4][r] : e2;
-                    wys[r] = hi ? e3 : acc[2][r];
-                    wzs[r] = hi ? acc[5][r] : e3;
-                }
-                // relativistic: (da/dv)^T w_v at the same points, which also need the velocity
-                // (lo: vy(0) held, vx(0) and vz(0) from hi; hi: vx(1), vz(1) held, vy(1) from lo)
-                double gvx[4] = {}, gvy[4] = {}, gvz[4] = {};
-                if constexpr (EIH) {
-                    double vxs[4], vys[4], vzs[4];
+            for (int q = 0; q < 4; ++q) {
+                const int h = q >> 1, r = q & 1;
+                const double p0 = acc[3 * h][r], p1 = acc[3 * h + 1][r], p2 = acc[3 * h + 2][r];
+                acc[3 * h][r] = fma(w2, hx[q], seed(0, h, r));
+                acc[3 * h + 1][r] = fma(w2, hy[q], seed(1, h, r));
+                acc[3 * h + 2][r] = fma(w2, hz[q], seed(2, h, r));
+                acc[3 * h][2 + r] = fma(w2, EIH ? p0 + gx[q] : p0, seed(3, h, r));
+                acc[3 * h + 1][2 + r] = fma(w2, EIH ? p1 + gy[q] : p1, seed(4, h, r));
+                acc[3 * h + 2][2 + r] = fma(w2, EIH ? p2 + gz[q] : p2, seed(5, h, r));
+                if (h == 1) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const double e4 = pc_dpp<0x128>(hi ? yc[1][r] : yc[5][r]);   // lo: vx(0); hi: vy(1)
-                        const double e5 = pc_dpp<0x128>(yc[2][r]);                   // lo: vz(0)
-                        vxs[r] = hi ? yc[4][r] : e4;
-                        vys[r] = hi ? e4 : yc[2][r];
-                        vzs[r] = hi ? yc[5][r] : e5;
+                    for (int b = 0; b < 3; ++b) {
+                        acc[3 + b][r] = right ? acc[3 + b][r] : 0.0;
+                        acc[3 + b][2 + r] = right ? acc[3 + b][2 + r] : 0.0;
                     }
-                    pc_eih_vjp<4, false>(xs, ys, zs, vxs, vys, vzs, wxs, wys, wzs, erec, jr, N, P, p.inv_c2, hx, hy,
-                                         hz, gvx, gvy, gvz);
-                } else if (rec_lds) {
-                    pc_hess_apply<4, true>(xs, ys, zs, wxs, wys, wzs, jr, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy,
-                                           hz);
-                } else {
-                    pc_hess_apply<4, false>(xs, ys, zs, wxs, wys, wzs, jr, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy,
-                                            hz);
                 }
-                // mu_new = gbar + J^T w: position rows (comp c < 3) take w2 (H w_v)_c of their
-                // point, from the lane that formed it; velocity rows (comp c >= 3) take
-                // w2 w_(c-3), which the partner lane holds
-                double part[3] = {0.0, 0.0, 0.0};
+            }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const double f1 = pc_dpp<0x128>(hi ? hx[r] : hy[r]);   // lo: hx(1); hi: hy(0)
-                    const double f2 = pc_dpp<0x128>(hz[r]);                // lo: hz(1)
-                    // relativistic velocity terms, on the lane that holds the row: comp 3
-                    // (hi) gvx, comp 4 (lo) gvy, comp 5 (hi) gvz of each strip
-                    double f3 = 0.0, f4 = 0.0;
-                    if constexpr (EIH) {
-                        f3 = pc_dpp<0x128>(hi ? gvy[r] : gvx[r]);   // lo: gvy(1); hi: gvx(0)
-                        f4 = pc_dpp<0x128>(gvz[r]);                 // hi: gvz(0)
-                    }
+            for (int c = 0; c < 6; ++c) {
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const double g = pc_dpp<0x128>(acc[3 * h][r]);      // lo: w1(h); hi: w0(h)
-                        const double k = pc_dpp<0x128>(acc[3 * h + 1][r]);  // hi: w2(h)
-                        const int j = pc_node(L, h, r);
-                        const double hc0 = h == 0 ? (hi ? f1 : hx[r]) : (hi ? hy[r] : f1);   // comp hi
-                        const double hc2 = h == 0 ? hz[r] : f2;                              // comp 2 (lo)
-                        const double gv1 = h == 0 ? f3 : gvx[r];                             // comp 3 (hi)
-                        const double gv2 = hi ? (h == 0 ? f4 : gvz[r]) : (h == 0 ? gvy[r] : f3);   // comp 4 + hi
-                        const double n0 = seed_at(hi, j, m) + w2 * hc0;
-                        const double n1 = seed_at(2 + hi, j, m) + w2 * (hi ? g + gv1 : hc2);
-                        const double n2 = seed_at(4 + hi, j, m) + w2 * ((hi ? k : g) + gv2);
-                        acc[3 * h][r] = n0;
-                        acc[3 * h + 1][r] = n1;
-                        acc[3 * h + 2][r] = n2;
-                        if (j < N) {
-                            part[0] += n0;
-                            part[1] += n1;
-                            part[2] += n2;
+                for (int r = 0; r < 2; ++r) {
+                    const double vl = acc[c % 3][r + 2 * (c / 3)], vr = acc[3 + c % 3][r + 2 * (c / 3)];
+                    if constexpr (Sh::PAR) {
+                        const double part = pc_row_sum16(L.ok ? vl + vr : 0.0);
+                        if (L.c == 0) sLamPart[(L.wave * 6 + c) * COLS + L.g + 4 * r] = part;
+                    } else {
+                        const double pl = pc_row_sum16(L.ok ? vl : 0.0), pr = pc_row_sum16(L.ok ? vr : 0.0);
+                        if (L.c == 0) {
+                            sLamPart[(L.wave * 6 + c) * COLS + L.g + 4 * r] = pl;
+                            sLamPart[(L.wave * 6 + c) * COLS + 8 + L.g + 4 * r] = pr;
                         }
                     }
-                }
-                // sum over the wave's 32 nodes: the four row groups of 16 lanes hold nodes
-                // l / 16 + 4 r of both strips
-#pragma unroll
-                for (int cb = 0; cb < 3; ++cb) {
-                    double v = part[cb];
-                    v += __shfl_xor(v, 16);
-                    v += __shfl_xor(v, 32);
-                    if (L.lane < 16) sLamPart[(L.wave * 6 + 2 * cb + hi) * 16 + m] = v;
                 }
             }
             int act[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) act[r] = sm.Active[pc_ic(L, r)];
+            for (int q = 0; q < 4; ++q) act[q] = sm.Active[pc_ic<PAIRS, NP>(L, q >> 1, q & 1)];
             __syncthreads();   // K^T mu read by every wave; partial sums complete
 
             // gradient estimate lambda = sum_j mu_j per IC; stop when it no longer changes
             if (tid < T && sm.Active[tid]) {
-                double ln[6], d2 = 0.0, n2 = 0.0;
+                double d2 = 0.0, n2 = 0.0;
+                const double* part = sLamPart + (tid / COLS) * Sh::STRIPS * 6 * COLS + tid % COLS;
                 for (int c = 0; c < 6; ++c) {
                     double v = 0.0;
-                    if constexpr (Sh::WIDE) {
-                        for (int w = tid >> 4; w < W; w += Sh::G16) v += sLamPart[(w * 6 + c) * 16 + (tid & 15)];
-                    } else {
-                        for (int w = 0; w < W; ++w) v += sLamPart[(w * 6 + c) * 16 + tid];
-                    }
-                    ln[c] = v;
+                    for (int w = 0; w < Sh::STRIPS; ++w) v += part[(w * 6 + c) * COLS];
                     const double d = v - sLamIt[c * T + tid];
                     d2 += d * d;
                     n2 += v * v;
@@ -1265,30 +1152,15 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
                     if (tid < n && a.adj_iters) a.adj_iters[(size_t)ic * a.ckpt_stride + s] = rec;
                 }
             }
-            if constexpr (Sh::WIDE) {
-                if (pc_node(L, 0, 0) < N) {
-                    const int j = pc_node(L, 0, 0);
+            // ICs that were iterating publish the new mu; a stopped IC's sweeps go on
+            // beside them where it shares a place, and nobody reads them
+            if (L.ok) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        if (act[r]) {
+                for (int c = 0; c < 6; ++c) {
 #pragma unroll
-                            for (int c = 0; c < 6; ++c)
-                                sF[j * ROW + c * T + pc_fcol<PAIRS, NP>(j, pc_ic(L, r))] = acc[c][r];
-                        }
-                    }
-                }
-            } else if (act[0]) {
-                const int m = pc_ic(L, 0);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int j = pc_node(L, h, r);
-                        if (j < N) {
-#pragma unroll
-                            for (int cb = 0; cb < 3; ++cb)
-                                sF[j * ROW + (2 * cb + L.hi) * T + pc_fcol<PAIRS, NP>(j, m)] = acc[3 * h + cb][r];
-                        }
+                    for (int r = 0; r < 2; ++r) {
+                        if (act[r] | act[2 + r])
+                            put_mu(c, r, acc[c % 3][r + 2 * (c / 3)], acc[3 + c % 3][r + 2 * (c / 3)]);
                     }
                 }
             }
@@ -1349,7 +1221,8 @@ int pc_launch_adjoint(const PcAdjParams& a, const PcAdjParams* a_dev, int grid, 
 // Test hooks
 // ---------------------------------------------------------------------------
 
-// Y[j][c] = y0[c] + scale * sum_l K[j][l] F[l][c]; one workgroup per 16 columns.
+// Y[j][c] = y0[c] + scale * sum_l K[j][l] F[l][c]; one workgroup per 16 columns (whole K_N,
+// fragments kfrag).
 __global__ __launch_bounds__(256) void pc_apply_operator_kernel(int NP, const double* kfrag, int N,
                                                                 int64_t n_cols, const double* F,
                                                                 const double* y0, double scale, double* Y)

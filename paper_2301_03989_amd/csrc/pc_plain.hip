@@ -105,9 +105,8 @@ __global__ __launch_bounds__(kPlainForceBlock) void pc_plain_force(PcPlainArgs a
                               (size_t)(a.g->rec_offset + (int64_t)s * a.N) * pc_eih_rec(P);
         const double x[1] = {Yj[0]}, y[1] = {Yj[a.Mpad]}, z[1] = {Yj[2 * a.Mpad]};
         const double vx[1] = {Yj[3 * a.Mpad]}, vy[1] = {Yj[4 * a.Mpad]}, vz[1] = {Yj[5 * a.Mpad]};
-        const int jr[1] = {j};
         double ax[1], ay[1], az[1];
-        pc_force_eih<1, true>(x, y, z, vx, vy, vz, erec, jr, a.N, P, a.p.inv_c2, ax, ay, az);
+        pc_force_eih<1>(x, y, z, vx, vy, vz, erec, j, a.N, P, a.p.inv_c2, ax, ay, az);
         Yj[6 * a.Mpad] = ax[0];
         Yj[7 * a.Mpad] = ay[0];
         Yj[8 * a.Mpad] = az[0];
@@ -130,10 +129,10 @@ template <int PAIRS, int NP>
 __global__ __launch_bounds__(PAIRS / 4) void pc_plain_step(PcPlainArgs a, int s, int it, double w2)
 {
     using Sh = PcShape<PAIRS, NP>;
-    constexpr int NT = Sh::NT, T = Sh::T, ROW = Sh::ROW, NQ = Sh::NQ;
-    __shared__ double sF[6 * PAIRS];   // F = (v, a); after the product: the new iterate (r, v)
-    __shared__ double sR[3 * PAIRS];   // positions of the current iterate, [node][3][IC]
+    constexpr int NT = Sh::NT, T = Sh::T, KR = Sh::KR;
+    __shared__ alignas(16) double sF[6 * PAIRS];   // the current iterate, then F, then the new iterate
     __shared__ double sY0[6 * T];
+    __shared__ double sWt[2 * KR];
     __shared__ int sFlag[Sh::W * 16];
     __shared__ int sActive[T];
     __shared__ int sWas[T];
@@ -142,22 +141,27 @@ __global__ __launch_bounds__(PAIRS / 4) void pc_plain_step(PcPlainArgs a, int s,
     const int tid = threadIdx.x;
     const int job = a.job_list[blockIdx.x];
     const int64_t m0 = (int64_t)job * T;
-    const int N = a.N;
+    const int N = a.N, M = Sh::PAR ? (N + 1) >> 1 : N;
     const PcLane L = pc_lane_geometry<PAIRS, NP>(tid, N);
     const size_t row = (size_t)9 * a.Mpad;
+    pc_d2v* f = reinterpret_cast<pc_d2v*>(sF);
 
-    // stage F = (v, a) (Y comps 3..8) and r (Y comps 0..2) of the job, and its initial states
-    for (int i = tid; i < 6 * PAIRS; i += NT) {
-        const int j = i / ROW, c = (i % ROW) / T, k = i % T;
-        sF[j * ROW + c * T + pc_fcol<PAIRS, NP>(j, k)] =
-            j < N ? a.Y[(size_t)j * row + (size_t)(3 + c) * a.Mpad + m0 + k] : 0.0;
-    }
-    for (int i = tid; i < 3 * PAIRS; i += NT) {
-        const int j = i / (3 * T), c = (i % (3 * T)) / T, k = i % T;
-        sR[j * 3 * T + c * T + pc_fcol<PAIRS, NP>(j, k)] =
-            j < N ? a.Y[(size_t)j * row + (size_t)c * a.Mpad + m0 + k] : 0.0;
-    }
+    // place of component c of the job's IC k in row i of sF, and the whole array by (row, half,
+    // component, IC) with the IC fastest: every node once
+    auto place = [&](int i, int c, int k) { return pc_unit<PAIRS, NP>(i, k / Sh::COLS, c % 3, 8 * (c / 3) + (k & 7)); };
+    auto each = [&](auto use) {
+        for (int q = tid; q < 6 * PAIRS; q += NT) {
+            const int k = q % T, c = (q / T) % 6, n = q / (6 * T);
+            const int i = Sh::PAR ? n >> 1 : n, h = Sh::PAR ? n & 1 : (k >> 3) & 1;
+            if (i >= M || (Sh::PAR && h && 2 * i == N - 1)) continue;
+            use(Sh::PAR && h ? N - 1 - i : i, c, k, sF + 2 * place(i, c, k) + h);
+        }
+    };
+    each([&](int j, int c, int k, double* at) { *at = a.Y[(size_t)j * row + (size_t)c * a.Mpad + m0 + k]; });
     for (int i = tid; i < 6 * T; i += NT) sY0[i] = a.Y0[(size_t)(i / T) * a.Mpad + m0 + i % T];
+    if constexpr (Sh::PAR) {
+        for (int i = tid; i < 2 * KR; i += NT) sWt[i] = pc_gcd(a.g->wts)[i];
+    }
     if (tid < T) {
         sActive[tid] = a.active[m0 + tid];
         sWas[tid] = sActive[tid];
@@ -166,43 +170,46 @@ __global__ __launch_bounds__(PAIRS / 4) void pc_plain_step(PcPlainArgs a, int s,
     __syncthreads();
     double yc[6][4];
 #pragma unroll
-    for (int h = 0; h < Sh::H; ++h) {
+    for (int b = 0; b < 3; ++b) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, h, r);
-            const int jj = j < N ? j : N - 1;
-            const int col = pc_fcol<PAIRS, NP>(jj, pc_ic(L, r));
-            if constexpr (Sh::WIDE) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) yc[c][r] = sR[jj * 3 * T + c * T + col];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) yc[3 + c][r] = sF[jj * ROW + c * T + col];
-            } else {
-#pragma unroll
-                for (int cb = 0; cb < 3; ++cb) {
-                    const int c = 2 * cb + L.hi;
-                    yc[3 * h + cb][r] = c < 3 ? sR[jj * 3 * T + c * T + col] : sF[jj * ROW + (c - 3) * T + col];
-                }
-            }
+            const int u = pc_unit<PAIRS, NP>(L.ok ? L.row : M - 1, L.grp, b, 8 * (r >> 1) + L.g + 4 * (r & 1));
+            const pc_d2v v = f[u];
+            yc[b][r] = v.x;
+            yc[3 + b][r] = !Sh::PAR || L.two ? v.y : v.x;
         }
     }
+    __syncthreads();
+    // F = (v, a) (Y comps 3..8) as the product reads it: even and odd parts of the row's nodes
+    for (int q = tid; q < KR * 6 * T; q += NT) {
+        const int k = q % T, c = (q / T) % 6, i = q / (6 * T);
+        const double* y = a.Y + (size_t)(3 + c) * a.Mpad + m0 + k;
+        const double l = i < M ? y[(size_t)i * row] : 0.0;
+        if constexpr (Sh::PAR) {
+            const double r = i < M ? y[(size_t)(N - 1 - i) * row] : 0.0;
+            f[place(i, c, k)] = pc_d2v{l + r, l - r};
+        } else {
+            sF[2 * place(i, c, k) + ((k >> 3) & 1)] = l;
+        }
+    }
+    __syncthreads();
 
     f64x4 acc[6];
-    gconst_dp kp0 = (gconst_dp)a.g->kfrag + (size_t)L.strip0 * NQ * 64 + L.lane;
-    double kpre[8];
-    pc_kpre_load<PAIRS, NP>(kp0, kpre);
-    const int flag = pc_product<PAIRS, NP, false, false>(sF, sY0, kp0, kpre, nullptr, yc, acc, w2,
-                                                         pc_tol(a.p.tol_mode, a.t2, 0.0), N, L);
-    if (L.lane < 16) sFlag[L.wave * 16 + L.lane] = flag;
+    const PcFragD kp = pc_frag<PAIRS, NP, PcFragD>(a.g->kpair, L);
+    pc_d2v kpre[4];
+    pc_kpre_load(kp, kpre);
+    const int flag = pc_product<PAIRS, NP, false>(sF, sY0, sWt, kp, kpre, yc, acc, w2,
+                                                  pc_tol(a.p.tol_mode, a.t2, 0.0), L);
+    pc_put_flags<PAIRS, NP>(sFlag, flag, L);
     __syncthreads();   // F read by every wave, flags complete
 
     if (tid < T && sActive[tid]) {
-        const int f = pc_gather_flags<PAIRS, NP>(sFlag, tid);
+        const int fl = pc_gather_flags<PAIRS, NP>(sFlag, tid);
         int rec = 0;
-        if (f & 2) rec = -2;
+        if (fl & 2) rec = -2;
         else if (a.p.fixed_iters > 0) rec = (it == a.p.fixed_iters) ? it : 0;
-        else if (a.p.conv == PC_CONV_GROUP_MAX) { if (f & 1) sOpen = 1; }   // the host decides
-        else if (!(f & 1)) rec = it;
+        else if (a.p.conv == PC_CONV_GROUP_MAX) { if (fl & 1) sOpen = 1; }   // the host decides
+        else if (!(fl & 1)) rec = it;
         else if (it == a.p.max_iter) rec = -1;
         if (rec != 0) {
             sActive[tid] = 0;
@@ -216,27 +223,19 @@ __global__ __launch_bounds__(PAIRS / 4) void pc_plain_step(PcPlainArgs a, int s,
     }
     // the new iterate into LDS (over F, now free), then out to HBM for the ICs that were
     // iterating
+    if (L.ok) {
 #pragma unroll
-    for (int h = 0; h < Sh::H; ++h) {
+        for (int b = 0; b < 3; ++b) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = pc_node(L, h, r);
-            if (j >= N) continue;
-            const int col = pc_fcol<PAIRS, NP>(j, pc_ic(L, r));
-            if constexpr (Sh::WIDE) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c) sF[j * ROW + c * T + col] = acc[c][r];
-            } else {
-#pragma unroll
-                for (int cb = 0; cb < 3; ++cb) sF[j * ROW + (2 * cb + L.hi) * T + col] = acc[3 * h + cb][r];
-            }
+            for (int r = 0; r < 4; ++r)
+                f[pc_unit<PAIRS, NP>(L.row, L.grp, b, 8 * (r >> 1) + L.g + 4 * (r & 1))] =
+                    pc_d2v{acc[b][r], acc[3 + b][r]};
         }
     }
     __syncthreads();
-    for (int i = tid; i < 6 * PAIRS; i += NT) {
-        const int j = i / ROW, c = (i % ROW) / T, k = i % T;
-        if (j < N && sWas[k]) a.Y[(size_t)j * row + (size_t)c * a.Mpad + m0 + k] = sF[j * ROW + c * T + pc_fcol<PAIRS, NP>(j, k)];
-    }
+    each([&](int j, int c, int k, double* at) {
+        if (sWas[k]) a.Y[(size_t)j * row + (size_t)c * a.Mpad + m0 + k] = *at;
+    });
     const int any = __syncthreads_or(tid < T ? sActive[tid] : 0);
     if (tid == 0) {
         a.job_flag[job] = any;
