@@ -790,9 +790,10 @@ static __device__ __forceinline__ void pc_grad_lds32(const double (&x)[4], const
 }
 
 // Records of the relativistic model per node: for every major body b = 0..P (0 = the
-// central body) three double4, (r_b, U_b - 2 v_b^2), (v_b, mu_b), (a_b, 0), with U_b the
-// potential of the other major bodies at b (the two terms of the bracket below that depend
-// on body b alone, summed once per node), then the indirect term (ax, ay, az, 0).  A
+// central body, at rest at the origin) three double4, (r_b, U_b - 2 v_b^2), (4 v_b, mu_b),
+// (7/2 a_b, 0), with U_b the potential of the other major bodies at b (the two terms of the
+// bracket below that depend on body b alone, summed once per node; the factors are those the
+// sums below need), then the indirect term (ax, ay, az, 0).  A
 // segment's records are stored slot-major, [slot][node], so that the lanes of a wave,
 // which hold consecutive nodes, read consecutive double4.
 constexpr int pc_eih_rec(int P) { return 3 * (P + 1) + 1; }
@@ -824,10 +825,14 @@ static __device__ __forceinline__ double4 pc_eih_load(const PcEihRecs& E, int k,
 //   a = sum_b -mu_b d / rho^3 [1 - (4 Phi + U_b - v^2 - 2 v_b^2 + 4 v.v_b
 //                                   + 3/2 (d.v_b / rho)^2 + 1/2 d.a_b) / c^2]
 //     + sum_b mu_b / (c^2 rho^3) [d.(4 v - 3 v_b)] (v - v_b) + 7/2 sum_b mu_b a_b / (c^2 rho)
-// minus the Newtonian indirect term.  The term in Phi is 4 Phi / c^2 sum_b mu_b d / rho^3,
-// so one pass over the bodies accumulates Phi, that sum and the rest, and the term is
-// added at the end (the same sum in another order).  e: the segment's records, slot k of
-// node j at e[k ns + j].
+// minus the Newtonian indirect term.  What does not depend on the body is taken out of the
+// sums: with N = sum m3 d (m3 = mu_b / rho^3), s the bracket without 4 Phi - v^2 and
+// k = m3 d.(4 v - 3 v_b) / 4,
+//   a = -N + [ (4 Phi - v^2) N + 4 v sum k + sum (m3 s d - 4 k v_b + 7/2 mu_b a_b / rho) ] / c^2,
+// one pass over the bodies and 48 FP64 instructions per body and point (22 for the central
+// body, whose v_b and a_b are zero); the terms one by one took 65 and the node's pass bounds
+// a relativistic sweep: eih_figures.
+// e: the segment's records, slot k of node j at e[k ns + j].
 template <int R>
 static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const double (&y)[R],
                                                     const double (&z)[R], const double (&vx)[R],
@@ -835,145 +840,141 @@ static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const 
                                                     const double4* __restrict__ e, int j, int ns, int P, double inv_c2,
                                                     double (&ax)[R], double (&ay)[R], double (&az)[R])
 {
-#pragma clang fp contract(fast)
     const PcEihRecs E = pc_eih_recs(e, ns);
     const uint32_t vo = (uint32_t)j * 32u;
     auto rec = [&](int k) -> double4 { return pc_eih_load(E, k, vo); };
-    const double c35 = 3.5 * inv_c2;
-    double phi[R], v2[R], nx[R], ny[R], nz[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        phi[r] = 0.0;
-        v2[r] = vx[r] * vx[r] + vy[r] * vy[r] + vz[r] * vz[r];
-        ax[r] = ay[r] = az[r] = 0.0;
-        nx[r] = ny[r] = nz[r] = 0.0;
-    }
-    // the next body's records are loaded while this one's terms are formed
-    double4 qn = rec(0), wn = rec(1), gn = rec(2);
-    for (int b = 0; b <= P; ++b) {
-        const double4 q = qn, w = wn, g = gn;
-        if (b < P) {
-            qn = rec(3 * b + 3);
-            wn = rec(3 * b + 4);
-            gn = rec(3 * b + 5);
-        }
+    double phi[R], nx[R], ny[R], nz[R], bx[R], by[R], bz[R], K[R];
+    const double4 sun = rec(0);
+    {
+        const double mu = rec(1).w;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const double mu = w.w;
+            const double i1 = pc_rsqrt_full(pc_norm2(x[r], y[r], z[r]));
+            phi[r] = mu * i1;
+            const double m3 = phi[r] * (i1 * i1), k1 = m3 * sun.w;
+            nx[r] = m3 * x[r];
+            ny[r] = m3 * y[r];
+            nz[r] = m3 * z[r];
+            bx[r] = k1 * x[r];
+            by[r] = k1 * y[r];
+            bz[r] = k1 * z[r];
+            K[r] = m3 * fma(z[r], vz[r], fma(y[r], vy[r], x[r] * vx[r]));
+        }
+    }
+    for (int b = 1; b <= P; ++b) {
+        const double4 q = rec(3 * b), w = rec(3 * b + 1), g = rec(3 * b + 2);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
             const double dx = x[r] - q.x, dy = y[r] - q.y, dz = z[r] - q.z;
-            const double i1 = pc_rsqrt_full(dx * dx + dy * dy + dz * dz);
-            const double m1 = mu * i1;
-            const double m3 = m1 * i1 * i1;          // mu / rho^3
+            const double i1 = pc_rsqrt_full(pc_norm2(dx, dy, dz));
+            const double i2 = i1 * i1;
+            const double m1 = w.w * i1;
+            const double m3 = m1 * i2;               // mu / rho^3
             phi[r] += m1;
             nx[r] = fma(m3, dx, nx[r]);
             ny[r] = fma(m3, dy, ny[r]);
             nz[r] = fma(m3, dz, nz[r]);
-            const double vbv = vx[r] * w.x + vy[r] * w.y + vz[r] * w.z;
-            const double dwb = dx * w.x + dy * w.y + dz * w.z;   // d.v_b
-            const double dvb = dwb * i1;
-            const double dab = dx * g.x + dy * g.y + dz * g.z;
-            const double s = q.w - v2[r] + 4.0 * vbv + 1.5 * dvb * dvb + 0.5 * dab;   // q.w = U_b - 2 v_b^2
-            const double k1 = -m3 * fma(-inv_c2, s, 1.0);
-            const double dv = dx * vx[r] + dy * vy[r] + dz * vz[r];
-            const double k2 = inv_c2 * m3 * fma(4.0, dv, -3.0 * dwb);   // d.(4 v - 3 v_b)
-            const double k3 = c35 * m1;
-            ax[r] += k1 * dx + k2 * (vx[r] - w.x) + k3 * g.x;
-            ay[r] += k1 * dy + k2 * (vy[r] - w.y) + k3 * g.y;
-            az[r] += k1 * dz + k2 * (vz[r] - w.z) + k3 * g.z;
+            const double dw = fma(dz, w.z, fma(dy, w.y, dx * w.x));   // 4 d.v_b
+            const double dg = fma(dz, g.z, fma(dy, g.y, dx * g.x));   // 7/2 d.a_b
+            const double dv = fma(dz, vz[r], fma(dy, vy[r], dx * vx[r]));
+            const double c = 0.09375 * dw;                            // 3/32
+            double s = fma(vz[r], w.z, fma(vy[r], w.y, fma(vx[r], w.x, q.w)));
+            s = fma(c * i2, dw, s);
+            s = fma(1.0 / 7.0, dg, s);
+            const double k1 = m3 * s, k2 = m3 * fma(-2.0, c, dv);
+            K[r] += k2;
+            bx[r] = fma(m1, g.x, fma(-k2, w.x, fma(k1, dx, bx[r])));
+            by[r] = fma(m1, g.y, fma(-k2, w.y, fma(k1, dy, by[r])));
+            bz[r] = fma(m1, g.z, fma(-k2, w.z, fma(k1, dz, bz[r])));
         }
     }
     const double4 ind = rec(3 * (P + 1));
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const double f = 4.0 * inv_c2 * phi[r];
-        ax[r] = fma(f, nx[r], ax[r]) - ind.x;
-        ay[r] = fma(f, ny[r], ay[r]) - ind.y;
-        az[r] = fma(f, nz[r], az[r]) - ind.z;
+        const double f = fma(4.0, phi[r], -pc_norm2(vx[r], vy[r], vz[r])), k4 = 4.0 * K[r];
+        ax[r] = fma(inv_c2, fma(k4, vx[r], fma(f, nx[r], bx[r])), -nx[r]) - ind.x;
+        ay[r] = fma(inv_c2, fma(k4, vy[r], fma(f, ny[r], by[r])), -ny[r]) - ind.y;
+        az[r] = fma(inv_c2, fma(k4, vz[r], fma(f, nz[r], bz[r])), -nz[r]) - ind.z;
     }
 }
 
-// Vector-Jacobian product of the relativistic acceleration of pc_force_eih at the lane's points:
-// with s = u . a, gr = ds/dr = (da/dr)^T u and gv = ds/dv = (da/dv)^T u (the adjoint's
-// J^T w with u = w_v).  Per body, with d, rho, m3 = mu/rho^3, m5 = 3 mu/rho^5,
-// S = U_b - v^2 - 2 v_b^2 + 4 v.v_b + 3/2 (d.v_b/rho)^2 + 1/2 d.a_b, q = 4 v - 3 v_b and
-// e = 1/c^2:
-//   gv += e m3 [-(u.d)(2 v - 4 v_b) + (d.q) u + 4 (u.(v - v_b)) d]
-//   gr += (1 - e S) (m5 (u.d) d - m3 u) + e m3 (u.d) dS/dr
-//         + e (u.(v - v_b)) (m3 q - m5 (d.q) d) - 7/2 e (u.a_b) m3 d,
-//   dS/dr = 3 (d.v_b/rho) (v_b - (d.v_b/rho) d/rho)/rho + a_b/2,
-// and the terms through Phi = sum_b mu_b/rho_b, whose gradient is -N with
-// N = sum_b m3 d: gr += -4 e Phi H - 4 e (u.N) N, H = sum_b (m5 (u.d) d - m3 u).  At
-// e = 0 this is the point-mass Hessian product (symmetric in r).  The indirect term does
-// not depend on the state.  Records as pc_force_eih, point p at node jn[p / 2].
-static __device__ __forceinline__ void pc_eih_vjp(const double (&x)[4], const double (&y)[4], const double (&z)[4],
-                                                  const double (&vx)[4], const double (&vy)[4],
-                                                  const double (&vz)[4], const double (&ux)[4],
-                                                  const double (&uy)[4], const double (&uz)[4],
-                                                  const double4* __restrict__ e, const int (&jn)[2], int ns, int P,
-                                                  double inv_c2, double (&grx)[4], double (&gry)[4],
-                                                  double (&grz)[4], double (&gvx)[4], double (&gvy)[4],
-                                                  double (&gvz)[4])
+// Vector-Jacobian product of that acceleration at one point: gr = (da/dr)^T u and
+// gv = (da/dv)^T u (the adjoint's J^T w with u = w_v).  Per body, with m3 = mu/rho^3,
+// m5 = 3 mu/rho^5, s the bracket without 4 Phi - v^2, W = 4 v_b, G = 7/2 a_b and
+// z = 4 u.(v - v_b), the gradients of u.a are collected along the directions they lie on:
+//   H  = sum (m5 (u.d) d - m3 u),   N = sum m3 d,   U = u.N = sum m3 u.d,
+//   gv = e [ sum (m3 z d + m3 (u.d) W) + 4 K u - 2 U v ],
+//   gr = H + e [ sum (kd d + kw W + kg G) + S u + Z v - (4 Phi - v^2) H - 4 U N ],
+//   kd = -s m5 (u.d) - (3/16) m3 (u.d) (d.W)^2/rho^4 - 3 m3 z q/rho^2 - m3 u.G,  q = d.v - (3/16) d.W
+//   kw = (3/16) (m3 (u.d) (d.W)/rho^2 - m3 z),   kg = m3 (u.d) / 7,
+//   K = sum m3 q,   S = sum m3 s,   Z = sum m3 z.
+// 84 FP64 instructions per body (term by term about 135).  At e = 0 this is the point-mass
+// Hessian product (symmetric in r); the indirect term does not depend on the state.
+// Records as pc_force_eih.
+static __device__ __forceinline__ void pc_eih_vjp(double x, double y, double z, double vx, double vy, double vz,
+                                                  double ux, double uy, double uz, const PcEihRecs& E, int j, int P,
+                                                  double inv_c2, double (&gr)[3], double (&gv)[3])
 {
-#pragma clang fp contract(fast)
-    const PcEihRecs E = pc_eih_recs(e, ns);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint32_t vo = (uint32_t)jn[r >> 1] * 32u;
-        auto rec = [&](int k, int) -> double4 { return pc_eih_load(E, k, vo); };
-        double phi = 0.0, v2 = vx[r] * vx[r] + vy[r] * vy[r] + vz[r] * vz[r];
-        double nx = 0.0, ny = 0.0, nz = 0.0, hx = 0.0, hy = 0.0, hz = 0.0;
-        double ax = 0.0, ay = 0.0, az = 0.0, bx = 0.0, by = 0.0, bz = 0.0;
-        for (int b = 0; b <= P; ++b) {
-            const double4 q = rec(3 * b, r), w = rec(3 * b + 1, r), g = rec(3 * b + 2, r);
-            const double mu = w.w;
-            const double dx = x[r] - q.x, dy = y[r] - q.y, dz = z[r] - q.z;
-            const double i1 = pc_rsqrt_full(dx * dx + dy * dy + dz * dz);
-            const double m1 = mu * i1, m3 = m1 * i1 * i1, m5 = 3.0 * m3 * i1 * i1;
-            phi += m1;
-            nx = fma(m3, dx, nx);
-            ny = fma(m3, dy, ny);
-            nz = fma(m3, dz, nz);
-            const double ud = ux[r] * dx + uy[r] * dy + uz[r] * dz;
-            // Newtonian part of the bracket, kept apart for the term in Phi
-            const double tx = m5 * ud * dx - m3 * ux[r], ty = m5 * ud * dy - m3 * uy[r], tz = m5 * ud * dz - m3 * uz[r];
-            hx += tx;
-            hy += ty;
-            hz += tz;
-            const double vbv = vx[r] * w.x + vy[r] * w.y + vz[r] * w.z;
-            const double dwb = dx * w.x + dy * w.y + dz * w.z;
-            const double dvb = dwb * i1;
-            const double dab = dx * g.x + dy * g.y + dz * g.z;
-            const double S = q.w - v2 + 4.0 * vbv + 1.5 * dvb * dvb + 0.5 * dab;   // q.w = U_b - 2 v_b^2
-            const double dq = fma(4.0, dx * vx[r] + dy * vy[r] + dz * vz[r], -3.0 * dwb);
-            const double uvw = ux[r] * (vx[r] - w.x) + uy[r] * (vy[r] - w.y) + uz[r] * (vz[r] - w.z);
-            const double ug = ux[r] * g.x + uy[r] * g.y + uz[r] * g.z;
-            // dS/dr
-            const double c1 = 3.0 * dvb * i1, c2 = c1 * dvb * i1;
-            const double sx = c1 * w.x - c2 * dx + 0.5 * g.x;
-            const double sy = c1 * w.y - c2 * dy + 0.5 * g.y;
-            const double sz = c1 * w.z - c2 * dz + 0.5 * g.z;
-            const double k0 = -S;                       // times e, on the Newtonian bracket
-            const double k1 = m3 * ud;                  // times e, on dS/dr
-            const double k2 = uvw;                      // times e, on m3 q - m5 (d.q) d
-            const double k3 = -3.5 * ug * m3;           // times e, on d
-            ax += k0 * tx + k1 * sx + k2 * (m3 * (4.0 * vx[r] - 3.0 * w.x) - m5 * dq * dx) + k3 * dx;
-            ay += k0 * ty + k1 * sy + k2 * (m3 * (4.0 * vy[r] - 3.0 * w.y) - m5 * dq * dy) + k3 * dy;
-            az += k0 * tz + k1 * sz + k2 * (m3 * (4.0 * vz[r] - 3.0 * w.z) - m5 * dq * dz) + k3 * dz;
-            // velocity gradient
-            bx += m3 * (-ud * (2.0 * vx[r] - 4.0 * w.x) + dq * ux[r] + 4.0 * uvw * dx);
-            by += m3 * (-ud * (2.0 * vy[r] - 4.0 * w.y) + dq * uy[r] + 4.0 * uvw * dy);
-            bz += m3 * (-ud * (2.0 * vz[r] - 4.0 * w.z) + dq * uz[r] + 4.0 * uvw * dz);
-        }
-        const double un = ux[r] * nx + uy[r] * ny + uz[r] * nz;
-        const double fp = -4.0 * inv_c2 * phi, fn = -4.0 * inv_c2 * un;
-        grx[r] = hx + inv_c2 * ax + fp * hx + fn * nx;
-        gry[r] = hy + inv_c2 * ay + fp * hy + fn * ny;
-        grz[r] = hz + inv_c2 * az + fp * hz + fn * nz;
-        gvx[r] = inv_c2 * bx;
-        gvy[r] = inv_c2 * by;
-        gvz[r] = inv_c2 * bz;
+    const uint32_t vo = (uint32_t)j * 32u;
+    auto rec = [&](int k) -> double4 { return pc_eih_load(E, k, vo); };
+    const double uv4 = 4.0 * fma(uz, vz, fma(uy, vy, ux * vx));
+    double phi = 0.0, K = 0.0, M = 0.0, S = 0.0, Z = 0.0, U = 0.0;
+    double nx = 0.0, ny = 0.0, nz = 0.0, hx = 0.0, hy = 0.0, hz = 0.0, ax = 0.0, ay = 0.0, az = 0.0;
+    double bx = 0.0, by = 0.0, bz = 0.0;
+    for (int b = 0; b <= P; ++b) {
+        const double4 q = rec(3 * b), w = rec(3 * b + 1), g = rec(3 * b + 2);
+        const double dx = x - q.x, dy = y - q.y, dz = z - q.z;
+        const double i1 = pc_rsqrt_full(pc_norm2(dx, dy, dz));
+        const double i2 = i1 * i1, m1 = w.w * i1, m3 = m1 * i2;
+        phi += m1;
+        M += m3;
+        nx = fma(m3, dx, nx);
+        ny = fma(m3, dy, ny);
+        nz = fma(m3, dz, nz);
+        const double ud = fma(uz, dz, fma(uy, dy, ux * dx));
+        const double dw = fma(dz, w.z, fma(dy, w.y, dx * w.x));
+        const double dg = fma(dz, g.z, fma(dy, g.y, dx * g.x));
+        const double dv = fma(dz, vz, fma(dy, vy, dx * vx));
+        const double uw = fma(uz, w.z, fma(uy, w.y, ux * w.x));
+        const double ug = fma(uz, g.z, fma(uy, g.y, ux * g.x));
+        const double c = dw * i2;
+        double s = fma(vz, w.z, fma(vy, w.y, fma(vx, w.x, q.w)));
+        s = fma(0.09375 * c, dw, s);
+        s = fma(1.0 / 7.0, dg, s);
+        const double qd = fma(-0.1875, dw, dv);
+        const double mud = m3 * ud, mz = m3 * (uv4 - uw);
+        U += mud;
+        Z += mz;
+        K = fma(m3, qd, K);
+        S = fma(s, m3, S);
+        const double p = 3.0 * (mud * i2);
+        const double t = 0.1875 * (c * mud);
+        double kd = fma(-s, p, -(m3 * ug));
+        kd = fma(-t, c, kd);
+        kd = fma(-3.0 * (i2 * mz), qd, kd);
+        const double kw = fma(-0.1875, mz, t), kg = (1.0 / 7.0) * mud;
+        hx = fma(p, dx, hx);
+        hy = fma(p, dy, hy);
+        hz = fma(p, dz, hz);
+        ax = fma(kg, g.x, fma(kw, w.x, fma(kd, dx, ax)));
+        ay = fma(kg, g.y, fma(kw, w.y, fma(kd, dy, ay)));
+        az = fma(kg, g.z, fma(kw, w.z, fma(kd, dz, az)));
+        bx = fma(mud, w.x, fma(mz, dx, bx));
+        by = fma(mud, w.y, fma(mz, dy, by));
+        bz = fma(mud, w.z, fma(mz, dz, bz));
     }
+    hx = fma(-M, ux, hx);
+    hy = fma(-M, uy, hy);
+    hz = fma(-M, uz, hz);
+    const double f = fma(4.0, phi, -pc_norm2(vx, vy, vz)), u4 = 4.0 * U, u2 = 2.0 * U, k4 = 4.0 * K;
+    gr[0] = fma(inv_c2, fma(-u4, nx, fma(-f, hx, fma(Z, vx, fma(S, ux, ax)))), hx);
+    gr[1] = fma(inv_c2, fma(-u4, ny, fma(-f, hy, fma(Z, vy, fma(S, uy, ay)))), hy);
+    gr[2] = fma(inv_c2, fma(-u4, nz, fma(-f, hz, fma(Z, vz, fma(S, uz, az)))), hz);
+    gv[0] = inv_c2 * fma(-u2, vx, fma(k4, ux, bx));
+    gv[1] = inv_c2 * fma(-u2, vy, fma(k4, uy, by));
+    gv[2] = inv_c2 * fma(-u2, vz, fma(k4, uz, bz));
 }
+
 // Software-pipelined k loop of a 16x16x4 product over nq steps (a multiple of 4, at most
 // NQ, at least 8 when NQ is; NQ fixes the layout of the operands).  The A operand of step q
 // (a K_N fragment, read from L2) is loaded DK steps ahead into a ring of DK registers, the

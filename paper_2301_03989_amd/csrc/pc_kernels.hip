@@ -69,8 +69,9 @@ __global__ void pc_ephem_kernel(const PcEphemParams p)
             const double iq3 = 1.0 / (q * q * q);   // Keplerian orbit about the central body
             const double vb2 = vb[b][0] * vb[b][0] + vb[b][1] * vb[b][1] + vb[b][2] * vb[b][2];
             er(3 * (b + 1)) = make_double4(rb[b][0], rb[b][1], rb[b][2], u - 2.0 * vb2);
-            er(3 * (b + 1) + 1) = make_double4(vb[b][0], vb[b][1], vb[b][2], p.bodies[b].mu);
-            er(3 * (b + 1) + 2) = make_double4(-rb[b][0] * iq3, -rb[b][1] * iq3, -rb[b][2] * iq3, 0.0);
+            er(3 * (b + 1) + 1) = make_double4(4.0 * vb[b][0], 4.0 * vb[b][1], 4.0 * vb[b][2], p.bodies[b].mu);
+            er(3 * (b + 1) + 2) =
+                make_double4(-3.5 * rb[b][0] * iq3, -3.5 * rb[b][1] * iq3, -3.5 * rb[b][2] * iq3, 0.0);
         }
         er(0) = make_double4(0.0, 0.0, 0.0, u0);
         er(1) = make_double4(0.0, 0.0, 0.0, p.mu_sun);
@@ -954,7 +955,7 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
     double* sF = sm.F;
     double* sY0 = sm.Y0;
     const int tid = threadIdx.x;
-    const PcLane L = pc_lane_geometry<PAIRS, NP>(tid, g.N);
+    PcLane L = pc_lane_geometry<PAIRS, NP>(tid, g.N);
     const int N = g.N, S = g.S, P = p.n_pert;
     const int n = job.n;
     const int64_t ic = job.ic0 + tid;
@@ -1031,16 +1032,25 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
         const double Ts = g.t0 + g.h * s, Te = g.t0 + g.h * (s + 1);
         const double w2 = 0.5 * (Te - Ts);
 
-        // seed of this segment at the lane's point (h, r): the next segment's gradient at the
+        // seed of this segment at the lane's point q = 2h + r: the next segment's gradient at the
         // end node, plus the node seeds when given (recomputed where needed, not held); none at
         // a middle node's second place
-        auto seed = [&](int c, int h, int r) __attribute__((always_inline)) -> double {
-            const int m = pc_ic<PAIRS, NP>(L, h, r);
-            if (!L.ok || (Sh::PAR && h == 1 && !L.two)) return 0.0;
-            double v = L.jn[h] == N - 1 ? sLam[c * T + m] : 0.0;
-            if (a.gbar_nodes && m < n)
-                v += pc_gcd(a.gbar_nodes)[(((size_t)(job.ic0 + m) * a.ckpt_stride + s) * a.nodes_stride + L.jn[h]) * 6 + c];
-            return v;
+        const gconst_dp g_seed = pc_gcd(a.gbar_nodes);
+        auto seeds = [&](int q, double (&sd)[6]) __attribute__((always_inline)) {
+            const int h = q >> 1, m = pc_ic<PAIRS, NP>(L, h, q & 1), j = L.jn[h];
+            const bool on = L.ok && !(Sh::PAR && h == 1 && !L.two);
+#pragma unroll
+            for (int c = 0; c < 6; ++c) sd[c] = 0.0;
+            if (g_seed && on && m < n) {
+                const gconst_dp v = g_seed + (((size_t)(job.ic0 + m) * a.ckpt_stride + s) * a.nodes_stride + j) * 6;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) sd[c] = v[c];
+            }
+            if (L.strip == (Sh::PAR ? 0 : (N - 1) >> 4)) {   // the strip of the last node
+                const bool end = on && j == N - 1;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) sd[c] += end ? sLam[c * T + m] : 0.0;
+            }
         };
         if (tid < T) {
             sm.Active[tid] = (tid < n) && !sm.Dead[tid];
@@ -1050,63 +1060,74 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
         // mu^(0) = gbar
         if (L.ok) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) {
+            for (int r = 0; r < 2; ++r) {
+                double sl[6], sr[6];
+                seeds(r, sl);
+                seeds(2 + r, sr);
 #pragma unroll
-                for (int r = 0; r < 2; ++r) put_mu(c, r, seed(c, 0, r), seed(c, 1, r));
+                for (int c = 0; c < 6; ++c) put_mu(c, r, sl[c], sr[c]);
             }
         }
         __syncthreads();
 
         int it = 1;
         for (; it <= a.adj_max_iter; ++it) {
+            L = pc_lane_again<PAIRS, NP>(L, N);
             f64x4 acc[6];
             pc_product_adj<PAIRS, NP>(sF, kpT, wr, acc, L);          // w = K^T mu
-            double x[4], y[4], z[4], wx[4], wy[4], wz[4], hx[4], hy[4], hz[4];
-            pc_points(yc, 0, x);
-            pc_points(yc, 1, y);
-            pc_points(yc, 2, z);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                wx[q] = acc[3 * (q >> 1)][2 + (q & 1)];
-                wy[q] = acc[3 * (q >> 1) + 1][2 + (q & 1)];
-                wz[q] = acc[3 * (q >> 1) + 2][2 + (q & 1)];
-            }
-            double gx[4] = {}, gy[4] = {}, gz[4] = {};   // (da/dv)^T w_v (relativistic)
+            // mu_new = gbar + J^T w: position rows w2 (da/dr)^T w_v, velocity rows w2 w_r (and the
+            // relativistic (da/dv)^T w_v)
             if constexpr (EIH) {
-                double vx[4], vy[4], vz[4];
+                const PcEihRecs R = pc_eih_recs(erec, N);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    vx[q] = yc[3 * (q >> 1)][2 + (q & 1)];
-                    vy[q] = yc[3 * (q >> 1) + 1][2 + (q & 1)];
-                    vz[q] = yc[3 * (q >> 1) + 2][2 + (q & 1)];
-                }
-                pc_eih_vjp(x, y, z, vx, vy, vz, wx, wy, wz, erec, L.jn, N, P, p.inv_c2, hx, hy, hz, gx, gy, gz);
-            } else if (rec_lds) {
-                pc_hess_apply<true>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
-            } else {
-                pc_hess_apply<false>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
-            }
-            // mu_new = gbar + J^T w, and its sum over the strip's nodes (the 16 lanes of a row
-            // group hold the rows of the same ICs)
-            const bool right = !Sh::PAR || L.two;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int h = q >> 1, r = q & 1;
-                const double p0 = acc[3 * h][r], p1 = acc[3 * h + 1][r], p2 = acc[3 * h + 2][r];
-                acc[3 * h][r] = fma(w2, hx[q], seed(0, h, r));
-                acc[3 * h + 1][r] = fma(w2, hy[q], seed(1, h, r));
-                acc[3 * h + 2][r] = fma(w2, hz[q], seed(2, h, r));
-                acc[3 * h][2 + r] = fma(w2, EIH ? p0 + gx[q] : p0, seed(3, h, r));
-                acc[3 * h + 1][2 + r] = fma(w2, EIH ? p1 + gy[q] : p1, seed(4, h, r));
-                acc[3 * h + 2][2 + r] = fma(w2, EIH ? p2 + gz[q] : p2, seed(5, h, r));
-                if (h == 1) {
+                    const int h = 3 * (q >> 1), r = q & 1;
+                    double gr[3], gv[3];
+                    pc_eih_vjp(yc[h][r], yc[h + 1][r], yc[h + 2][r], yc[h][2 + r], yc[h + 1][2 + r], yc[h + 2][2 + r],
+                               acc[h][2 + r], acc[h + 1][2 + r], acc[h + 2][2 + r], R, L.jn[q >> 1], P, p.inv_c2, gr, gv);
 #pragma unroll
                     for (int b = 0; b < 3; ++b) {
-                        acc[3 + b][r] = right ? acc[3 + b][r] : 0.0;
-                        acc[3 + b][2 + r] = right ? acc[3 + b][2 + r] : 0.0;
+                        acc[h + b][2 + r] = acc[h + b][r] + gv[b];
+                        acc[h + b][r] = gr[b];
                     }
                 }
+            } else {
+                double x[4], y[4], z[4], wx[4], wy[4], wz[4], hx[4], hy[4], hz[4];
+                pc_points(yc, 0, x);
+                pc_points(yc, 1, y);
+                pc_points(yc, 2, z);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    wx[q] = acc[3 * (q >> 1)][2 + (q & 1)];
+                    wy[q] = acc[3 * (q >> 1) + 1][2 + (q & 1)];
+                    wz[q] = acc[3 * (q >> 1) + 2][2 + (q & 1)];
+                }
+                if (rec_lds) pc_hess_apply<true>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
+                else pc_hess_apply<false>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int h = 3 * (q >> 1), r = q & 1;
+#pragma unroll
+                    for (int b = 0; b < 3; ++b) acc[h + b][2 + r] = acc[h + b][r];
+                    acc[h][r] = hx[q];
+                    acc[h + 1][r] = hy[q];
+                    acc[h + 2][r] = hz[q];
+                }
             }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                double sd[6];
+                seeds(q, sd);
+                const bool on = (q >> 1) == 0 || !Sh::PAR || L.two;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) {
+                    const int k = 3 * (q >> 1) + c % 3, r = (q & 1) + 2 * (c / 3);
+                    const double v = fma(w2, acc[k][r], sd[c]);
+                    acc[k][r] = q < 2 || on ? v : 0.0;   // no second place at a middle node
+                }
+            }
+            // the sum over the strip's nodes (the 16 lanes of a row group hold the rows of the
+            // same ICs)
 #pragma unroll
             for (int c = 0; c < 6; ++c) {
 #pragma unroll
