@@ -1683,4 +1683,64 @@ static __device__ __forceinline__ void pc_publish_chord(float* sD, float* sG, co
     }
 }
 
+// Initial guess of segment s at the lane's points: warm (Kepler) or cold start, Sec. 2.1, or the
+// caller's node states; each staged in the lane's own part of the F area (one call site, no
+// private array).  sY0, dead: initial states and status of the job's n ICs (the first is ic0).
+template <int PAIRS, int NP>
+static __device__ __forceinline__ void pc_initial_guess(const PcParams& p, const PcGroupDev& g, int n, int64_t ic0,
+                                                        int s, double w2, const PcLane& L, const double* sY0,
+                                                        const int* dead, double* sF, double (&yc)[6][4])
+{
+    using Sh = PcShape<PAIRS, NP>;
+    constexpr int NT = Sh::NT, T = Sh::T;
+    const int tid = threadIdx.x;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        const int j = q < 2 ? L.jn[0] : L.jn[1];
+        const int m = pc_ic<PAIRS, NP>(L, q >> 1, q & 1);
+        double y0[6], y[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) y0[c] = sY0[c * T + m];
+        bool have = false;
+        if (!dead[m]) {
+            if (p.init == 2 && m < n) {   // the caller's node states
+                const gconst_dp gp =
+                    pc_gcd(p.guess) + (((size_t)(ic0 + m) * p.iters_stride + s) * p.nodes_stride + j) * 6;
+                have = true;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) {
+                    y[c] = gp[c];
+                    have = have && isfinite(y[c]);
+                }
+            } else if (p.init == 0) {
+                have = pc_kepler(y0, w2 * (pc_gcd(g.tau)[j] + 1.0), y);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) sF[(q * 6 + c) * NT + tid] = have ? y[c] : y0[c];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) yc[3 * (q >> 1) + c % 3][(q & 1) + 2 * (c / 3)] = sF[(q * 6 + c) * NT + tid];
+    }
+}
+
+// The rows of F past the last one holding nodes are zero (they meet zero operator columns,
+// which a stale NaN would survive), and so are the unused halves of the second-order blocks.
+template <int PAIRS, int NP, bool SO>
+static __device__ __forceinline__ void pc_clear_rows(double* sF, int N)
+{
+    using Sh = PcShape<PAIRS, NP>;
+    const int M = Sh::PAR ? (N + 1) >> 1 : N;
+    for (int i = M * Sh::ROW + (int)threadIdx.x; i < Sh::KR * Sh::ROW; i += Sh::NT) sF[i] = 0.0;
+    if constexpr (SO) {
+        for (int k = threadIdx.x; k < M * Sh::GN * 16; k += Sh::NT) {
+            const int i = k & 15, q = k >> 4;
+            const int u = pc_unit<PAIRS, NP>(q / Sh::GN, q % Sh::GN, i < 8 ? 2 : 1, i);
+            reinterpret_cast<pc_d2v*>(sF)[u] = pc_d2v{0.0, 0.0};
+        }
+    }
+}
+
 #pragma clang fp contract(fast)

@@ -196,23 +196,6 @@ static __device__ __forceinline__ void pc_stage_records(const double4* grec, int
     }
 }
 
-// The rows of F past the last one holding nodes are zero (they meet zero operator columns,
-// which a stale NaN would survive), and so are the unused halves of the second-order blocks.
-template <int PAIRS, int NP, bool SO>
-static __device__ __forceinline__ void pc_clear_rows(double* sF, int N)
-{
-    using Sh = PcShape<PAIRS, NP>;
-    const int M = Sh::PAR ? (N + 1) >> 1 : N;
-    for (int i = M * Sh::ROW + (int)threadIdx.x; i < Sh::KR * Sh::ROW; i += Sh::NT) sF[i] = 0.0;
-    if constexpr (SO) {
-        for (int k = threadIdx.x; k < M * Sh::GN * 16; k += Sh::NT) {
-            const int i = k & 15, q = k >> 4;
-            const int u = pc_unit<PAIRS, NP>(q / Sh::GN, q % Sh::GN, i < 8 ? 2 : 1, i);
-            reinterpret_cast<pc_d2v*>(sF)[u] = pc_d2v{0.0, 0.0};
-        }
-    }
-}
-
 // Picard iterations of one segment for the job's ICs (initial states in sm.Y0): ephemeris
 // records into LDS, initial guess, then sweeps until every IC of the job has stopped.
 // On return yc holds the lane's share of the final iterate.  iters_out (may be null)
@@ -226,7 +209,7 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
                                                         int rec_cap = PcSmem<PAIRS>::REC)
 {
     using Sh = PcShape<PAIRS, NP>;
-    constexpr int NT = Sh::NT, T = Sh::T;
+    constexpr int T = Sh::T;
     double* sF = sm.F;
     double* sY0 = sm.Y0;
     const double* sWt = pc_weights<PAIRS, NP>(sm);
@@ -246,38 +229,7 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
     const double4* grec = reinterpret_cast<const double4*>(p.recs) +
                           (size_t)(g.rec_offset + (int64_t)s * N) * (P + 1);
     if (rec_lds) pc_stage_records<PAIRS>(grec, N, P, sm);
-    // initial guess at the lane's points: warm (Kepler) or cold start, Sec. 2.1, each staged in
-    // the lane's own part of the F area (one call site, no private array)
-#pragma unroll 1
-    for (int q = 0; q < 4; ++q) {
-        const int j = q < 2 ? L.jn[0] : L.jn[1];
-        const int m = pc_ic<PAIRS, NP>(L, q >> 1, q & 1);
-        double y0[6], y[6];
-#pragma unroll
-        for (int c = 0; c < 6; ++c) y0[c] = sY0[c * T + m];
-        bool have = false;
-        if (!sm.Dead[m]) {
-            if (p.init == 2 && m < n) {   // the caller's node states
-                const gconst_dp gp =
-                    pc_gcd(p.guess) + (((size_t)(ic0 + m) * p.iters_stride + s) * p.nodes_stride + j) * 6;
-                have = true;
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    y[c] = gp[c];
-                    have = have && isfinite(y[c]);
-                }
-            } else if (p.init == 0) {
-                have = pc_kepler(y0, w2 * (pc_gcd(g.tau)[j] + 1.0), y);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < 6; ++c) sF[(q * 6 + c) * NT + tid] = have ? y[c] : y0[c];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int c = 0; c < 6; ++c) yc[3 * (q >> 1) + c % 3][(q & 1) + 2 * (c / 3)] = sF[(q * 6 + c) * NT + tid];
-    }
+    pc_initial_guess<PAIRS, NP>(p, g, n, ic0, s, w2, L, sY0, sm.Dead, sF, yc);
     if (tid < T) sm.Active[tid] = (tid < n) && !sm.Dead[tid];
     __syncthreads();   // staging read before F is built
     pc_clear_rows<PAIRS, NP, SO != 0>(sF, N);

@@ -1,30 +1,68 @@
-// pc_plain.hip -- the "plain" GPU path: one group at a time, a sequence of kernels per
-// Picard iteration and a host-side loop, the structure of the paper's CUDA program
-// (Sec. 5.4): dynamics kernel over all stacked states, the fit/integrate/evaluate
-// product (here one FP64 MFMA product with the +y0 term in its epilogue), the error
-// computation and its reduction, and a host check of the result every iteration.
+// pc_plain.hip -- the "plain" GPU path: one group at a time, a kernel per Picard iteration and
+// a host-side loop, the structure of the paper's CUDA program (Sec. 5.4): the iterate lives in
+// HBM between the iterations, each of which evaluates the dynamics of all stacked states, takes
+// the fit/integrate/evaluate product and the error, reduces it over the group and lets the host
+// decide whether another one follows.
 //
 // Differences from the paper's program: by default the error is per IC (converged ICs are
-// frozen and jobs whose ICs have all converged are compacted out of the next launches)
-// and the host reads back one active-job count per iteration instead of block maxima.
+// frozen and jobs whose ICs have all converged are compacted out of the next launches).
 // With PC_CONV_GROUP_MAX the paper's whole-system rule holds per group: no IC stops on
-// its own, the step kernels count the jobs that still hold a change above tol, and the
-// host ends the segment for the whole group when that count is zero.
+// its own, the sweep kernels count the jobs that still hold a change above tol, and the
+// segment ends for the whole group when that count is zero.
 //
-// State in HBM, per group: Y[node][comp 9][IC] (comps 0..5 iterate, 6..8 acceleration),
-// IC index fastest -- the component-major, row-by-node layout of Sec. 5.4.1.
+// One iteration is one kernel (pc_plain_sweep): its last workgroup to finish compacts the job
+// list and reduces the group's decision, which the host reads from pinned memory.  Separate
+// kernels for the dynamics, the product and the compaction, two copies per iteration and a
+// host round trip after each were mostly launches and gaps between kernels of 4 to 15 us: six
+// groups of 64 to 256 nodes with 2500 ICs on four streams took 12.0 ms, now 5.0.  The host
+// queues several iterations ahead of each read-back (plain_batch); the ones past the end find
+// the group's done mark and return.
+//
+// State in HBM, per job: the register image of the sweep kernel's threads, Y[job][value 24]
+// [thread] (value and thread of a node, component and IC: plain_at), so that a wave's loads and
+// stores are contiguous.
 #include "pcprop.h"
 #include "pc_device.h"
 #include "pc_plain.h"
 
 namespace {
 
-constexpr int kPlainForceBlock = 256;
+constexpr int kPlainPairs = 2048;
+constexpr int kPlainBs = 256;
 
-// Initial states of the group's ICs (padding columns copy the job's first IC).
+// Words of PcPlainArgs::count.
+enum { kCountA = 0, kCountB = 1, kOpen = 2, kArrived = 3, kDone = 4 };
+
+// Place of component c of the job's IC k at node j in its job's part of Y.
+template <int NP>
+__device__ size_t plain_at(int N, int j, int c, int k)
+{
+    using Sh = PcShape<kPlainPairs, NP>;
+    const int M = Sh::PAR ? (N + 1) >> 1 : N;
+    const int row = j < M ? j : N - 1 - j;
+    const int h = Sh::PAR ? (j < M ? 0 : 1) : (k >> 3) & 1;
+    const int m = k & 7, wave = (k / Sh::COLS) * Sh::STRIPS + (row >> 4);
+    const int value = (3 * h + c % 3) * 4 + (m >> 2) + 2 * (c / 3);
+    return (size_t)value * Sh::NT + wave * 64 + (m & 3) * 16 + (row & 15);
+}
+__device__ size_t plain_at(int NP, int N, int j, int c, int k)
+{
+    switch (NP) {
+    case 16: return plain_at<16>(N, j, c, k);
+    case 32: return plain_at<32>(N, j, c, k);
+    case 64: return plain_at<64>(N, j, c, k);
+    case 128: return plain_at<128>(N, j, c, k);
+    default: return plain_at<256>(N, j, c, k);
+    }
+}
+constexpr size_t kJobValues = (size_t)24 * (kPlainPairs / 4);   // doubles of one job in Y
+
+// Initial states of the group's ICs (padding columns copy the job's first IC), their records,
+// the first boundary record and the group's counters.
 __global__ void pc_plain_load(PcPlainArgs a)
 {
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (m < 5) a.count[m] = 0;
     if (m >= a.Mpad) return;
     const PcJobDev job = a.jobs[m / a.T];
     const int i = (int)(m % a.T);
@@ -34,315 +72,223 @@ __global__ void pc_plain_load(PcPlainArgs a)
         const double v = y[c];
         a.Y0[c * a.Mpad + m] = v;
         fin = fin && isfinite(v);
+        if (i < job.n && a.p.bounds_out) a.p.bounds_out[(size_t)(job.ic0 + i) * (a.p.iters_stride + 1) * 6 + c] = v;
     }
     a.dead[m] = !fin;
     a.notconv[m] = 0;
     a.valid[m] = i < job.n;
 }
 
-// Segment start: initial guess (Kepler or cold, Sec. 2.1) at every (node, IC) pair,
-// zero padding rows, flags and the full job list.
-__global__ void pc_plain_init(PcPlainArgs a, int s, double w2)
+// Sweep `it` of segment s, one active job per workgroup: the job's iterate (the initial guess
+// on the first sweep, which runs every job), its dynamics, the product y_new = y0 + w2 K_N F
+// with the error of every IC, the stopping decision, and the new iterate of the ICs that were
+// iterating.  Bound by latency: a group rarely fills the chip.
+template <int NP, bool EIH>
+__global__ __launch_bounds__(kPlainPairs / 4, 2) void pc_plain_sweep(PcPlainArgs a, int s, int it, double w2)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t total = (int64_t)a.NP * a.Mpad;
-    if (idx < a.n_jobs) a.job_list[idx] = (int32_t)idx;
-    if (idx == 0) {
-        a.count[0] = a.n_jobs;
-        a.count[2] = 0;
-    }
-    if (idx >= total) return;
-    const int j = (int)(idx / a.Mpad);
-    const int64_t m = idx - (int64_t)j * a.Mpad;
-    double* Yj = a.Y + (size_t)j * 9 * a.Mpad + m;
-    if (j >= a.N) {
-        for (int c = 0; c < 9; ++c) Yj[c * a.Mpad] = 0.0;
-        return;
-    }
-    double y0[6], y[6];
-    for (int c = 0; c < 6; ++c) y0[c] = a.Y0[c * a.Mpad + m];
-    const bool dead = a.dead[m];
-    bool have = false;
-    if (a.p.init == 2 && !dead && a.valid[m]) {   // the caller's node states
-        const PcJobDev job = a.jobs[m / a.T];
-        const double* gp =
-            a.p.guess + (((size_t)(job.ic0 + m % a.T) * a.p.iters_stride + s) * a.p.nodes_stride + j) * 6;
-        have = true;
-        for (int c = 0; c < 6; ++c) {
-            y[c] = gp[c];
-            have = have && isfinite(y[c]);
-        }
-    } else if (a.p.init == 0 && !dead) {
-        have = pc_kepler(y0, w2 * (a.g->tau[j] + 1.0), y);
-    }
-    if (!have)
-        for (int c = 0; c < 6; ++c) y[c] = y0[c];
-    for (int c = 0; c < 6; ++c) Yj[c * a.Mpad] = y[c];
-    if (j == 0) {
-        a.active[m] = a.valid[m] && !dead;
-        if (dead && a.valid[m] && a.p.iters_out) {
-            const PcJobDev job = a.jobs[m / a.T];
-            a.p.iters_out[(size_t)(job.ic0 + m % a.T) * a.p.iters_stride + s] = -2;
-        }
-    }
-}
-
-// Dynamics at every (node, IC) pair of the active jobs (the paper's dynamics kernel):
-// one thread per pair, state read from and acceleration written to HBM.
-__global__ __launch_bounds__(kPlainForceBlock) void pc_plain_force(PcPlainArgs a, int s)
-{
-    const int bpj = (a.NP * a.T) / kPlainForceBlock;          // blocks per job
-    const int job = a.job_list[blockIdx.x / bpj];
-    const int pr = (blockIdx.x % bpj) * kPlainForceBlock + threadIdx.x;
-    const int j = pr / a.T;
-    const int64_t m = (int64_t)job * a.T + pr % a.T;
-    if (j >= a.N || !a.active[m]) return;
-    const int P = a.p.n_pert;
-    double* Yj = a.Y + (size_t)j * 9 * a.Mpad + m;
-    if (a.p.inv_c2 != 0.0) {
-        // relativistic model: the segment's records of the major bodies (slot-major)
-        const double4* erec = reinterpret_cast<const double4*>(a.p.recs_eih) +
-                              (size_t)(a.g->rec_offset + (int64_t)s * a.N) * pc_eih_rec(P);
-        const double x[1] = {Yj[0]}, y[1] = {Yj[a.Mpad]}, z[1] = {Yj[2 * a.Mpad]};
-        const double vx[1] = {Yj[3 * a.Mpad]}, vy[1] = {Yj[4 * a.Mpad]}, vz[1] = {Yj[5 * a.Mpad]};
-        double ax[1], ay[1], az[1];
-        pc_force_eih<1>(x, y, z, vx, vy, vz, erec, j, a.N, P, a.p.inv_c2, ax, ay, az);
-        Yj[6 * a.Mpad] = ax[0];
-        Yj[7 * a.Mpad] = ay[0];
-        Yj[8 * a.Mpad] = az[0];
-        return;
-    }
-    const double4* rec = reinterpret_cast<const double4*>(a.p.recs) +
-                         (size_t)(a.g->rec_offset + (int64_t)s * a.N + j) * (P + 1);
-    double ax, ay, az;
-    pc_accel(Yj[0], Yj[a.Mpad], Yj[2 * a.Mpad], rec, P, a.p.mu_sun, ax, ay, az);
-    Yj[6 * a.Mpad] = ax;
-    Yj[7 * a.Mpad] = ay;
-    Yj[8 * a.Mpad] = az;
-}
-
-// The product y_new = y0 + w2 K_N F for one active job per workgroup, with the error of
-// every IC against the previous iterate and the stopping decision in the epilogue.  The
-// job's state moves between HBM and LDS with IC-contiguous (coalesced) accesses; the
-// lanes' shares of it come from LDS.
-template <int PAIRS, int NP>
-__global__ __launch_bounds__(PAIRS / 4) void pc_plain_step(PcPlainArgs a, int s, int it, double w2)
-{
+    constexpr int PAIRS = kPlainPairs;
     using Sh = PcShape<PAIRS, NP>;
     constexpr int NT = Sh::NT, T = Sh::T, KR = Sh::KR;
-    __shared__ alignas(16) double sF[6 * PAIRS];   // the current iterate, then F, then the new iterate
+    __shared__ alignas(16) double sF[6 * PAIRS];
     __shared__ double sY0[6 * T];
     __shared__ double sWt[2 * KR];
     __shared__ int sFlag[Sh::W * 16];
     __shared__ int sActive[T];
-    __shared__ int sWas[T];
+    __shared__ int sDead[T];
     __shared__ int sOpen;   // group-max rule: some IC of the job changed by more than tol
+    __shared__ int sLast, sBase;
+    __shared__ int sSum[Sh::W];
 
     const int tid = threadIdx.x;
-    const int job = a.job_list[blockIdx.x];
-    const int64_t m0 = (int64_t)job * T;
-    const int N = a.N, M = Sh::PAR ? (N + 1) >> 1 : N;
-    const PcLane L = pc_lane_geometry<PAIRS, NP>(tid, N);
-    const size_t row = (size_t)9 * a.Mpad;
-    pc_d2v* f = reinterpret_cast<pc_d2v*>(sF);
-
-    // place of component c of the job's IC k in row i of sF, and the whole array by (row, half,
-    // component, IC) with the IC fastest: every node once
-    auto place = [&](int i, int c, int k) { return pc_unit<PAIRS, NP>(i, k / Sh::COLS, c % 3, 8 * (c / 3) + (k & 7)); };
-    auto each = [&](auto use) {
-        for (int q = tid; q < 6 * PAIRS; q += NT) {
-            const int k = q % T, c = (q / T) % 6, n = q / (6 * T);
-            const int i = Sh::PAR ? n >> 1 : n, h = Sh::PAR ? n & 1 : (k >> 3) & 1;
-            if (i >= M || (Sh::PAR && h && 2 * i == N - 1)) continue;
-            use(Sh::PAR && h ? N - 1 - i : i, c, k, sF + 2 * place(i, c, k) + h);
-        }
-    };
-    each([&](int j, int c, int k, double* at) { *at = a.Y[(size_t)j * row + (size_t)c * a.Mpad + m0 + k]; });
-    for (int i = tid; i < 6 * T; i += NT) sY0[i] = a.Y0[(size_t)(i / T) * a.Mpad + m0 + i % T];
-    if constexpr (Sh::PAR) {
-        for (int i = tid; i < 2 * KR; i += NT) sWt[i] = pc_gcd(a.g->wts)[i];
-    }
-    if (tid < T) {
-        sActive[tid] = a.active[m0 + tid];
-        sWas[tid] = sActive[tid];
-    }
-    if (tid == 0) sOpen = 0;
-    __syncthreads();
-    double yc[6][4];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int u = pc_unit<PAIRS, NP>(L.ok ? L.row : M - 1, L.grp, b, 8 * (r >> 1) + L.g + 4 * (r & 1));
-            const pc_d2v v = f[u];
-            yc[b][r] = v.x;
-            yc[3 + b][r] = !Sh::PAR || L.two ? v.y : v.x;
-        }
-    }
-    __syncthreads();
-    // F = (v, a) (Y comps 3..8) as the product reads it: even and odd parts of the row's nodes
-    for (int q = tid; q < KR * 6 * T; q += NT) {
-        const int k = q % T, c = (q / T) % 6, i = q / (6 * T);
-        const double* y = a.Y + (size_t)(3 + c) * a.Mpad + m0 + k;
-        const double l = i < M ? y[(size_t)i * row] : 0.0;
+    const bool first = it == 1;
+    if (!first && a.count[kDone]) return;   // queued past the segment's end
+    const int n_in = first ? a.n_jobs : a.count[it & 1];
+    const int slot = blockIdx.x;
+    int job = -1, any = 0, open = 0;
+    if (slot < n_in) {
+        job = first ? slot : a.job_list[slot];
+        const int64_t m0 = (int64_t)job * T;
+        const int N = a.N, P = a.p.n_pert;
+        const PcLane L = pc_lane_geometry<PAIRS, NP>(tid, N);
+        const PcJobDev jd = a.jobs[job];
+        for (int i = tid; i < 6 * T; i += NT) sY0[i] = a.Y0[(size_t)(i / T) * a.Mpad + m0 + i % T];
         if constexpr (Sh::PAR) {
-            const double r = i < M ? y[(size_t)(N - 1 - i) * row] : 0.0;
-            f[place(i, c, k)] = pc_d2v{l + r, l - r};
+            for (int i = tid; i < 2 * KR; i += NT) sWt[i] = pc_gcd(a.g->wts)[i];
+        }
+        if (tid < T) {
+            const int dead = a.dead[m0 + tid];
+            sDead[tid] = dead;
+            sActive[tid] = first ? a.valid[m0 + tid] && !dead : a.active[m0 + tid];
+            if (first) {
+                a.active[m0 + tid] = sActive[tid];
+                if (dead && tid < jd.n && a.p.iters_out)
+                    a.p.iters_out[(size_t)(jd.ic0 + tid) * a.p.iters_stride + s] = -2;
+            }
+        }
+        if (tid == 0) sOpen = 0;
+        const PcFragD kp = pc_frag<PAIRS, NP, PcFragD>(a.g->kpair, L);
+        pc_d2v kpre[4];
+        pc_kpre_load(kp, kpre);
+        const gdp Y = pc_gd(a.Y) + (size_t)job * kJobValues + tid;
+        double yc[6][4];
+        if (!first) {
+#pragma unroll
+            for (int b = 0; b < 6; ++b) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) yc[b][r] = Y[(4 * b + r) * NT];
+            }
+        }
+        __syncthreads();
+        if (first) {
+            pc_initial_guess<PAIRS, NP>(a.p, *a.g, jd.n, jd.ic0, s, w2, L, sY0, sDead, sF, yc);
+            __syncthreads();   // staging read before F is built
+        }
+        pc_clear_rows<PAIRS, NP, false>(sF, N);
+        if constexpr (EIH) {
+            const double4* erec = reinterpret_cast<const double4*>(a.p.recs_eih) +
+                                  (size_t)(a.g->rec_offset + (int64_t)s * N) * pc_eih_rec(P);
+            pc_publish_eih<PAIRS, NP>(sF, yc, L, N, P, erec, a.p.inv_c2);
         } else {
-            sF[2 * place(i, c, k) + ((k >> 3) & 1)] = l;
+            const double4* grec = reinterpret_cast<const double4*>(a.p.recs) +
+                                  (size_t)(a.g->rec_offset + (int64_t)s * N) * (P + 1);
+            pc_publish<PAIRS, NP>(sF, yc, L, P, a.p.mu_sun, false, nullptr, nullptr, grec);
         }
-    }
-    __syncthreads();
-
-    f64x4 acc[6];
-    const PcFragD kp = pc_frag<PAIRS, NP, PcFragD>(a.g->kpair, L);
-    pc_d2v kpre[4];
-    pc_kpre_load(kp, kpre);
-    const int flag = pc_product<PAIRS, NP, false>(sF, sY0, sWt, kp, kpre, yc, acc, w2,
-                                                  pc_tol(a.p.tol_mode, a.t2, 0.0), L);
-    pc_put_flags<PAIRS, NP>(sFlag, flag, L);
-    __syncthreads();   // F read by every wave, flags complete
-
-    if (tid < T && sActive[tid]) {
-        const int fl = pc_gather_flags<PAIRS, NP>(sFlag, tid);
-        int rec = 0;
-        if (fl & 2) rec = -2;
-        else if (a.p.fixed_iters > 0) rec = (it == a.p.fixed_iters) ? it : 0;
-        else if (a.p.conv == PC_CONV_GROUP_MAX) { if (fl & 1) sOpen = 1; }   // the host decides
-        else if (!(fl & 1)) rec = it;
-        else if (it == a.p.max_iter) rec = -1;
-        if (rec != 0) {
-            sActive[tid] = 0;
-            a.active[m0 + tid] = 0;
-            if (rec == -2) a.dead[m0 + tid] = 1;
-            if (rec == -1) a.notconv[m0 + tid] = 1;
-            const PcJobDev jd = a.jobs[job];
-            if (tid < jd.n && a.p.iters_out)
-                a.p.iters_out[(size_t)(jd.ic0 + tid) * a.p.iters_stride + s] = rec;
-        }
-    }
-    // the new iterate into LDS (over F, now free), then out to HBM for the ICs that were
-    // iterating
-    if (L.ok) {
+        __syncthreads();
+        f64x4 acc[6];
+        const int flag =
+            pc_product<PAIRS, NP, false>(sF, sY0, sWt, kp, kpre, yc, acc, w2, pc_tol(a.p.tol_mode, a.t2, 0.0), L);
+        pc_put_flags<PAIRS, NP>(sFlag, flag, L);
+        // the new iterate of the ICs that were iterating (on the first sweep the frozen ones
+        // keep their guess)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
+        for (int b = 0; b < 6; ++b) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                f[pc_unit<PAIRS, NP>(L.row, L.grp, b, 8 * (r >> 1) + L.g + 4 * (r & 1))] =
-                    pc_d2v{acc[b][r], acc[3 + b][r]};
+            for (int r = 0; r < 4; ++r) {
+                const int on = sActive[pc_ic<PAIRS, NP>(L, b / 3, r & 1)];
+                if (on || first) Y[(4 * b + r) * NT] = on ? acc[b][r] : yc[b][r];
+            }
         }
+        __syncthreads();   // flags complete
+        if (tid < T && sActive[tid]) {
+            const int fl = pc_gather_flags<PAIRS, NP>(sFlag, tid);
+            int rec = 0;
+            if (fl & 2) rec = -2;
+            else if (a.p.fixed_iters > 0) rec = (it == a.p.fixed_iters) ? it : 0;
+            else if (a.p.conv == PC_CONV_GROUP_MAX) { if (fl & 1) sOpen = 1; }   // decided for the group
+            else if (!(fl & 1)) rec = it;
+            else if (it == a.p.max_iter) rec = -1;
+            if (rec != 0) {
+                sActive[tid] = 0;
+                a.active[m0 + tid] = 0;
+                if (rec == -2) a.dead[m0 + tid] = 1;
+                if (rec == -1) a.notconv[m0 + tid] = 1;
+                if (tid < jd.n && a.p.iters_out)
+                    a.p.iters_out[(size_t)(jd.ic0 + tid) * a.p.iters_stride + s] = rec;
+            }
+        }
+        any = __syncthreads_or(tid < T ? sActive[tid] : 0);
+        open = sOpen;
     }
-    __syncthreads();
-    each([&](int j, int c, int k, double* at) {
-        if (sWas[k]) a.Y[(size_t)j * row + (size_t)c * a.Mpad + m0 + k] = *at;
-    });
-    const int any = __syncthreads_or(tid < T ? sActive[tid] : 0);
+    // the last workgroup to arrive compacts the jobs that still hold an iterating IC, in list
+    // order, and takes the segment's decision (agent scope: the workgroups run on several XCDs)
     if (tid == 0) {
-        a.job_flag[job] = any;
-        if (sOpen) atomicAdd(&a.count[2], 1);
+        if (job >= 0) __hip_atomic_store(a.job_flag + job, any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (open) __hip_atomic_fetch_add(a.count + kOpen, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int prev = __hip_atomic_fetch_add(a.count + kArrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        sLast = prev == (int)gridDim.x - 1;
+        sBase = 0;
     }
-}
-
-// Stream compaction of the active job list: prefix sum of the job flags (one workgroup).
-__global__ __launch_bounds__(1024) void pc_plain_compact(PcPlainArgs a)
-{
-    __shared__ int sScan[1024];
-    __shared__ int sBase;
-    const int n_in = a.count[0];
-    if (threadIdx.x == 0) sBase = 0;
     __syncthreads();
-    for (int c0 = 0; c0 < n_in; c0 += 1024) {
-        const int i = c0 + threadIdx.x;
-        const int job = i < n_in ? a.job_list[i] : -1;
-        const int f = (job >= 0) ? (a.job_flag[job] != 0) : 0;
-        sScan[threadIdx.x] = f;
+    if (!sLast) return;
+    for (int c0 = 0; c0 < n_in; c0 += NT) {
+        const int i = c0 + tid;
+        const int jb = i < n_in ? (first ? i : a.job_list[i]) : -1;
+        const bool f = jb >= 0 && __hip_atomic_load(a.job_flag + jb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        const unsigned long long b = __ballot(f);
+        if ((tid & 63) == 0) sSum[tid >> 6] = __popcll(b);
         __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {          // inclusive Hillis-Steele scan
-            const int v = threadIdx.x >= off ? sScan[threadIdx.x - off] : 0;
-            __syncthreads();
-            sScan[threadIdx.x] += v;
-            __syncthreads();
+        int at = sBase + __popcll(b & ((1ull << (tid & 63)) - 1ull));
+        for (int w = 0; w < (tid >> 6); ++w) at += sSum[w];
+        if (f) a.job_list_out[at] = jb;
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 0; w < Sh::W; ++w) sBase += sSum[w];
         }
-        if (f) a.job_list_out[sBase + sScan[threadIdx.x] - 1] = job;
-        __syncthreads();
-        if (threadIdx.x == 1023) sBase += sScan[1023];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        a.count[1] = sBase;
-        a.count[3] = a.count[2];   // jobs with a change above tol (group-max rule)
-        a.count[2] = 0;
+    if (tid == 0) {
+        const int op = __hip_atomic_load(a.count + kOpen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        a.count[(it + 1) & 1] = sBase;
+        a.count[kOpen] = 0;
+        a.count[kArrived] = 0;
+        const bool group = a.p.conv == PC_CONV_GROUP_MAX && a.p.fixed_iters == 0;
+        const int n_it = a.p.fixed_iters > 0 ? a.p.fixed_iters : a.p.max_iter;
+        const bool settled = group && op == 0;   // no job holds a change above tol
+        const int done = settled || sBase == 0 || it >= n_it;
+        a.count[kDone] = done;
+        // the host reads these once the stream has reached its event
+        __hip_atomic_store(a.host + 0, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(a.host + 1, sBase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(a.host + 2, settled ? it : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(a.host + 3, it, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-}
-
-// Group-max rule, end of a segment's sweeps: every IC still in the group records the
-// group's status (the sweep count, or -1 when max_iter sweeps did not converge).
-__global__ void pc_plain_group_end(PcPlainArgs a, int s, int status)
-{
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= a.Mpad || !a.active[m]) return;
-    a.active[m] = 0;
-    if (status == -1) a.notconv[m] = 1;
-    const PcJobDev job = a.jobs[m / a.T];
-    const int i = (int)(m % a.T);
-    if (i < job.n && a.p.iters_out) a.p.iters_out[(size_t)(job.ic0 + i) * a.p.iters_stride + s] = status;
 }
 
 // Segment end: the last node starts the next segment; optional node / boundary outputs.
-__global__ void pc_plain_chain(PcPlainArgs a, int s, int last)
+// Group-max rule: every IC still in the group records the group's status (the sweep count, or
+// -1 when max_iter sweeps did not converge).
+__global__ void pc_plain_chain(PcPlainArgs a, int s, int last, int group, int status)
 {
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (m == 0) a.count[kDone] = 0;
     if (m >= a.Mpad) return;
     const PcJobDev job = a.jobs[m / a.T];
     const int i = (int)(m % a.T);
     const bool valid = i < job.n;
     const int64_t ic = job.ic0 + i;
-    const size_t row = (size_t)9 * a.Mpad;
+    const double* Y = a.Y + (size_t)(m / a.T) * kJobValues;
+    if (group && a.active[m]) {
+        a.active[m] = 0;
+        if (status == -1) a.notconv[m] = 1;
+        if (valid && a.p.iters_out) a.p.iters_out[(size_t)ic * a.p.iters_stride + s] = status;
+    }
     if (valid && a.p.nodes_out) {
         for (int j = 0; j < a.N; ++j) {
             double* o = a.p.nodes_out + (((size_t)ic * a.p.iters_stride + s) * a.p.nodes_stride + j) * 6;
-            for (int c = 0; c < 6; ++c) o[c] = a.Y[(size_t)j * row + (size_t)c * a.Mpad + m];
+            for (int c = 0; c < 6; ++c) o[c] = Y[plain_at(a.NP, a.N, j, c, i)];
         }
     }
     const bool dead = a.dead[m];
     for (int c = 0; c < 6; ++c) {
-        const double v = dead ? (double)NAN : a.Y[(size_t)(a.N - 1) * row + (size_t)c * a.Mpad + m];
+        const double v = dead ? (double)NAN : Y[plain_at(a.NP, a.N, a.N - 1, c, i)];
         a.Y0[c * a.Mpad + m] = v;
         if (valid && a.p.bounds_out)
             a.p.bounds_out[((size_t)ic * (a.p.iters_stride + 1) + s + 1) * 6 + c] = v;
+        if (valid && last) a.p.states_out[(size_t)ic * 6 + c] = v;
     }
     if (valid && last) {
-        for (int c = 0; c < 6; ++c) a.p.states_out[(size_t)ic * 6 + c] = a.Y0[c * a.Mpad + m];
         if (a.notconv[m]) atomicAdd(&a.p.counters[0], 1);
         if (dead) atomicAdd(&a.p.counters[1], 1);
     }
 }
 
-__global__ void pc_plain_bounds0(PcPlainArgs a)
+template <int NP>
+void launch_sweep(const PcPlainArgs& a, int grid, int s, int it, double w2, hipStream_t st)
 {
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= a.Mpad || !a.p.bounds_out) return;
-    const PcJobDev job = a.jobs[m / a.T];
-    const int i = (int)(m % a.T);
-    if (i >= job.n) return;
-    for (int c = 0; c < 6; ++c)
-        a.p.bounds_out[((size_t)(job.ic0 + i) * (a.p.iters_stride + 1)) * 6 + c] = a.Y0[c * a.Mpad + m];
+    if (a.p.inv_c2 != 0.0)
+        hipLaunchKernelGGL((pc_plain_sweep<NP, true>), dim3(grid), dim3(kPlainPairs / 4), 0, st, a, s, it, w2);
+    else
+        hipLaunchKernelGGL((pc_plain_sweep<NP, false>), dim3(grid), dim3(kPlainPairs / 4), 0, st, a, s, it, w2);
 }
 
-template <int PAIRS, int NP>
-void launch_step(const PcPlainArgs& a, int grid, int s, int it, double w2, hipStream_t st)
-{
-    hipLaunchKernelGGL((pc_plain_step<PAIRS, NP>), dim3(grid), dim3(PAIRS / 4), 0, st, a, s, it, w2);
-}
-
-int launch_step_np(const PcPlainArgs& a, int grid, int s, int it, double w2, hipStream_t st)
+hipError_t launch_sweep_np(const PcPlainArgs& a, int grid, int s, int it, double w2, hipStream_t st)
 {
     switch (a.NP) {
-    case 16: launch_step<2048, 16>(a, grid, s, it, w2, st); break;
-    case 32: launch_step<2048, 32>(a, grid, s, it, w2, st); break;
-    case 64: launch_step<2048, 64>(a, grid, s, it, w2, st); break;
-    case 128: launch_step<2048, 128>(a, grid, s, it, w2, st); break;
-    case 256: launch_step<2048, 256>(a, grid, s, it, w2, st); break;
+    case 16: launch_sweep<16>(a, grid, s, it, w2, st); break;
+    case 32: launch_sweep<32>(a, grid, s, it, w2, st); break;
+    case 64: launch_sweep<64>(a, grid, s, it, w2, st); break;
+    case 128: launch_sweep<128>(a, grid, s, it, w2, st); break;
+    case 256: launch_sweep<256>(a, grid, s, it, w2, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -350,71 +296,60 @@ int launch_step_np(const PcPlainArgs& a, int grid, int s, int it, double w2, hip
 
 }  // namespace
 
-size_t pc_plain_bytes(int NP, int n_jobs, int T)
+size_t pc_plain_bytes(int, int n_jobs, int T)
 {
     const size_t Mpad = (size_t)n_jobs * T;
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    return al(9 * (size_t)NP * Mpad * 8) + al(6 * Mpad * 8) + 4 * al(Mpad * 4) + 3 * al((size_t)n_jobs * 4) + 256;
+    return al((size_t)n_jobs * kJobValues * 8) + al(6 * Mpad * 8) + 4 * al(Mpad * 4) + 3 * al((size_t)n_jobs * 4) + 256;
 }
 
 namespace {
 
-constexpr int kPlainBs = 256;
-
-// One Picard iteration of the active jobs, then the read-back of the active-job count
-// (and, for the group-max rule, of the jobs with a change above tol) that drives the
-// host loop (Sec. 5.4.2).
-hipError_t plain_enqueue_iteration(PcPlainRun& r)
+// Queue the segment's next sweeps, up to the next read-back: as many as the previous segment of
+// the group took but one, then two at a time (a sweep queued past the end costs about 3 us on
+// the stream, a read-back and its host round trip about 10 us).
+hipError_t plain_batch(PcPlainRun& r)
 {
     PcPlainArgs& a = r.a;
-    hipStream_t st = (hipStream_t)r.stream;
-    a.job_list = r.lists[r.cur];
-    a.job_list_out = r.lists[1 - r.cur];
-    const int bpj = a.NP * a.T / kPlainForceBlock;
-    hipLaunchKernelGGL(pc_plain_force, dim3((unsigned)(r.count * bpj)), dim3(kPlainForceBlock), 0, st, a, r.s);
-    hipError_t e = (hipError_t)launch_step_np(a, r.count, r.s, r.it, r.w2, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(pc_plain_compact, dim3(1), dim3(1024), 0, st, a);
-    e = hipMemcpyAsync(r.host, a.count + 1, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return e;
-    return hipMemcpyAsync(a.count, a.count + 1, sizeof(int32_t), hipMemcpyDeviceToDevice, st);
+    int k = r.it == 0 && r.last > 2 ? r.last - 1 : r.it == 0 ? 4 : 2;
+    k = k < r.n_it - r.it ? k : r.n_it - r.it;
+    for (; k > 0; --k) {
+        ++r.it;
+        a.job_list = r.lists[r.it & 1];
+        a.job_list_out = r.lists[(r.it + 1) & 1];
+        const hipError_t e = launch_sweep_np(a, r.count, r.s, r.it, r.w2, (hipStream_t)r.stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
-// Segment r.s: initial guess at every node, full job list, first iteration.
+// Segment r.s: every job, from the first sweep.
 hipError_t plain_begin_segment(PcPlainRun& r)
 {
-    PcPlainArgs& a = r.a;
-    hipStream_t st = (hipStream_t)r.stream;
-    const double h = a.g_host.h;
-    const double Ts = a.g_host.t0 + h * r.s, Te = a.g_host.t0 + h * (r.s + 1);
+    const double h = r.a.g_host.h;
+    const double Ts = r.a.g_host.t0 + h * r.s, Te = r.a.g_host.t0 + h * (r.s + 1);
     r.w2 = 0.5 * (Te - Ts);
-    r.cur = 0;
-    a.job_list = r.lists[0];
-    const int64_t total = (int64_t)a.NP * a.Mpad;
-    hipLaunchKernelGGL(pc_plain_init, dim3((unsigned)((total + kPlainBs - 1) / kPlainBs)), dim3(kPlainBs), 0, st,
-                       a, r.s, r.w2);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    r.count = a.n_jobs;
-    r.status = -1;
-    r.it = 1;
-    return plain_enqueue_iteration(r);
+    r.last = r.s > 0 ? r.host[3] : 0;
+    r.count = r.a.n_jobs;
+    r.it = 0;
+    return plain_batch(r);
 }
 
 }  // namespace
 
-int pc_plain_begin(PcPlainRun& r, const PcPlainArgs& args, void* workspace, int32_t* host_count, void* stream)
+int pc_plain_begin(PcPlainRun& r, const PcPlainArgs& args, void* workspace, int32_t* host, void* stream)
 {
     r = PcPlainRun{};
     r.a = args;
-    r.host = host_count;
+    r.host = host;
     r.stream = stream;
     PcPlainArgs& a = r.a;
+    a.host = host;
     hipStream_t st = (hipStream_t)stream;
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     char* w = static_cast<char*>(workspace);
     a.Mpad = (int64_t)a.n_jobs * a.T;
-    a.Y = reinterpret_cast<double*>(w);                w += al(9 * (size_t)a.NP * a.Mpad * 8);
+    a.Y = reinterpret_cast<double*>(w);                w += al((size_t)a.n_jobs * kJobValues * 8);
     a.Y0 = reinterpret_cast<double*>(w);               w += al(6 * (size_t)a.Mpad * 8);
     a.active = reinterpret_cast<int32_t*>(w);          w += al(a.Mpad * 4);
     a.dead = reinterpret_cast<int32_t*>(w);            w += al(a.Mpad * 4);
@@ -431,9 +366,6 @@ int pc_plain_begin(PcPlainRun& r, const PcPlainArgs& args, void* workspace, int3
     hipLaunchKernelGGL(pc_plain_load, dim3(gm), dim3(kPlainBs), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(pc_plain_bounds0, dim3(gm), dim3(kPlainBs), 0, st, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
     return plain_begin_segment(r);
 }
 
@@ -441,26 +373,13 @@ int pc_plain_advance(PcPlainRun& r)
 {
     PcPlainArgs& a = r.a;
     hipStream_t st = (hipStream_t)r.stream;
-    r.count = r.host[0];
-    r.cur = 1 - r.cur;
-    bool end = false;
-    if (r.group && r.host[2] == 0) {   // group-max rule: no job holds a change above tol
-        r.status = r.it;
-        end = true;
-    } else if (r.it >= r.n_it || r.count == 0) {
-        end = true;
-    }
-    if (!end) {
-        ++r.it;
-        return plain_enqueue_iteration(r);
+    if (!r.host[0]) {
+        r.count = r.host[1];
+        return plain_batch(r);
     }
     const unsigned gm = (unsigned)((a.Mpad + kPlainBs - 1) / kPlainBs);
-    if (r.group) {
-        hipLaunchKernelGGL(pc_plain_group_end, dim3(gm), dim3(kPlainBs), 0, st, a, r.s, r.status);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(pc_plain_chain, dim3(gm), dim3(kPlainBs), 0, st, a, r.s, r.s == a.S - 1 ? 1 : 0);
+    hipLaunchKernelGGL(pc_plain_chain, dim3(gm), dim3(kPlainBs), 0, st, a, r.s, r.s == a.S - 1 ? 1 : 0,
+                       r.group ? 1 : 0, r.host[2]);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (++r.s == a.S) {
@@ -470,10 +389,10 @@ int pc_plain_advance(PcPlainRun& r)
     return plain_begin_segment(r);
 }
 
-int pc_run_plain(PcPlainArgs a, void* workspace, int32_t* host_count, void* stream)
+int pc_run_plain(PcPlainArgs a, void* workspace, int32_t* host, void* stream)
 {
     PcPlainRun r;
-    hipError_t e = (hipError_t)pc_plain_begin(r, a, workspace, host_count, stream);
+    hipError_t e = (hipError_t)pc_plain_begin(r, a, workspace, host, stream);
     while (e == hipSuccess && !r.done) {
         e = hipStreamSynchronize((hipStream_t)stream);
         if (e == hipSuccess) e = (hipError_t)pc_plain_advance(r);
