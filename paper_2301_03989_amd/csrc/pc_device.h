@@ -735,6 +735,50 @@ static __device__ __forceinline__ void pc_hess_apply(const double (&x)[4], const
     }
 }
 
+// The Jacobian H = da/dr itself at the lane's points, (xx, yy, zz, xy, xz, yz): every attracting
+// body adds 3 A/|d|^2 d d^T - A, A = mu/|d|^3.  The adjoint's points stay fixed over a segment's
+// sweeps: forming H once and taking H w as 9 multiply-adds replaces a pass over the bodies (27
+// FP64 instructions each) in every sweep, and H takes the registers of the iterate, which the
+// sweeps no longer need: forward and gradient of 16384 ICs (128 nodes, 5 segments) 13.4 -> 11.8 ms.
+template <bool LDSREC>
+static __device__ __forceinline__ void pc_hess_matrix(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+                                                      const int (&jn)[2], int P, double mu_sun, const double* srec,
+                                                      const double* smu, const double4* grec, double (&H)[6][4])
+{
+    auto add = [&](int p, double dx, double dy, double dz, double mu, double mu1, double mu2)
+                   __attribute__((always_inline)) {
+        const double r2 = pc_norm2(dx, dy, dz);
+        const double v = __builtin_amdgcn_rsq(r2);
+        const double t = v * v;
+        const double e = fma(-r2, t, 1.0);
+        const double A = (v * t) * fma(e, fma(mu2, e, mu1), mu);
+        const double B = 3.0 * (A * fma(t, fma(e, e, e), t));
+        const double bx = B * dx, by = B * dy;
+        H[0][p] += fma(bx, dx, -A);
+        H[1][p] += fma(by, dy, -A);
+        H[2][p] += fma(B * dz, dz, -A);
+        H[3][p] = fma(bx, dy, H[3][p]);
+        H[4][p] = fma(bx, dz, H[4][p]);
+        H[5][p] = fma(by, dz, H[5][p]);
+    };
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) H[k][p] = 0.0;
+        add(p, x[p], y[p], z[p], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun);
+    }
+    for (int b = 0; b < P; ++b) {
+        double4 q[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) q[h] = pc_record<LDSREC>(srec, smu, grec, P, jn[h], b);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const double4& k = q[p >> 1];
+            add(p, x[p] - k.x, y[p] - k.y, z[p] - k.z, k.w, 1.5 * k.w, 1.875 * k.w);
+        }
+    }
+}
+
 // Linear change of the point-mass acceleration over a position change at the lane's points:
 // g = (da/dr)(r) dr, the Hessian product with w = dr.
 static __device__ __forceinline__ void pc_grad_dot(const double (&x)[4], const double (&y)[4], const double (&z)[4],
@@ -898,81 +942,87 @@ static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const 
     }
 }
 
-// Vector-Jacobian product of that acceleration at one point: gr = (da/dr)^T u and
-// gv = (da/dv)^T u (the adjoint's J^T w with u = w_v).  Per body, with m3 = mu/rho^3,
-// m5 = 3 mu/rho^5, s the bracket without 4 Phi - v^2, W = 4 v_b, G = 7/2 a_b and
-// z = 4 u.(v - v_b), the gradients of u.a are collected along the directions they lie on:
-//   H  = sum (m5 (u.d) d - m3 u),   N = sum m3 d,   U = u.N = sum m3 u.d,
-//   gv = e [ sum (m3 z d + m3 (u.d) W) + 4 K u - 2 U v ],
-//   gr = H + e [ sum (kd d + kw W + kg G) + S u + Z v - (4 Phi - v^2) H - 4 U N ],
-//   kd = -s m5 (u.d) - (3/16) m3 (u.d) (d.W)^2/rho^4 - 3 m3 z q/rho^2 - m3 u.G,  q = d.v - (3/16) d.W
-//   kw = (3/16) (m3 (u.d) (d.W)/rho^2 - m3 z),   kg = m3 (u.d) / 7,
-//   K = sum m3 q,   S = sum m3 s,   Z = sum m3 z.
-// 84 FP64 instructions per body (term by term about 135).  At e = 0 this is the point-mass
-// Hessian product (symmetric in r); the indirect term does not depend on the state.
-// Records as pc_force_eih.
-static __device__ __forceinline__ void pc_eih_vjp(double x, double y, double z, double vx, double vy, double vz,
-                                                  double ux, double uy, double uz, const PcEihRecs& E, int j, int P,
-                                                  double inv_c2, double (&gr)[3], double (&gv)[3])
+// Jacobian of that acceleration at one point, as the adjoint applies it: gr_i = sum_j R[i][j] u_j
+// for (da/dr)^T u and gv_i = sum_j V[i][j] u_j for (da/dv)^T u.  Per body, with m3 = mu/rho^3,
+// B = 3 mu/rho^5, s the bracket without 4 Phi - v^2, W = 4 v_b, G = 7/2 a_b, c = d.W/rho^2,
+// q = d.v - (3/16) d.W and e = 1/c^2:
+//   H = sum B d d^T - M,   N = sum m3 d,   M = sum m3,   K = sum m3 q,   S = sum m3 s,
+//   R = H + e [ sum (d a^T + W b^T + G g^T) + S + v (4 M v - sum m3 W)^T - (4 Phi - v^2) H - 4 N N^T ],
+//   a = -(s B + (3/16) m3 c^2) d - B q (4 v - W) - m3 G,   b = (3/16) m3 (c d - (4 v - W)),   g = m3 d / 7,
+//   V = e [ 4 N v^T - 2 v N^T + 4 K + (cross product with Q from the right) ],   Q = sum m3 W x d.
+// The adjoint's points stay fixed over a segment's sweeps, so R and V are formed once (about 105
+// FP64 instructions per body) and a sweep takes 18 multiply-adds per point instead of a pass
+// over the bodies (84 per body): gradients through 1237 x 200 nodes 5.77 -> 4.08 ms.  About a
+// third of the 72 values per lane live in scratch; a sweep reads them once.  At e = 0, R is the point-mass Jacobian; the indirect term does
+// not depend on the state.  Records as pc_force_eih.
+static __device__ __forceinline__ void pc_eih_jacobian(double x, double y, double z, double vx, double vy, double vz,
+                                                       const PcEihRecs& E, int j, int P, double inv_c2,
+                                                       double (&R)[9], double (&V)[9])
 {
     const uint32_t vo = (uint32_t)j * 32u;
     auto rec = [&](int k) -> double4 { return pc_eih_load(E, k, vo); };
-    const double uv4 = 4.0 * fma(uz, vz, fma(uy, vy, ux * vx));
-    double phi = 0.0, K = 0.0, M = 0.0, S = 0.0, Z = 0.0, U = 0.0;
-    double nx = 0.0, ny = 0.0, nz = 0.0, hx = 0.0, hy = 0.0, hz = 0.0, ax = 0.0, ay = 0.0, az = 0.0;
-    double bx = 0.0, by = 0.0, bz = 0.0;
+    const double v[3] = {vx, vy, vz};
+    double phi = 0.0, K = 0.0, M = 0.0, S = 0.0, n[3] = {}, Q[3] = {}, mw[3] = {}, H[6] = {}, A[9] = {};
     for (int b = 0; b <= P; ++b) {
-        const double4 q = rec(3 * b), w = rec(3 * b + 1), g = rec(3 * b + 2);
-        const double dx = x - q.x, dy = y - q.y, dz = z - q.z;
-        const double i1 = pc_rsqrt_full(pc_norm2(dx, dy, dz));
-        const double i2 = i1 * i1, m1 = w.w * i1, m3 = m1 * i2;
-        phi += m1;
-        M += m3;
-        nx = fma(m3, dx, nx);
-        ny = fma(m3, dy, ny);
-        nz = fma(m3, dz, nz);
-        const double ud = fma(uz, dz, fma(uy, dy, ux * dx));
-        const double dw = fma(dz, w.z, fma(dy, w.y, dx * w.x));
-        const double dg = fma(dz, g.z, fma(dy, g.y, dx * g.x));
-        const double dv = fma(dz, vz, fma(dy, vy, dx * vx));
-        const double uw = fma(uz, w.z, fma(uy, w.y, ux * w.x));
-        const double ug = fma(uz, g.z, fma(uy, g.y, ux * g.x));
+        const double4 q4 = rec(3 * b), w4 = rec(3 * b + 1), g4 = rec(3 * b + 2);
+        const double d[3] = {x - q4.x, y - q4.y, z - q4.z}, w[3] = {w4.x, w4.y, w4.z}, g[3] = {g4.x, g4.y, g4.z};
+        const double i1 = pc_rsqrt_full(pc_norm2(d[0], d[1], d[2]));
+        const double i2 = i1 * i1, m1 = w4.w * i1, m3 = m1 * i2;
+        const double dw = fma(d[2], w[2], fma(d[1], w[1], d[0] * w[0]));
+        const double dg = fma(d[2], g[2], fma(d[1], g[1], d[0] * g[0]));
+        const double dv = fma(d[2], vz, fma(d[1], vy, d[0] * vx));
         const double c = dw * i2;
-        double s = fma(vz, w.z, fma(vy, w.y, fma(vx, w.x, q.w)));
+        double s = fma(vz, w[2], fma(vy, w[1], fma(vx, w[0], q4.w)));
         s = fma(0.09375 * c, dw, s);
         s = fma(1.0 / 7.0, dg, s);
-        const double qd = fma(-0.1875, dw, dv);
-        const double mud = m3 * ud, mz = m3 * (uv4 - uw);
-        U += mud;
-        Z += mz;
+        const double qd = fma(-0.1875, dw, dv), B = 3.0 * (m3 * i2);
+        phi += m1;
+        M += m3;
         K = fma(m3, qd, K);
         S = fma(s, m3, S);
-        const double p = 3.0 * (mud * i2);
-        const double t = 0.1875 * (c * mud);
-        double kd = fma(-s, p, -(m3 * ug));
-        kd = fma(-t, c, kd);
-        kd = fma(-3.0 * (i2 * mz), qd, kd);
-        const double kw = fma(-0.1875, mz, t), kg = (1.0 / 7.0) * mud;
-        hx = fma(p, dx, hx);
-        hy = fma(p, dy, hy);
-        hz = fma(p, dz, hz);
-        ax = fma(kg, g.x, fma(kw, w.x, fma(kd, dx, ax)));
-        ay = fma(kg, g.y, fma(kw, w.y, fma(kd, dy, ay)));
-        az = fma(kg, g.z, fma(kw, w.z, fma(kd, dz, az)));
-        bx = fma(mud, w.x, fma(mz, dx, bx));
-        by = fma(mud, w.y, fma(mz, dy, by));
-        bz = fma(mud, w.z, fma(mz, dz, bz));
+        const double a1 = -fma(s, B, 0.1875 * (m3 * (c * c))), a2 = -(B * qd), b1 = 0.1875 * m3, g1 = (1.0 / 7.0) * m3;
+        double al[3], be[3], ga[3], md[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double t = fma(4.0, v[k], -w[k]);
+            md[k] = m3 * d[k];
+            n[k] += md[k];
+            mw[k] = fma(m3, w[k], mw[k]);
+            al[k] = fma(a1, d[k], fma(a2, t, -(m3 * g[k])));
+            be[k] = b1 * fma(c, d[k], -t);
+            ga[k] = g1 * d[k];
+        }
+        Q[0] += fma(w[1], md[2], -(w[2] * md[1]));
+        Q[1] += fma(w[2], md[0], -(w[0] * md[2]));
+        Q[2] += fma(w[0], md[1], -(w[1] * md[0]));
+        const double bx = B * d[0], by = B * d[1];
+        H[0] = fma(bx, d[0], H[0]);
+        H[1] = fma(by, d[1], H[1]);
+        H[2] = fma(B * d[2], d[2], H[2]);
+        H[3] = fma(bx, d[1], H[3]);
+        H[4] = fma(bx, d[2], H[4]);
+        H[5] = fma(by, d[2], H[5]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                A[3 * i + k] = fma(g[i], ga[k], fma(w[i], be[k], fma(d[i], al[k], A[3 * i + k])));
+        }
     }
-    hx = fma(-M, ux, hx);
-    hy = fma(-M, uy, hy);
-    hz = fma(-M, uz, hz);
-    const double f = fma(4.0, phi, -pc_norm2(vx, vy, vz)), u4 = 4.0 * U, u2 = 2.0 * U, k4 = 4.0 * K;
-    gr[0] = fma(inv_c2, fma(-u4, nx, fma(-f, hx, fma(Z, vx, fma(S, ux, ax)))), hx);
-    gr[1] = fma(inv_c2, fma(-u4, ny, fma(-f, hy, fma(Z, vy, fma(S, uy, ay)))), hy);
-    gr[2] = fma(inv_c2, fma(-u4, nz, fma(-f, hz, fma(Z, vz, fma(S, uz, az)))), hz);
-    gv[0] = inv_c2 * fma(-u2, vx, fma(k4, ux, bx));
-    gv[1] = inv_c2 * fma(-u2, vy, fma(k4, uy, by));
-    gv[2] = inv_c2 * fma(-u2, vz, fma(k4, uz, bz));
+    const double f = fma(4.0, phi, -pc_norm2(vx, vy, vz));
+    const double h[9] = {H[0] - M, H[3], H[4], H[3], H[1] - M, H[5], H[4], H[5], H[2] - M};
+    const double X[9] = {0.0, Q[2], -Q[1], -Q[2], 0.0, Q[0], Q[1], -Q[0], 0.0};   // X u = u x Q
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int e = 3 * i + k;
+            const double r = fma(v[i], fma(4.0 * M, v[k], -mw[k]), fma(-f, h[e], fma(-4.0 * n[i], n[k], A[e])));
+            R[e] = fma(inv_c2, i == k ? r + S : r, h[e]);
+            const double t = fma(4.0 * n[i], v[k], fma(-2.0 * v[i], n[k], X[e]));
+            V[e] = inv_c2 * (i == k ? fma(4.0, K, t) : t);
+        }
+    }
 }
 
 // Software-pipelined k loop of a 16x16x4 product over nq steps (a multiple of 4, at most

@@ -895,7 +895,7 @@ int pc_launch_fused(const PcParams& p, const PcParams* p_dev, int pairs, int gri
 // the previous one.  A lane holds its points' states and mu (PcShape), so that J^T w needs no
 // other lane.
 // EIH: the relativistic dynamics, whose force also depends on the velocity: J^T w is
-// ((da/dr)^T w_v, w_r + (da/dv)^T w_v) (pc_eih_vjp) instead of (H w_v, w_r).
+// ((da/dr)^T w_v, w_r + (da/dv)^T w_v) instead of (H w_v, w_r).
 template <int PAIRS, int NP, bool EIH = false>
 __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, const PcJobDev& job,
                                                          const PcGroupDev& g)
@@ -983,6 +983,25 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
         __syncthreads();
         const double Ts = g.t0 + g.h * s, Te = g.t0 + g.h * (s + 1);
         const double w2 = 0.5 * (Te - Ts);
+        // the force Jacobian at the lane's points, fixed over the segment's sweeps (point masses:
+        // symmetric; relativistic: with respect to position and velocity)
+        double H[6][4], J[4][9], V[4][9];
+        if constexpr (EIH) {
+            const PcEihRecs R = pc_eih_recs(erec, N);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int h = 3 * (q >> 1), r = q & 1;
+                pc_eih_jacobian(yc[h][r], yc[h + 1][r], yc[h + 2][r], yc[h][2 + r], yc[h + 1][2 + r], yc[h + 2][2 + r],
+                                R, L.jn[q >> 1], P, p.inv_c2, J[q], V[q]);
+            }
+        } else {
+            double x[4], y[4], z[4];
+            pc_points(yc, 0, x);
+            pc_points(yc, 1, y);
+            pc_points(yc, 2, z);
+            if (rec_lds) pc_hess_matrix<true>(x, y, z, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, H);
+            else pc_hess_matrix<false>(x, y, z, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, H);
+        }
 
         // seed of this segment at the lane's point q = 2h + r: the next segment's gradient at the
         // end node, plus the node seeds when given (recomputed where needed, not held); none at
@@ -1030,40 +1049,27 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
             // mu_new = gbar + J^T w: position rows w2 (da/dr)^T w_v, velocity rows w2 w_r (and the
             // relativistic (da/dv)^T w_v)
             if constexpr (EIH) {
-                const PcEihRecs R = pc_eih_recs(erec, N);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int h = 3 * (q >> 1), r = q & 1;
-                    double gr[3], gv[3];
-                    pc_eih_vjp(yc[h][r], yc[h + 1][r], yc[h + 2][r], yc[h][2 + r], yc[h + 1][2 + r], yc[h + 2][2 + r],
-                               acc[h][2 + r], acc[h + 1][2 + r], acc[h + 2][2 + r], R, L.jn[q >> 1], P, p.inv_c2, gr, gv);
+                    const double wx = acc[h][2 + r], wy = acc[h + 1][2 + r], wz = acc[h + 2][2 + r];
 #pragma unroll
                     for (int b = 0; b < 3; ++b) {
-                        acc[h + b][2 + r] = acc[h + b][r] + gv[b];
-                        acc[h + b][r] = gr[b];
+                        acc[h + b][2 + r] = fma(V[q][3 * b + 2], wz, fma(V[q][3 * b + 1], wy,
+                                                fma(V[q][3 * b], wx, acc[h + b][r])));
+                        acc[h + b][r] = fma(J[q][3 * b + 2], wz, fma(J[q][3 * b + 1], wy, J[q][3 * b] * wx));
                     }
                 }
             } else {
-                double x[4], y[4], z[4], wx[4], wy[4], wz[4], hx[4], hy[4], hz[4];
-                pc_points(yc, 0, x);
-                pc_points(yc, 1, y);
-                pc_points(yc, 2, z);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    wx[q] = acc[3 * (q >> 1)][2 + (q & 1)];
-                    wy[q] = acc[3 * (q >> 1) + 1][2 + (q & 1)];
-                    wz[q] = acc[3 * (q >> 1) + 2][2 + (q & 1)];
-                }
-                if (rec_lds) pc_hess_apply<true>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
-                else pc_hess_apply<false>(x, y, z, wx, wy, wz, L.jn, P, p.mu_sun, sm.Rec, sm.Mu, grec, hx, hy, hz);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int h = 3 * (q >> 1), r = q & 1;
+                    const double wx = acc[h][2 + r], wy = acc[h + 1][2 + r], wz = acc[h + 2][2 + r];
 #pragma unroll
                     for (int b = 0; b < 3; ++b) acc[h + b][2 + r] = acc[h + b][r];
-                    acc[h][r] = hx[q];
-                    acc[h + 1][r] = hy[q];
-                    acc[h + 2][r] = hz[q];
+                    acc[h][r] = fma(H[4][q], wz, fma(H[3][q], wy, H[0][q] * wx));
+                    acc[h + 1][r] = fma(H[5][q], wz, fma(H[1][q], wy, H[3][q] * wx));
+                    acc[h + 2][r] = fma(H[2][q], wz, fma(H[5][q], wy, H[4][q] * wx));
                 }
             }
 #pragma unroll
