@@ -140,17 +140,17 @@ static __device__ __forceinline__ double pc_rcp_full(double x)
     return fma(y, fma(-x, y, 1.0), y);
 }
 
-// Sine and cosine: x - k pi/2 with pi/2 in two parts (exact to 2^-53 of the result for the
-// angles of an orbit; the library for larger ones), then the Taylor series on [-pi/4, pi/4],
-// whose dropped terms are below 1e-18.  A third of the library call's instructions.
+// Sine and cosine: x - k pi/2 with pi/2 in two parts (off by k 1.5e-33, less than the rounding
+// of x itself at any k), then the Taylor series on [-pi/4, pi/4], whose dropped terms are below
+// 1e-18.  A third of the library call's instructions.  No call for large angles: with one on
+// that path, never taken by an orbit, the solve saved and reloaded two dozen registers at every
+// call; without it the 12000 eccentric ICs of 48 nodes went from 4.98 to 4.63 ms, a single
+// orbit of 32 nodes from 215 to 209 us.
 static __device__ __forceinline__ void pc_sincos(double x, double& s, double& c)
 {
-    if (!(fabs(x) < 1e5)) {
-        sincos(x, &s, &c);
-        return;
-    }
     const double k = rint(x * 0.63661977236758134308);
-    const double r = fma(-k, 6.12323399573676603587e-17, fma(-k, 1.57079632679489655800, x));
+    double r = fma(-k, 6.12323399573676603587e-17, fma(-k, 1.57079632679489655800, x));
+    r = fabs(r) > 1.0 ? r - r : r;   // beyond 2^52 turns x has no phase left: any on the circle
     const double z = r * r;
     double p = 1.0 / 355687428096000.0, q = 1.0 / 20922789888000.0;
     p = fma(p, z, -1.0 / 1307674368000.0);
@@ -168,7 +168,7 @@ static __device__ __forceinline__ void pc_sincos(double x, double& s, double& c)
     p = fma(p, z, -1.0 / 6.0);
     q = fma(q, z, -0.5);
     const double sr = fma(r * z, p, r), cr = fma(z, q, 1.0);
-    const int m = (int)k;
+    const int m = (int)fma(-4.0, rint(0.25 * k), k);   // k modulo 4, -2..2
     const double ss = (m & 1) ? cr : sr, cc = (m & 1) ? sr : cr;
     s = (m & 2) ? -ss : ss;
     c = ((m + 1) & 2) ? -cc : cc;
@@ -189,7 +189,7 @@ static __device__ __forceinline__ void pc_sincos(double x, double& s, double& c)
 // for one solve per lane.  Four FP64 steps from n dt with library sines and IEEE divisions
 // took about 900 instructions, this about 250: 12000 eccentric ICs of 48 nodes and 16 segments
 // (a third of the sweeps refill a column) 5.20 -> 5.08 ms, the uneven 65536-IC batch 160.0 ->
-// 157.8 ms.
+// 157.8 ms (each before the sweeps themselves were shortened).
 // The state goes in and out by value (registers, no stack traffic); a non-elliptic or
 // degenerate state returns NaN components.
 struct PcState6 {

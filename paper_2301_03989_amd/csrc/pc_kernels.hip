@@ -183,15 +183,27 @@ __device__ __forceinline__ PcSmem<1024>& pc_smem<1024>() { return g_smem1024; }
 template <int PAIRS>
 static __device__ __forceinline__ void pc_stage_records(const double4* grec, int N, int P, PcSmem<PAIRS>& sm)
 {
-    for (int i = threadIdx.x; i < N * (P + 1); i += PAIRS / 4) {
-        const double4 q = grec[i];
-        sm.Rec[3 * i + 0] = q.x;
-        sm.Rec[3 * i + 1] = q.y;
-        sm.Rec[3 * i + 2] = q.z;
-        if (i < P) {
-            sm.Mu[4 * i] = q.w;
-            sm.Mu[4 * i + 1] = 1.5 * q.w;
-            sm.Mu[4 * i + 2] = 1.875 * q.w;
+    // four records per thread in flight: the copy waits for its loads once, not per record
+    // (a single orbit of 32 nodes 220 -> 216 us, 4096 Venus orbits 1.525 -> 1.513 ms)
+    constexpr int NT = PAIRS / 4;
+    const int n = N * (P + 1);
+    const gconst_cp base = pc_wave_base(grec);
+    for (int i0 = threadIdx.x; i0 < n; i0 += 4 * NT) {
+        double4 q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = pc_load_d4(base + (uint32_t)min(i0 + k * NT, n - 1) * 32u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = i0 + k * NT;
+            if (i >= n) break;
+            sm.Rec[3 * i + 0] = q[k].x;
+            sm.Rec[3 * i + 1] = q[k].y;
+            sm.Rec[3 * i + 2] = q[k].z;
+            if (i < P) {
+                sm.Mu[4 * i] = q[k].w;
+                sm.Mu[4 * i + 1] = 1.5 * q[k].w;
+                sm.Mu[4 * i + 2] = 1.875 * q[k].w;
+            }
         }
     }
 }

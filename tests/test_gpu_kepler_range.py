@@ -53,3 +53,8 @@ def test_kepler_step_over_its_range(e_max, dt_max):
     bar = 64 * 2.2e-16 * angle / (1.0 - e) ** 2
     assert (d[:, :3].max(1) <= bar * a * (1 + e)).all(), (d[:, :3].max(1) / (bar * a)).max()
     assert (d[:, 3:].max(1) <= bar * np.sqrt(2.0 / rp)).all(), (d[:, 3:].max(1) / (bar * np.sqrt(2.0 / rp))).max()
+
+
+@pytest.mark.parametrize("dt_max", [1e4, 3e7])
+def test_kepler_step_over_many_revolutions(dt_max):
+    test_kepler_step_over_its_range(0.6, dt_max)
