@@ -471,12 +471,14 @@ int choose_pairs(const pc_ctx* ctx, const pc_group* groups, int n_groups, const 
     if (o.tile_pairs == 1024 || o.tile_pairs == 2048) return o.tile_pairs;
     int np_max = 16;
     for (int i = 0; i < n_groups; ++i) np_max = std::max(np_max, padded_nodes(groups[i].nodes));
-    // untuned default: the 256-thread shape up to 64 padded nodes, where two of its
-    // workgroups share a CU and overlap their jobs (about 9 % faster at 64 nodes than one
-    // 512-thread workgroup per CU); the 512-thread shape above, where its transposed
-    // 16-IC blocks beat the 8-IC node-row blocks of the small shape
+    // untuned default: the 256-thread shape up to 128 padded nodes, where two of its
+    // workgroups share a CU and one's sweeps fill the other's waits at barriers, segment
+    // starts and refills; both shapes hold mirrored pairs by 8 ICs.  At 128 nodes 4096 Venus
+    // orbits take 1.49 ms against 1.52 with 512-thread workgroups, 12000 eccentric ICs in
+    // refilled columns 5.72 against 6.03; at 64 nodes about 9 %.  A 256-node block of 8 ICs
+    // needs all 512 threads.
     const int tuned = ctx->tile_table[log2_index(np_max)];
-    const int pick = tuned != 0 ? tuned : (np_max <= 64 ? 1024 : 2048);
+    const int pick = tuned != 0 ? tuned : (np_max <= 128 ? 1024 : 2048);
     if (pick == 1024 && np_max * 8 <= 1024) return 1024;
     return 2048;
 }
