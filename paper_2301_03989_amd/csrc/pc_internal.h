@@ -139,7 +139,7 @@ struct PcFlybyParams {
     int64_t n_threads;        // sum over groups of n_ic * samples
 };
 int pc_launch_flyby(const PcFlybyParams& p, void* stream);
-int pc_launch_adjoint(const PcAdjParams& a, const PcAdjParams* a_dev, int grid, void* stream);
+int pc_launch_adjoint(const PcAdjParams& a, const PcAdjParams* a_dev, int pairs, int grid, void* stream);
 int pc_launch_apply_operator(int NP, const double* kfrag, int N, int64_t n_cols, const double* F,
                              const double* y0, double scale, double* Y, void* stream);
 int pc_launch_eval_force(const double* r, const double* t, int64_t n, const PcBodyDev* bodies,

@@ -166,16 +166,17 @@ int pc_launch_copy_runs(const PcCopyDev* list, int64_t n, void* stream)
 // keeps its blocks of the current iterate in registers (in the MFMA result layout), computes
 // the dynamics for the (node, IC) pairs it owns straight from them, and publishes only the
 // force matrix F = (v, a) to LDS, where the product y_new = y0 + w2 K_N F reads it.
-// The workgroup's LDS arena, one per job shape (file scope, so that the non-inlined job
-// bodies below address it as LDS).
-__shared__ PcSmem<2048> g_smem2048;
-__shared__ PcSmem<1024> g_smem1024;
-template <int PAIRS>
-static __device__ __forceinline__ PcSmem<PAIRS>& pc_smem();
-template <>
-__device__ __forceinline__ PcSmem<2048>& pc_smem<2048>() { return g_smem2048; }
-template <>
-__device__ __forceinline__ PcSmem<1024>& pc_smem<1024>() { return g_smem1024; }
+// The workgroup's LDS arena (file scope, so that the non-inlined job bodies below address it as
+// LDS), one per kernel and job shape: an arena that two kernels reach, beside another such one,
+// has its address looked up in a table in memory by every use.
+__shared__ PcSmem<2048> g_smem2048, g_smem2048_adj;
+__shared__ PcSmem<1024> g_smem1024, g_smem1024_adj;
+template <int PAIRS, bool ADJ = false>
+static __device__ __forceinline__ PcSmem<PAIRS>& pc_smem()
+{
+    if constexpr (PAIRS == 2048) return ADJ ? g_smem2048_adj : g_smem2048;
+    else return ADJ ? g_smem1024_adj : g_smem1024;
+}
 
 // Segment s's ephemeris records (perturber data per node, Sec. 5.4.1) into LDS: positions
 // as [node][body][3] with the indirect term as body P, and per body mu, 3 mu / 2 and
@@ -914,7 +915,7 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
 {
     using Sh = PcShape<PAIRS, NP>;
     constexpr int T = Sh::T, W = Sh::W, COLS = Sh::COLS;
-    PcSmem<PAIRS>& sm = pc_smem<PAIRS>();
+    PcSmem<PAIRS>& sm = pc_smem<PAIRS, true>();
     const PcParams& p = a.fwd;
     double* sF = sm.F;
     double* sY0 = sm.Y0;
@@ -923,13 +924,15 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
     const int N = g.N, S = g.S, P = p.n_pert;
     const int n = job.n;
     const int64_t ic = job.ic0 + tid;
-    // adjoint scratch at the top of the record area: seed Lam, estimate LamIt, partial sums
-    // [wave][comp][column]
-    constexpr int ADJ = 12 * T + W * 6 * COLS;
-    constexpr int REC_CAP = PcSmem<PAIRS>::REC - ADJ;
-    double* sLam = sm.Rec + REC_CAP;
+    // adjoint scratch: seed Lam and estimate LamIt behind the weights in Y0 where they fit, else
+    // at the top of the record area; the sweeps' partial sums [wave][comp][column] over the
+    // records' end, which the sweeps no longer read (the Jacobian is formed before them)
+    constexpr int PARTS = W * 6 * COLS;
+    constexpr bool IN_Y0 = 18 * T + 3 * Sh::KR <= 6 * (PAIRS / 16);
+    constexpr int REC_CAP = PcSmem<PAIRS>::REC - (IN_Y0 ? 0 : 12 * T);
+    double* sLam = IN_Y0 ? sY0 + 6 * T + 3 * Sh::KR : sm.Rec + REC_CAP;
     double* sLamIt = sLam + 6 * T;
-    double* sLamPart = sLamIt + 6 * T;
+    double* sLamPart = sm.Rec + REC_CAP - PARTS;
     const bool rec_lds = N * 3 * (P + 1) <= REC_CAP;
     const double t2a = a.adj_tol * a.adj_tol;
 
@@ -1176,7 +1179,7 @@ __device__ __attribute__((noinline)) void pc_adjoint_job(const PcAdjParams& a, c
 }
 
 template <int PAIRS>
-__global__ __launch_bounds__(PAIRS / 4) void pc_adjoint_kernel(const PcAdjParams* __restrict__ ap)
+__global__ __launch_bounds__(PAIRS / 4, 2) void pc_adjoint_kernel(const PcAdjParams* __restrict__ ap)
 {
     __shared__ int sJob;
     const PcAdjParams& a = *ap;
@@ -1194,17 +1197,22 @@ __global__ __launch_bounds__(PAIRS / 4) void pc_adjoint_kernel(const PcAdjParams
         case 32: eih ? pc_adjoint_job<PAIRS, 32, true>(a, job, g) : pc_adjoint_job<PAIRS, 32>(a, job, g); break;
         case 64: eih ? pc_adjoint_job<PAIRS, 64, true>(a, job, g) : pc_adjoint_job<PAIRS, 64>(a, job, g); break;
         case 128: eih ? pc_adjoint_job<PAIRS, 128, true>(a, job, g) : pc_adjoint_job<PAIRS, 128>(a, job, g); break;
-        case 256: eih ? pc_adjoint_job<PAIRS, 256, true>(a, job, g) : pc_adjoint_job<PAIRS, 256>(a, job, g); break;
+        case 256:
+            if constexpr (PAIRS >= 2048) eih ? pc_adjoint_job<PAIRS, 256, true>(a, job, g) : pc_adjoint_job<PAIRS, 256>(a, job, g);
+            break;
         default: break;
         }
     }
 }
 
-int pc_launch_adjoint(const PcAdjParams& a, const PcAdjParams* a_dev, int grid, void* stream)
+int pc_launch_adjoint(const PcAdjParams& a, const PcAdjParams* a_dev, int pairs, int grid, void* stream)
 {
     if (a.fwd.n_jobs <= 0) return hipSuccess;
     if (grid <= 0 || grid > a.fwd.n_jobs) grid = a.fwd.n_jobs;
-    hipLaunchKernelGGL(pc_adjoint_kernel<2048>, dim3(grid), dim3(512), 0, (hipStream_t)stream, a_dev);
+    if (pairs == 1024)
+        hipLaunchKernelGGL(pc_adjoint_kernel<1024>, dim3(grid), dim3(256), 0, (hipStream_t)stream, a_dev);
+    else
+        hipLaunchKernelGGL(pc_adjoint_kernel<2048>, dim3(grid), dim3(512), 0, (hipStream_t)stream, a_dev);
     return hipGetLastError();
 }
 

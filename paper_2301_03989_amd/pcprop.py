@@ -422,7 +422,7 @@ class Context:
         garr = (_Group * len(groups))(*[_Group(g.ic_offset, g.n_ic, g.t0, g.tf, g.nodes, g.segments, g.tol)
                                        for g in groups])
         mc, oc = model._c(), self.opts(**opts)
-        oc.tile_pairs = 2048
+        oc.tile_pairs = 1024 if N_max <= 128 and oc.order == 1 else 2048   # the shape pc_adjoint takes
         nb = ctypes.c_size_t()
         rc = self.lib.pc_workspace_bytes(self.handle, garr, len(groups), ctypes.byref(mc), ctypes.byref(oc),
                                          ctypes.byref(nb))
