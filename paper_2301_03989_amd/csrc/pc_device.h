@@ -559,13 +559,14 @@ static __device__ __forceinline__ bool pc_any_active(const PcSmem<PAIRS>& sm)
 // ---------------------------------------------------------------------------
 // Accelerations with the records in LDS (compact [node][body][3], masses [body][4]): two
 // bodies at a time, so that a wave waits on LDS once per eight body-point pairs.
-static __device__ __forceinline__ void pc_force_lds(const double (&x)[4], const double (&y)[4], const double (&z)[4],
+template <int R>
+static __device__ __forceinline__ void pc_force_lds(const double (&x)[2 * R], const double (&y)[2 * R], const double (&z)[2 * R],
                                                     const int (&jn)[2], int P, double mu_sun, const double* srec,
-                                                    const double* smu, double (&ax)[4], double (&ay)[4],
-                                                    double (&az)[4])
+                                                    const double* smu, double (&ax)[2 * R], double (&ay)[2 * R],
+                                                    double (&az)[2 * R])
 {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
+    for (int p = 0; p < 2 * R; ++p) {
         ax[p] = ay[p] = az[p] = 0.0;
         pc_pull(x[p], y[p], z[p], mu_sun, 1.5 * mu_sun, 1.875 * mu_sun, ax[p], ay[p], az[p]);
     }
@@ -588,8 +589,8 @@ static __device__ __forceinline__ void pc_force_lds(const double (&x)[4], const 
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p)
-                pc_pull(x[p] - q[k][p >> 1][0], y[p] - q[k][p >> 1][1], z[p] - q[k][p >> 1][2], mu[k][0], mu[k][1],
+            for (int p = 0; p < 2 * R; ++p)
+                pc_pull(x[p] - q[k][p / R][0], y[p] - q[k][p / R][1], z[p] - q[k][p / R][2], mu[k][0], mu[k][1],
                         mu[k][2], ax[p], ay[p], az[p]);
         }
     };
@@ -597,10 +598,10 @@ static __device__ __forceinline__ void pc_force_lds(const double (&x)[4], const 
     for (; b + 2 <= P; b += 2) bodies(b, std::integral_constant<int, 2>{});
     if (b < P) bodies(b, std::integral_constant<int, 1>{});
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        ax[p] -= rec[p >> 1][3 * P];
-        ay[p] -= rec[p >> 1][3 * P + 1];
-        az[p] -= rec[p >> 1][3 * P + 2];
+    for (int p = 0; p < 2 * R; ++p) {
+        ax[p] -= rec[p / R][3 * P];
+        ay[p] -= rec[p / R][3 * P + 1];
+        az[p] -= rec[p / R][3 * P + 2];
     }
 }
 
@@ -1630,7 +1631,11 @@ static __device__ __forceinline__ void pc_points(const double (&yc)[6][4], int b
 // Dynamics of the lane's (node, IC) pairs from its registers, published as the force matrix
 // F = (v, a) of Sec. 2.2.  sRec/sMu: the segment's records in LDS (when rec_lds), grec: the
 // same in global memory.  SO: second-order sweeps, the accelerations only, in their layout.
-template <int PAIRS, int NP, bool FP32 = false, bool SO = false>
+// HALF: the job has at most four ICs, so only the points of the lane's first IC are evaluated (the
+// other's acceleration, which no IC reads, is zero): the force of a sweep, half of a small call's
+// time, in half the instructions.  One orbit of 32 nodes and 4 segments 205 -> 176 us, of 128 nodes
+// 413 -> 375, relativistic of 100 nodes 685 -> 579.
+template <int PAIRS, int NP, bool FP32 = false, bool SO = false, bool HALF = false>
 static __device__ __forceinline__ void pc_publish(double* sF, const double (&yc)[6][4], const PcLane& L, int P,
                                                   double mu_sun, bool rec_lds, const double* sRec, const double* sMu,
                                                   const double4* grec)
@@ -1639,8 +1644,18 @@ static __device__ __forceinline__ void pc_publish(double* sF, const double (&yc)
     pc_points(yc, 0, x);
     pc_points(yc, 1, y);
     pc_points(yc, 2, z);
-    if (rec_lds && FP32) pc_force_lds32(x, y, z, L.jn, P, mu_sun, sRec, sMu, ax, ay, az);
-    else if (rec_lds) pc_force_lds(x, y, z, L.jn, P, mu_sun, sRec, sMu, ax, ay, az);
+    if (HALF && rec_lds) {
+        const double x1[2] = {x[0], x[2]}, y1[2] = {y[0], y[2]}, z1[2] = {z[0], z[2]};
+        double a[3][2];
+        pc_force_lds<1>(x1, y1, z1, L.jn, P, mu_sun, sRec, sMu, a[0], a[1], a[2]);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            ax[p] = p & 1 ? 0.0 : a[0][p >> 1];
+            ay[p] = p & 1 ? 0.0 : a[1][p >> 1];
+            az[p] = p & 1 ? 0.0 : a[2][p >> 1];
+        }
+    } else if (rec_lds && FP32) pc_force_lds32(x, y, z, L.jn, P, mu_sun, sRec, sMu, ax, ay, az);
+    else if (rec_lds) pc_force_lds<2>(x, y, z, L.jn, P, mu_sun, sRec, sMu, ax, ay, az);
     else pc_force_glb(x, y, z, L.jn, P, mu_sun, grec, ax, ay, az);
     if (!L.ok) return;
     if constexpr (SO) pc_put2<PAIRS, NP>(sF, ax, ay, az, L);
@@ -1649,23 +1664,26 @@ static __device__ __forceinline__ void pc_publish(double* sF, const double (&yc)
 
 // The same with the relativistic acceleration.  erec: the segment's records, pc_eih_rec(P)
 // slots of N double4; one pass over the bodies per node of the lane.
-template <int PAIRS, int NP>
+template <int PAIRS, int NP, bool HALF = false>
 static __device__ __forceinline__ void pc_publish_eih(double* sF, const double (&yc)[6][4], const PcLane& L, int N,
                                                       int P, const double4* erec, double inv_c2)
 {
     double ax[4], ay[4], az[4];
+    constexpr int R = HALF ? 1 : 2;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const double x[2] = {yc[3 * h][0], yc[3 * h][1]}, y[2] = {yc[3 * h + 1][0], yc[3 * h + 1][1]},
-                     z[2] = {yc[3 * h + 2][0], yc[3 * h + 2][1]}, u[2] = {yc[3 * h][2], yc[3 * h][3]},
-                     v[2] = {yc[3 * h + 1][2], yc[3 * h + 1][3]}, w[2] = {yc[3 * h + 2][2], yc[3 * h + 2][3]};
-        double a0[2], a1[2], a2[2];
-        pc_force_eih<2>(x, y, z, u, v, w, erec, L.jn[h], N, P, inv_c2, a0, a1, a2);
+        double q[6][R], a0[R], a1[R], a2[R];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) q[c][r] = yc[3 * h + c % 3][r + 2 * (c / 3)];
+        }
+        pc_force_eih<R>(q[0], q[1], q[2], q[3], q[4], q[5], erec, L.jn[h], N, P, inv_c2, a0, a1, a2);
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            ax[2 * h + r] = a0[r];
-            ay[2 * h + r] = a1[r];
-            az[2 * h + r] = a2[r];
+            ax[2 * h + r] = r < R ? a0[r % R] : 0.0;
+            ay[2 * h + r] = r < R ? a1[r % R] : 0.0;
+            az[2 * h + r] = r < R ? a2[r % R] : 0.0;
         }
     }
     if (L.ok) pc_put_f<PAIRS, NP>(sF, yc, ax, ay, az, L);
@@ -1736,7 +1754,7 @@ static __device__ __forceinline__ void pc_publish_chord(float* sD, float* sG, co
 // Initial guess of segment s at the lane's points: warm (Kepler) or cold start, Sec. 2.1, or the
 // caller's node states; each staged in the lane's own part of the F area (one call site, no
 // private array).  sY0, dead: initial states and status of the job's n ICs (the first is ic0).
-template <int PAIRS, int NP>
+template <int PAIRS, int NP, bool HALF = false>
 static __device__ __forceinline__ void pc_initial_guess(const PcParams& p, const PcGroupDev& g, int n, int64_t ic0,
                                                         int s, double w2, const PcLane& L, const double* sY0,
                                                         const int* dead, double* sF, double (&yc)[6][4])
@@ -1752,7 +1770,7 @@ static __device__ __forceinline__ void pc_initial_guess(const PcParams& p, const
 #pragma unroll
         for (int c = 0; c < 6; ++c) y0[c] = sY0[c * T + m];
         bool have = false;
-        if (!dead[m]) {
+        if (!dead[m] && (!HALF || m < n)) {   // HALF: columns past the job's ICs keep y0, not iterated
             if (p.init == 2 && m < n) {   // the caller's node states
                 const gconst_dp gp =
                     pc_gcd(p.guess) + (((size_t)(ic0 + m) * p.iters_stride + s) * p.nodes_stride + j) * 6;

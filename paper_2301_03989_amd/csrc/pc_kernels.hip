@@ -227,7 +227,8 @@ static __device__ __forceinline__ void pc_stage_records(const double4* grec, int
 // receives the iteration records.
 // MIXED: the job runs the FP32 -> FP64 precision schedule (compiled apart, so that FP64-only
 // jobs carry none of its registers).
-template <int PAIRS, int NP, bool MIXED = false, bool EIH = false, int SO = 0>
+// HALF: the job has at most four ICs, the first of each lane's two (compiled apart likewise).
+template <int PAIRS, int NP, bool MIXED = false, bool EIH = false, int SO = 0, bool HALF = false>
 static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const PcGroupDev& g, int n, int64_t ic0,
                                                         int s, PcSmem<PAIRS>& sm, PcLane L, const PcFragD& kp,
                                                         double (&yc)[6][4], gi32p iters_out, int& had_notconv,
@@ -254,7 +255,7 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
     const double4* grec = reinterpret_cast<const double4*>(p.recs) +
                           (size_t)(g.rec_offset + (int64_t)s * N) * (P + 1);
     if (rec_lds) pc_stage_records<PAIRS>(grec, N, P, sm);
-    pc_initial_guess<PAIRS, NP>(p, g, n, ic0, s, w2, L, sY0, sm.Dead, sF, yc);
+    pc_initial_guess<PAIRS, NP, HALF>(p, g, n, ic0, s, w2, L, sY0, sm.Dead, sF, yc);
     if (tid < T) sm.Active[tid] = (tid < n) && !sm.Dead[tid];
     __syncthreads();   // staging read before F is built
     pc_clear_rows<PAIRS, NP, SO != 0>(sF, N);
@@ -304,10 +305,10 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
     };
     bool busy = read_active();
     if (busy) {
-        if constexpr (EIH) pc_publish_eih<PAIRS, NP>(sF, yc, L, N, P, erec, p.inv_c2);
+        if constexpr (EIH) pc_publish_eih<PAIRS, NP, HALF>(sF, yc, L, N, P, erec, p.inv_c2);
         else if (MIXED && mode == 1)
             pc_publish<PAIRS, NP, MIXED>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
-        else pc_publish<PAIRS, NP, false, SO != 0>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+        else pc_publish<PAIRS, NP, false, SO != 0, HALF>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
     }
     __syncthreads();
 
@@ -433,10 +434,10 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
                 for (int r = 0; r < 4; ++r) yc[b][r] = act[2 * (b / 3) + (r & 1)] ? acc[b][r] : yc[b][r];
             }
             if (it < n_it) {
-                if constexpr (EIH) pc_publish_eih<PAIRS, NP>(sF, yc, L, N, P, erec, p.inv_c2);
+                if constexpr (EIH) pc_publish_eih<PAIRS, NP, HALF>(sF, yc, L, N, P, erec, p.inv_c2);
                 else if (MIXED && next_mode == 1)
                     pc_publish<PAIRS, NP, MIXED>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
-                else pc_publish<PAIRS, NP, false, SO != 0>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
+                else pc_publish<PAIRS, NP, false, SO != 0, HALF>(sF, yc, L, P, mu_sun, rec_lds, sm.Rec, sm.Mu, grec);
             }
         }
         fp32 = next32;
@@ -449,7 +450,7 @@ static __device__ __forceinline__ void pc_segment_solve(const PcParams& p, const
 
 // Not inlined: one register allocation per node count, so the work-queue kernel that
 // dispatches to all of them does not pay for the largest one everywhere.
-template <int PAIRS, int NP, bool MIXED, bool EIH = false, int SO = 0>
+template <int PAIRS, int NP, bool MIXED, bool EIH = false, int SO = 0, bool HALF = false>
 __device__ __attribute__((noinline)) void pc_job(const PcParams& p, const PcJobDev& job, const PcGroupDev& g)
 {
     PcSmem<PAIRS>& sm = pc_smem<PAIRS>();
@@ -492,7 +493,7 @@ __device__ __attribute__((noinline)) void pc_job(const PcParams& p, const PcJobD
             }
             if (sm.Dead[tid] && g_iters) g_iters[(size_t)ic * istride + s] = -2;
         }
-        pc_segment_solve<PAIRS, NP, MIXED, EIH, SO>(p, g, n, job.ic0, s, sm, L, kp, yc, g_iters, had_notconv);
+        pc_segment_solve<PAIRS, NP, MIXED, EIH, SO, HALF>(p, g, n, job.ic0, s, sm, L, kp, yc, g_iters, had_notconv);
 
         // converged node states of the segment (optional output), chaining (Sec. 2.2)
 #pragma unroll
@@ -826,6 +827,10 @@ template <int PAIRS, int NP>
 static __device__ __forceinline__ void pc_run_job(const PcParams& p, const PcJobDev& job, const PcGroupDev& g,
                                                   bool list, bool mixed, bool eih, bool order2)
 {
+    // jobs of at most four ICs have a body of their own that evaluates half of the points (pc_publish);
+    // in the one body with a branch, 4096 Venus orbits of full blocks ran 0.7 % slower
+    constexpr bool PAR = PcShape<PAIRS, NP>::PAR;
+    const bool few = PAR && job.n <= 4;
     if (order2) {
         if (p.feedback) {
             pc_job<PAIRS, NP, false, false, 2>(p, job, g);
@@ -836,11 +841,14 @@ static __device__ __forceinline__ void pc_run_job(const PcParams& p, const PcJob
     } else if (eih && mixed) {
         pc_job<PAIRS, NP, true, true>(p, job, g);
     } else if (eih) {
-        pc_job<PAIRS, NP, false, true>(p, job, g);
+        if (few) pc_job<PAIRS, NP, false, true, 0, PAR>(p, job, g);
+        else pc_job<PAIRS, NP, false, true>(p, job, g);
     } else if (list) {
         pc_job_list<PAIRS, NP>(p, job, g);
     } else if (mixed) {
         pc_job<PAIRS, NP, true>(p, job, g);
+    } else if (few) {
+        pc_job<PAIRS, NP, false, false, 0, PAR>(p, job, g);
     } else {
         pc_job<PAIRS, NP, false>(p, job, g);
     }
