@@ -506,8 +506,8 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
         plan.small_128 = o.tile_pairs == 0 && plan.pairs == 1024 && np_max == 128 && ctx->tile_table[log2_index(128)] == 0;
     }
     if (o.order == 2) {
-        // second-order sweeps need blocks of 16 or more ICs (the transposed product) up to
-        // 128 nodes; 256-node groups run 8-IC node-row jobs
+        // second-order sweeps run in blocks of 16 or more ICs up to 128 nodes (an explicit
+        // tile_pairs 1024 that leaves fewer is refused), of 8 at 256
         for (int gi = 0; gi < n_groups; ++gi) {
             const int np = padded_nodes(std::max(3, std::min((int)groups[gi].nodes, PC_MAX_NODES)));
             if (np > 128) continue;
