@@ -426,6 +426,7 @@ struct JobClass {
 struct Plan {
     int pairs = 2048;
     bool small_128 = false;   // 1024 pairs by the untuned rule at 128 nodes: 2048 would do as well
+    bool few = false;         // jobs of four ICs by the untuned rule: whole blocks would do as well
     bool plain = false;
     std::vector<JobClass> classes;
     std::vector<int> group_job_begin;   // plain path: jobs of group g are [begin[g], begin[g+1])
@@ -490,9 +491,10 @@ int choose_pairs(const pc_ctx* ctx, const pc_group* groups, int n_groups, const 
 // (the allocation-free entry point builds none).
 // seg0 (or null): per group, the first segment to run on its t0 + k h grid (refinement
 // passes resume a span at a segment boundary); the group then runs segments - seg0[g].
+// few_ok: small calls may run jobs of four ICs (Plan::few), a longer job table.
 int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, const pc_model* model,
               const pc_opts& o, bool build_tables, Plan& plan, bool lists_ok = false, bool cached_only = false,
-              const int* seg0 = nullptr)
+              const int* seg0 = nullptr, bool few_ok = true)
 {
     if (!groups || n_groups < 1) return set_error(ctx, PC_EINVAL, "need at least one group");
     if (o.tile_pairs != 0 && o.tile_pairs != 1024 && o.tile_pairs != 2048)
@@ -589,6 +591,24 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
         list_np[k] = list;
         if (lists_ok && o.job_list == 0 && ctx->list_table[k] != 0) list_np[k] = ctx->list_table[k];
     }
+    // Small calls: jobs of four ICs, which have a body of half the force work (pc_publish), as long
+    // as each job has a CU of its own.  Sweeps of a small call are one wave's serial chain, so fewer
+    // ICs per workgroup shorten it and idle CUs take the rest (past one job per CU two jobs would
+    // share it, each as long as a whole block's sweep).  With whole blocks and with four ICs: 300
+    // Venus orbits of 128 nodes 418 and 381 us, 1000 of them 424 and 387, 1000 relativistic ones of
+    // 100 nodes 691 and 584, 512 eccentric ICs of 48 nodes 766 and 631.
+    const bool few_can = few_ok && o.tile_pairs == 0 && o.job_list == 0 && o.path == PC_PATH_FUSED &&
+                         o.precision == PC_FP64 && o.order == 1;
+    if (few_can) {
+        int64_t nj = 0;
+        bool tuned = false;
+        for (int gi = 0; gi < n_groups; ++gi) {
+            nj += (groups[gi].n_ic + 3) / 4;
+            const int np = padded_nodes(groups[gi].nodes);
+            tuned = tuned || np < 32 || ctx->list_table[log2_index(np)] != 0;
+        }
+        plan.few = !tuned && nj <= ctx->n_cu;
+    }
     plan.list = list;
     struct Cost { int np; double c; PcJobDev j; };
     std::vector<Cost> costs;
@@ -625,7 +645,7 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
         plan.groups.push_back(d);
         // cost model of one job: segments x NP x column blocks (matrix work per iteration
         // ~ NP^2 T = NP * PAIRS per block)
-        const int64_t per_job = (int64_t)list_np[log2_index(d.NP)] * d.T;
+        const int64_t per_job = plan.few ? 4 : (int64_t)list_np[log2_index(d.NP)] * d.T;
         for (int64_t i0 = 0; i0 < G.n_ic; i0 += per_job) {
             PcJobDev j{};
             j.ic0 = G.ic_offset + i0;
@@ -1253,11 +1273,13 @@ static int propagate_impl(pc_ctx* ctx, const double* ics, int64_t n_ic, const pc
                           o.init != PC_INIT_GUESS;
     rc = make_plan(ctx, n_ic, groups, n_groups, model, o, true, plan, lists_ok, no_alloc);
     if (rc != PC_OK) return rc;
-    if (plan.small_128 && (ws_bytes < plan.total || (no_alloc && plan.staged + kAlign > ctx->staging_bytes))) {
-        // the small shape's longer job table does not fit what the caller gave: the large shape's may
-        o.tile_pairs = 2048;
+    // where the longer job tables of four-IC jobs or of the small shape do not fit what the caller
+    // gave, those of whole blocks or of the large shape may
+    auto fits = [&] { return plan.total <= ws_bytes && !(no_alloc && plan.staged + kAlign > ctx->staging_bytes); };
+    for (int tries = 0; tries < 2 && (plan.few || plan.small_128) && !fits(); ++tries) {
+        if (!plan.few) o.tile_pairs = 2048;
         plan = Plan();
-        rc = make_plan(ctx, n_ic, groups, n_groups, model, o, true, plan, lists_ok, no_alloc);
+        rc = make_plan(ctx, n_ic, groups, n_groups, model, o, true, plan, lists_ok, no_alloc, nullptr, false);
         if (rc != PC_OK) return rc;
     }
     if ((iters_out || bounds_out || nodes_out) && iters_stride < plan.max_S)
