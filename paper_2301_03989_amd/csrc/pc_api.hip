@@ -1428,7 +1428,10 @@ static int propagate_impl(pc_ctx* ctx, const double* ics, int64_t n_ic, const pc
         if (ctx->timing) PC_HIP_DRAIN(ctx, hs, hipEventRecord(ctx->ev1, hs));
         PC_HIP_DRAIN(ctx, hs, hipMemcpyAsync(hc, pp.counters, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, hs));
     } else if (o.graph) {
-        // signature of the call: a captured graph is replayed only for the same one
+        // signature of the call: a captured graph is replayed only for the same one.  The plan's
+        // layout belongs to it: the job lengths also follow the context's tables (pc_set_job_list,
+        // pc_autotune), and the captured copy and ephemeris launch hold the table offsets they
+        // were captured with.
         std::vector<char> key;
         auto put = [&key](const void* q, size_t nb) {
             key.insert(key.end(), static_cast<const char*>(q), static_cast<const char*>(q) + nb);
@@ -1448,6 +1451,9 @@ static int propagate_impl(pc_ctx* ctx, const double* ics, int64_t n_ic, const pc
         put(&nodes_stride, sizeof(nodes_stride));
         put(&ws_bytes, sizeof(ws_bytes));
         put(&plan.pairs, sizeof(plan.pairs));
+        const size_t layout[9] = {plan.jobs.size(), plan.off_counters, plan.off_params, plan.off_groups, plan.off_jobs,
+                                  plan.off_bodies, plan.off_recs, plan.off_recs_eih, plan.staged};
+        put(layout, sizeof(layout));
         if (!ctx->graph_exec || key != ctx->graph_key) {
             drop_graph(ctx);
             PC_HIP(ctx, hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal));
