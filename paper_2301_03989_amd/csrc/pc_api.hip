@@ -499,26 +499,6 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
     if (!groups || n_groups < 1) return set_error(ctx, PC_EINVAL, "need at least one group");
     if (o.tile_pairs != 0 && o.tile_pairs != 1024 && o.tile_pairs != 2048)
         return set_error(ctx, PC_EINVAL, "tile_pairs must be 0, 1024 or 2048");
-    plan.pairs = choose_pairs(ctx, groups, n_groups, o);
-    plan.plain = (o.path == PC_PATH_PLAIN);
-    if (plan.plain) plan.pairs = 2048;
-    {
-        int np_max = 16;
-        for (int gi = 0; gi < n_groups; ++gi) np_max = std::max(np_max, padded_nodes(groups[gi].nodes));
-        plan.small_128 = o.tile_pairs == 0 && plan.pairs == 1024 && np_max == 128 && ctx->tile_table[log2_index(128)] == 0;
-    }
-    if (o.order == 2) {
-        // second-order sweeps run in blocks of 16 or more ICs up to 128 nodes (an explicit
-        // tile_pairs 1024 that leaves fewer is refused), of 8 at 256
-        for (int gi = 0; gi < n_groups; ++gi) {
-            const int np = padded_nodes(std::max(3, std::min((int)groups[gi].nodes, PC_MAX_NODES)));
-            if (np > 128) continue;
-            if (plan.pairs / np < 16) {
-                if (o.tile_pairs == 1024) return set_error(ctx, PC_EINVAL, "order 2 with %d nodes needs tile_pairs 2048", groups[gi].nodes);
-                plan.pairs = 2048;
-            }
-        }
-    }
     std::vector<std::pair<int64_t, int64_t>> spans;
     plan.groups.clear();
     plan.jobs.clear();
@@ -538,9 +518,6 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
             return set_error(ctx, PC_EINVAL, "group %d: need finite t0 != tf", gi);
         if (!(G.tol > 0.0) || !std::isfinite(G.tol))
             return set_error(ctx, PC_EINVAL, "group %d: tol must be positive and finite", gi);
-        const int NP = padded_nodes(G.nodes);
-        if (NP * 8 > plan.pairs)
-            return set_error(ctx, PC_EINVAL, "group %d: %d nodes need tile_pairs >= %d", gi, G.nodes, NP * 8);
         spans.push_back({G.ic_offset, G.ic_offset + G.n_ic});
         plan.max_S = std::max(plan.max_S, G.segments - (seg0 ? seg0[gi] : 0));
         plan.max_N = std::max(plan.max_N, G.nodes);
@@ -548,6 +525,33 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
     std::sort(spans.begin(), spans.end());
     for (size_t i = 1; i < spans.size(); ++i)
         if (spans[i].first < spans[i - 1].second) return set_error(ctx, PC_EINVAL, "groups overlap");
+
+    // the shape, now that every node count is known to be in range (padded_nodes only ends then)
+    plan.pairs = choose_pairs(ctx, groups, n_groups, o);
+    plan.plain = (o.path == PC_PATH_PLAIN);
+    if (plan.plain) plan.pairs = 2048;
+    {
+        int np_max = 16;
+        for (int gi = 0; gi < n_groups; ++gi) np_max = std::max(np_max, padded_nodes(groups[gi].nodes));
+        plan.small_128 = o.tile_pairs == 0 && plan.pairs == 1024 && np_max == 128 && ctx->tile_table[log2_index(128)] == 0;
+    }
+    if (o.order == 2) {
+        // second-order sweeps run in blocks of 16 or more ICs up to 128 nodes (an explicit
+        // tile_pairs 1024 that leaves fewer is refused), of 8 at 256
+        for (int gi = 0; gi < n_groups; ++gi) {
+            const int np = padded_nodes(groups[gi].nodes);
+            if (np > 128) continue;
+            if (plan.pairs / np < 16) {
+                if (o.tile_pairs == 1024) return set_error(ctx, PC_EINVAL, "order 2 with %d nodes needs tile_pairs 2048", groups[gi].nodes);
+                plan.pairs = 2048;
+            }
+        }
+    }
+    for (int gi = 0; gi < n_groups; ++gi) {
+        const int NP = padded_nodes(groups[gi].nodes);
+        if (NP * 8 > plan.pairs)
+            return set_error(ctx, PC_EINVAL, "group %d: %d nodes need tile_pairs >= %d", gi, groups[gi].nodes, NP * 8);
+    }
 
     // ICs per job in units of the job's columns (1, 2, 4 or 8 blocks).  Longer jobs refill
     // their columns for longer, so fewer columns idle in segment tails (on 16384 eccentric
