@@ -124,7 +124,10 @@ typedef struct {
     int32_t fixed_iters;  /* > 0: run exactly this many iterations per segment (no stopping rule) */
     int32_t tile_pairs;   /* nodes x ICs held by one workgroup: 0 = the context's table (set by
                              pc_autotune or pc_set_tile_pairs; untuned: 1024 up to 128 padded
-                             nodes, else 2048), 1024 or 2048 */
+                             nodes, else 2048; also 2048 where the records of more than 8
+                             perturbers fit that shape's LDS only, for the FP32 schedule and
+                             for point-mass calls that fill the chip or run jobs of four ICs),
+                             1024 or 2048 */
     int32_t graph;        /* fused path: 1 = capture the call's device work (table copy, ephemeris,
                              propagation kernel, status copy) in a HIP graph and replay it while
                              the call's shapes, options and pointers repeat (default 0) */

@@ -468,21 +468,41 @@ int log2_index(int np)
     return k;   // 16 -> 0 ... 256 -> 4
 }
 
-int choose_pairs(const pc_ctx* ctx, const pc_group* groups, int n_groups, const pc_opts& o)
+// few: the call runs jobs of four ICs (Plan::few).
+int choose_pairs(const pc_ctx* ctx, const pc_group* groups, int n_groups, const pc_model* model, const pc_opts& o,
+                 bool few)
 {
     if (o.tile_pairs == 1024 || o.tile_pairs == 2048) return o.tile_pairs;
     int np_max = 16;
     for (int i = 0; i < n_groups; ++i) np_max = std::max(np_max, padded_nodes(groups[i].nodes));
+    const int tuned = ctx->tile_table[log2_index(np_max)];
+    if (tuned != 0) return tuned == 1024 && np_max * 8 <= 1024 ? 1024 : 2048;
     // untuned default: the 256-thread shape up to 128 padded nodes, where two of its
     // workgroups share a CU and one's sweeps fill the other's waits at barriers, segment
     // starts and refills; both shapes hold mirrored pairs by 8 ICs.  At 128 nodes 4096 Venus
     // orbits take 1.49 ms against 1.52 with 512-thread workgroups, 12000 eccentric ICs in
     // refilled columns 5.72 against 6.03; at 64 nodes about 9 %.  A 256-node block of 8 ICs
     // needs all 512 threads.
-    const int tuned = ctx->tile_table[log2_index(np_max)];
-    const int pick = tuned != 0 ? tuned : (np_max <= 128 ? 1024 : 2048);
-    if (pick == 1024 && np_max * 8 <= 1024) return 1024;
-    return 2048;
+    if (np_max > 128) return 2048;
+    // With more than 8 perturbers near 128 nodes the records fit the large shape's LDS only; in
+    // the small one every sweep reads them from memory.  Small and large shape at 128 nodes, 9 and
+    // 16 perturbers: 4096 Venus orbits 1.62 and 1.52, 1.98 and 1.81 ms; 12000 of them 5.33 and
+    // 4.44, 5.81 and 5.29.  While every block of the small shape has a CU of its own, the large
+    // one's twice as long blocks lose more (2000 orbits: 1.00 and 1.50, 1.24 and 1.80), unless the
+    // jobs are of four ICs, equally long in both (300 orbits: 0.99 and 0.84, 1.23 and 0.95).  The FP32 -> FP64 schedule needs the records
+    // in LDS for its increment sweeps: without them it runs FP32 Picard sweeps (12000 orbits, 16
+    // perturbers: 6.27 and 3.89 ms, largest error 1.7e-12 and 1.1e-12).  Relativistic FP64 sweeps
+    // read other records, from memory in both.
+    bool fit = true;
+    int64_t blocks = 0;
+    for (int i = 0; i < n_groups; ++i) {
+        const int np = padded_nodes(groups[i].nodes);
+        fit = fit && 3 * groups[i].nodes * (model->n_pert + 1) <= pc_rec_cap(1024);
+        blocks += (groups[i].n_ic + 1024 / np - 1) / (1024 / np);
+    }
+    if (fit) return 1024;
+    if (o.precision == PC_FP32_THEN_FP64) return 2048;
+    return model->inv_c2 > 0.0 || !(few || blocks > ctx->n_cu) ? 1024 : 2048;
 }
 
 // lists_ok: jobs may hold more ICs than columns (refilled columns; fused FP64 forward calls).
@@ -526,8 +546,26 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
     for (size_t i = 1; i < spans.size(); ++i)
         if (spans[i].first < spans[i - 1].second) return set_error(ctx, PC_EINVAL, "groups overlap");
 
-    // the shape, now that every node count is known to be in range (padded_nodes only ends then)
-    plan.pairs = choose_pairs(ctx, groups, n_groups, o);
+    // from here on every node count is known to be in range (padded_nodes only ends then)
+    // Small calls: jobs of four ICs, which have a body of half the force work (pc_publish), as long
+    // as each job has a CU of its own.  Sweeps of a small call are one wave's serial chain, so fewer
+    // ICs per workgroup shorten it and idle CUs take the rest (past one job per CU two jobs would
+    // share it, each as long as a whole block's sweep).  With whole blocks and with four ICs: 300
+    // Venus orbits of 128 nodes 418 and 381 us, 1000 of them 424 and 387, 1000 relativistic ones of
+    // 100 nodes 691 and 584, 512 eccentric ICs of 48 nodes 766 and 631.
+    const bool few_can = few_ok && o.tile_pairs == 0 && o.job_list == 0 && o.path == PC_PATH_FUSED &&
+                         o.precision == PC_FP64 && o.order == 1;
+    if (few_can) {
+        int64_t nj = 0;
+        bool tuned = false;
+        for (int gi = 0; gi < n_groups; ++gi) {
+            nj += (groups[gi].n_ic + 3) / 4;
+            const int np = padded_nodes(groups[gi].nodes);
+            tuned = tuned || np < 32 || ctx->list_table[log2_index(np)] != 0;
+        }
+        plan.few = !tuned && nj <= ctx->n_cu;
+    }
+    plan.pairs = choose_pairs(ctx, groups, n_groups, model, o, plan.few);
     plan.plain = (o.path == PC_PATH_PLAIN);
     if (plan.plain) plan.pairs = 2048;
     {
@@ -594,24 +632,6 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
     for (int k = 0; k < 5; ++k) {
         list_np[k] = list;
         if (lists_ok && o.job_list == 0 && ctx->list_table[k] != 0) list_np[k] = ctx->list_table[k];
-    }
-    // Small calls: jobs of four ICs, which have a body of half the force work (pc_publish), as long
-    // as each job has a CU of its own.  Sweeps of a small call are one wave's serial chain, so fewer
-    // ICs per workgroup shorten it and idle CUs take the rest (past one job per CU two jobs would
-    // share it, each as long as a whole block's sweep).  With whole blocks and with four ICs: 300
-    // Venus orbits of 128 nodes 418 and 381 us, 1000 of them 424 and 387, 1000 relativistic ones of
-    // 100 nodes 691 and 584, 512 eccentric ICs of 48 nodes 766 and 631.
-    const bool few_can = few_ok && o.tile_pairs == 0 && o.job_list == 0 && o.path == PC_PATH_FUSED &&
-                         o.precision == PC_FP64 && o.order == 1;
-    if (few_can) {
-        int64_t nj = 0;
-        bool tuned = false;
-        for (int gi = 0; gi < n_groups; ++gi) {
-            nj += (groups[gi].n_ic + 3) / 4;
-            const int np = padded_nodes(groups[gi].nodes);
-            tuned = tuned || np < 32 || ctx->list_table[log2_index(np)] != 0;
-        }
-        plan.few = !tuned && nj <= ctx->n_cu;
     }
     plan.list = list;
     struct Cost { int np; double c; PcJobDev j; };
@@ -1691,7 +1711,10 @@ int pc_adjoint(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int32_t n_grou
     // call, for the same reason), unless only the shorter job table of the 512-thread ones fits the
     // caller's workspace.  Whole gradient calls with 512- and 256-thread workgroups: 16384 Venus
     // orbits of 128 nodes 11.5 and 10.9 ms, 3494 of 26 nodes 1.60 and 1.25, 12 of 72 nodes 1.45 and
-    // 1.10, 2944 of 78 nodes under the relativistic dynamics 3.91 and 3.78
+    // 1.10, 2944 of 78 nodes under the relativistic dynamics 3.91 and 3.78.  Records that fit the
+    // large shape's LDS only do not change that (the adjoint sweeps read none, only the re-solve
+    // does): pc_adjoint alone, 128 nodes, 9 perturbers, 300, 3000 and 16384 orbits 1.96 and 1.25,
+    // 1.28 and 1.28, 7.81 and 7.61 ms; 16 perturbers 2.16 and 1.42, 1.40 and 1.43, 8.63 and 8.48
     o.tile_pairs = 1024;
     for (int i = 0; groups && i < n_groups; ++i)
         if (groups[i].nodes > 128) o.tile_pairs = 2048;
@@ -1905,9 +1928,9 @@ int pc_autotune(pc_ctx* ctx, const double* ics, int64_t n_ic, const pc_group* gr
     ctx->timing = was_timing;
     int pairs = best_pairs;
     if (pairs == 0) {   // record the shape the untuned rule picked
-        pc_opts d;
-        pc_default_opts(&d);
-        pairs = choose_pairs(ctx, groups, n_groups, d);
+        Plan plan;
+        if ((rc = make_plan(ctx, n_ic, groups, n_groups, model, o, false, plan, true)) != PC_OK) return fail(rc);
+        pairs = plan.pairs;
     }
     ctx->tile_table[kmax] = pairs;
     *chosen_pairs = pairs;

@@ -495,11 +495,10 @@ static __device__ __forceinline__ int pc_unit(int row, int grp, int b, int i)
 }
 
 // Shared-memory arena of one workgroup (sized for the largest job shape).
-// REC: ephemeris kept in LDS, 8 perturbers at the shape's largest node count.  Past the 6T
-// doubles in use, Y0 holds the weights of the job's rows (pc_weights).
+// Past the 6T doubles in use, Y0 holds the weights of the job's rows (pc_weights).
 template <int PAIRS>
 struct PcSmem {
-    static constexpr int REC = PAIRS >= 2048 ? 7040 : 3456;
+    static constexpr int REC = pc_rec_cap(PAIRS);
     alignas(16) double F[6 * PAIRS];
     alignas(16) double Rec[REC];  // [node][body 0..P][3]: perturber positions, then the indirect term
     double Y0[6 * (PAIRS / 16)];  // [comp][IC] initial state of the current segment

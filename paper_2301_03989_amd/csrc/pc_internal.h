@@ -20,6 +20,10 @@
 #define PC_MAX_NP_FOR_HOOK 256   // largest padded node count of the operator hook
 #define PC_MAX_PERT_DEV 16       // perturbers per force evaluation
 
+// Doubles of ephemeris records (3 per node and body, the indirect term one more body) that a
+// workgroup's LDS arena holds: 8 perturbers at the shape's largest node count.
+constexpr int pc_rec_cap(int pairs) { return pairs >= 2048 ? 7040 : 3456; }
+
 struct PcGroupDev {
     double t0, h, tol;         // segment s spans [t0 + (s0 + s) h, t0 + (s0 + s + 1) h]
     int64_t ic_offset, n_ic;
