@@ -188,6 +188,9 @@ __global__ __launch_bounds__(kPlainPairs / 4, 2) void pc_plain_sweep(PcPlainArgs
         }
         any = __syncthreads_or(tid < T ? sActive[tid] : 0);
         open = sOpen;
+    } else {
+        __syncthreads();   // every wave has read the done mark before this workgroup arrives: the last
+                           // workgroup to arrive may set it
     }
     // the last workgroup to arrive compacts the jobs that still hold an iterating IC, in list
     // order, and takes the segment's decision (agent scope: the workgroups run on several XCDs)
