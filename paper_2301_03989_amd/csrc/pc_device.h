@@ -128,6 +128,15 @@ static __device__ __forceinline__ double pc_rsqrt_full(double x)
     return y * fma(e, fma(0.375, e, 0.5), 1.0);
 }
 
+// sqrt(x) and 1/sqrt(x), each rounded about once (one more correction by the residual of each).
+static __device__ __forceinline__ void pc_roots(double x, double& s, double& i)
+{
+    i = pc_rsqrt_full(x);
+    s = x * i;
+    s = fma(0.5 * i, fma(-s, s, x), s);
+    i = fma(i, fma(-s, i, 1.0), i);
+}
+
 // 1/x by the hardware estimate (relative error near 2^-22) and one Newton step (2^-44) or two.
 static __device__ __forceinline__ double pc_rcp1(double x)
 {
@@ -184,10 +193,14 @@ static __device__ __forceinline__ void pc_sincos(double x, double& s, double& c)
 // before it (close to the step) and K = O(1) for e < 0.8, so that leaves an error near 1e-15,
 // usually after the first; the sine and cosine at the final x follow from those of the last
 // step by its second-order Taylor expansion (the dropped cubic term is under 2e-16).
-// The square roots and divisions are the hardware estimates refined to full FP64.
+// The square roots and divisions are the hardware estimates refined to full FP64, the roots to
+// their last place (pc_roots), and 1/n is corrected against n: an ulp of either is multiplied by the
+// angle n dt.  Steps of up to 8 time units, e = 0, 0.3 and 0.6: median error 1.0e-15, 1.0e-15 and
+// 0.9e-15 with IEEE roots and divisions, 1.5e-15, 1.4e-15 and 1.2e-15 without these corrections,
+// 0.9e-15, 1.0e-15 and 0.9e-15 with them (sixteen of 250 instructions).
 // What bounds it is one wave's chain of dependent FP64 instructions: a column refill waits
 // for one solve per lane.  Four FP64 steps from n dt with library sines and IEEE divisions
-// took about 900 instructions, this about 250: 12000 eccentric ICs of 48 nodes and 16 segments
+// took about 900 instructions, this about 250 without them: 12000 eccentric ICs of 48 nodes and 16 segments
 // (a third of the sweeps refill a column) 5.20 -> 5.08 ms, the uneven 65536-IC batch 160.0 ->
 // 157.8 ms (each before the sweeps themselves were shortened).
 // The state goes in and out by value (registers, no stack traffic); a non-elliptic or
@@ -202,17 +215,18 @@ static __device__ __attribute__((noinline)) PcState6 pc_kepler_state(PcState6 s0
     PcState6 out;
     const double r02 = y0[0] * y0[0] + y0[1] * y0[1] + y0[2] * y0[2];
     const double v02 = y0[3] * y0[3] + y0[4] * y0[4] + y0[5] * y0[5];
-    const double ir0 = pc_rsqrt_full(r02);
-    const double r0n = r02 * ir0;
+    double r0n, ir0;
+    pc_roots(r02, r0n, ir0);
     const double alpha = fma(2.0, ir0, -v02);      // 1/a
     if (!(r0n > 0.0) || !isfinite(r0n) || !isfinite(v02) || !(alpha > 0.0)) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) out.c[k] = (double)NAN;
         return out;
     }
-    const double sqa = pc_rsqrt_full(alpha);       // sqrt(a)
-    const double a = sqa * sqa;
-    const double sqal = alpha * sqa;
+    double sqal, sqa;
+    pc_roots(alpha, sqal, sqa);                    // sqa = sqrt(a)
+    double a = sqa * sqa;
+    a = fma(a, fma(-alpha, a, 1.0), a);
     const double n = alpha * sqal;                 // mean motion
     const double sig = y0[0] * y0[3] + y0[1] * y0[4] + y0[2] * y0[5];
     const double ec = fma(-r0n, alpha, 1.0);       // e cos E0
@@ -267,8 +281,11 @@ static __device__ __attribute__((noinline)) PcState6 pc_kepler_state(PcState6 s0
     const double rn = a + (r0n - a) * cx + sig * sqa * sx;
     const double irn = pc_rcp_full(rn);
     const double f = 1.0 - a * ir0 * (1.0 - cx);
-    const double g = dt - (x - sx) * (sqa * a);
-    const double fd = -sqa * sx * (irn * ir0);
+    double in = sqa * a;                           // 1/n
+    in = fma(in, fma(-n, in, 1.0), in);
+    const double g = fma(sx - x, in, dt);
+    const double irr = irn * ir0, fq = -sqa * sx;
+    const double fd0 = fq * irr, fd = fma(fma(-fd0, rn * r0n, fq), irr, fd0);
     const double gd = 1.0 - a * irn * (1.0 - cx);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
