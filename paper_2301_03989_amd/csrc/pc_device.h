@@ -1050,6 +1050,7 @@ static __device__ __forceinline__ void pc_eih_jacobian(double x, double y, doubl
 // make the wave wait for the load it copies right after issuing it.
 // loadB(q, q % 4, buffer) gets the phase as a compile-time constant after unrolling;
 // loadA0(u) supplies the first DK A operands (registers kept across calls, or loads).
+// mma may take the phase as well.
 // SG_DS / SG_MFMA / SG_VMEM > 0 pin the order of one step in the steady-state loop for
 // the scheduler: the B reads of the next step, this step's MFMAs, then the A read DK
 // steps ahead (left to itself, the scheduler sinks the reads below the MFMAs that free
@@ -1069,7 +1070,8 @@ static __device__ __forceinline__ void pc_kloop(int nq, LA0 loadA0, LA loadA, LB
 #pragma unroll
         for (int u = 0; u < DK; ++u) {
             loadB(q0 + u + 1, (u + 1) & 3, bb[(u + 1) & 1]);
-            mma(ka[u], bb[u & 1]);
+            if constexpr (std::is_invocable_v<MM, AT, BT, int>) mma(ka[u], bb[u & 1], u);
+            else mma(ka[u], bb[u & 1]);
             ka[u] = loadA(q0 + u + DK);
             if constexpr (SG_MFMA > 0) {
                 __builtin_amdgcn_sched_group_barrier(0x100, SG_DS, 0);     // DS reads
@@ -1088,7 +1090,8 @@ static __device__ __forceinline__ void pc_kloop(int nq, LA0 loadA0, LA loadA, LB
 #pragma unroll
         for (int u = 0; u < DK; ++u) {   // the last DK steps load nothing past the end
             if (u + 1 < DK) loadB(n - DK + u + 1, (u + 1) & 3, bb[(u + 1) & 1]);
-            mma(ka[u], bb[u & 1]);
+            if constexpr (std::is_invocable_v<MM, AT, BT, int>) mma(ka[u], bb[u & 1], u);
+            else mma(ka[u], bb[u & 1]);
         }
     };
     // a job whose nodes fill every k step keeps the compile-time bound (constant B
@@ -1263,7 +1266,7 @@ struct PcB {
 };
 struct PcBf {
     pc_f2v f[3];
-    float w;
+    double w;
 };
 
 // Lane's base of the k rows 4q + u (u = q % 4): the place of its A-operand row i in F, in
@@ -1317,6 +1320,14 @@ static __device__ __forceinline__ void pc_mm(const double* sF, const double* sWt
 // from FP64 ones rounded here (FP32 Picard sweeps).  The f32 result holds A row 4(l/16) + r in
 // element r, the f64 one row l/16 + 4r: reading IC row i from row i/4 + 4 (i%4) puts the same
 // IC in the same lane and element.
+// Rounding: a row of the operator is now U s + O d, so the early nodes' small integrals are
+// differences of sums as large as the late nodes', and an error of W shifts every node of the second
+// half alike.  W is summed in FP64 (its lanes put back in the f64 product's order), and U s and O d
+// go into two accumulators each (odd and even k steps) that are added in FP64.  32768 Venus orbits,
+// 8 segments, error of the schedule at 64, 128 and 256 nodes (median, 99th percentile, 1e-13):
+// whole operator 6.1 6.9, 6.1 7.0, 6.1 7.2; halves all in FP32 6.1 8.0, 6.2 8.2, 6.0 8.2; this 6.2
+// 7.1, 6.2 7.0, 6.1 6.9, for 3.36 against 3.38, 9.16 against 9.07 and 13.7 against 13.2 ms (the
+// last: 16384 orbits).
 template <int PAIRS, int NP, class V>
 static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, const PcFragF& kp, f64x4 (&acc)[6],
                                                f64x4 (&wd)[3], const PcLane& L)
@@ -1327,10 +1338,10 @@ static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, c
     const v2* f = reinterpret_cast<const v2*>(sF);
     int bp[4];
     pc_kbase<PAIRS, NP>(L, (L.c >> 2) + 4 * (L.c & 3), bp);
-    float ws[3] = {0.0f, 0.0f, 0.0f};
-    f32x4 a[6];
+    double ws[3] = {0.0, 0.0, 0.0};
+    f32x4 a[2][6];
 #pragma unroll
-    for (int b = 0; b < 6; ++b) a[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int b = 0; b < 6; ++b) a[0][b] = a[1][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     pc_kloop<Sh::NQ, pc_f2v, PcBf, Sh::PAR ? 4 : 3, 6, 1>(
         L.nq, [&](int q) { return kp[q]; }, [&](int q) { return kp[q]; },
         [&](int q, int u, PcBf& B) {
@@ -1339,30 +1350,27 @@ static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, c
                 const v2 t = f[bp[u] + q * STEP + 16 * b];
                 B.f[b] = pc_f2v{(float)t.x, (float)t.y};
             }
-            if constexpr (Sh::PAR) B.w = (float)sWt[4 * q + L.g];
+            if constexpr (Sh::PAR) B.w = sWt[4 * q + L.g];
         },
-        [&](const pc_f2v& k, const PcBf& B) {
+        [&](const pc_f2v& k, const PcBf& B, int u) {
 #pragma unroll
-            for (int b = 0; b < 3; ++b) a[b] = mfma16f(B.f[b].x, k.x, a[b]);
+            for (int b = 0; b < 3; ++b) a[u & 1][b] = mfma16f(B.f[b].x, k.x, a[u & 1][b]);
 #pragma unroll
-            for (int b = 0; b < 3; ++b) a[3 + b] = mfma16f(B.f[b].y, k.y, a[3 + b]);
+            for (int b = 0; b < 3; ++b) a[u & 1][3 + b] = mfma16f(B.f[b].y, k.y, a[u & 1][3 + b]);
             if constexpr (Sh::PAR) {
 #pragma unroll
-                for (int b = 0; b < 3; ++b) ws[b] = fmaf(B.w, B.f[b].x, ws[b]);
+                for (int b = 0; b < 3; ++b) ws[b] = fma(B.w, (double)B.f[b].x, ws[b]);
             }
         });
 #pragma unroll
     for (int b = 0; b < 6; ++b) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[b][r] = (double)a[b][r];
+        for (int r = 0; r < 4; ++r) acc[b][r] = (double)a[0][b][r] + (double)a[1][b][r];
     }
     if constexpr (Sh::PAR) {
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const f32x4 t = mfma16f(ws[b], 1.0f, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-#pragma unroll
-            for (int r = 0; r < 4; ++r) wd[b][r] = (double)t[r];
-        }
+        for (int b = 0; b < 3; ++b)
+            wd[b] = mfma16(__shfl(ws[b], 16 * L.g + (L.c >> 2) + 4 * (L.c & 3)), 1.0, f64x4{0.0, 0.0, 0.0, 0.0});
     }
 }
 
