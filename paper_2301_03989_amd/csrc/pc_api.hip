@@ -506,7 +506,8 @@ int choose_pairs(const pc_ctx* ctx, const pc_group* groups, int n_groups, const 
 }
 
 // lists_ok: jobs may hold more ICs than columns (refilled columns; fused FP64 forward calls).
-// A plan without lists has the most jobs, so its workspace size bounds every other plan's.
+// Of the plans of one shape the one without lists has the most jobs, and four-IC jobs more still;
+// a call whose workspace only holds a shorter table falls back to it (propagate_impl).
 // cached_only: take the operators from the context's cache and fail where one is missing
 // (the allocation-free entry point builds none).
 // seg0 (or null): per group, the first segment to run on its t0 + k h grid (refinement
@@ -1598,7 +1599,8 @@ int pc_flyby_ratio(pc_ctx* ctx, const double* ics, int64_t n_ic, const pc_group*
     int rc = validate_model(ctx, model);
     if (rc != PC_OK) return rc;
     PC_HIP(ctx, hipSetDevice(ctx->device));
-    const pc_opts o = defaults();
+    pc_opts o = defaults();
+    o.tile_pairs = 2048;   // the screen reads no jobs: the plan with the shortest table
     Plan plan;
     rc = make_plan(ctx, n_ic, groups, n_groups, model, o, false, plan);
     if (rc != PC_OK) return rc;
