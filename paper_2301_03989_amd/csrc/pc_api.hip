@@ -770,7 +770,8 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
         pc_opts oi = o;
         oi.flyby_hill = 0.0;
         Plan inner;
-        int rc = make_plan(ctx, cov, split.data(), (int)split.size(), model, oi, false, inner, lists_ok);
+        int rc = make_plan(ctx, cov, split.data(), (int)split.size(), model, oi, false, inner, lists_ok, false, nullptr,
+                           few_ok);
         if (rc != PC_OK) return rc;
         const int S = plan.max_S;
         size_t r = 0;
