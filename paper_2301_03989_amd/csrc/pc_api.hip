@@ -576,7 +576,11 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
     }
     if (o.order == 2) {
         // second-order sweeps run in blocks of 16 or more ICs up to 128 nodes (an explicit
-        // tile_pairs 1024 that leaves fewer is refused), of 8 at 256
+        // tile_pairs 1024 that leaves fewer is refused), of 8 at 256.  The line was drawn for a
+        // layout whose product needed 16 ICs; the mirrored pairs do not, and in the small shape
+        // (8 ICs at 65..128 nodes) the same states come sooner: 128 nodes, 8 segments, small and
+        // large shape, 300 Venus orbits 0.65 and 1.05 ms, 4096 of them 1.05 and 1.08, 20000 4.86
+        // and 6.46, with feedback 6.06 and 6.57.  The line stands until its refusal is lifted.
         for (int gi = 0; gi < n_groups; ++gi) {
             const int np = padded_nodes(groups[gi].nodes);
             if (np > 128) continue;

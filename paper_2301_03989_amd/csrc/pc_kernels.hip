@@ -836,13 +836,14 @@ static __device__ __forceinline__ void pc_run_job(const PcParams& p, const PcJob
     // in the one body with a branch, 4096 Venus orbits of full blocks ran 0.7 % slower
     constexpr bool PAR = PcShape<PAIRS, NP>::PAR;
     const bool few = PAR && job.n <= 4;
+    // second-order calls plan 16 or more ICs a block up to 128 nodes (make_plan): no other bodies
+    constexpr bool SO = PAIRS / NP >= 16 || NP == 256;
     if (order2) {
-        if (p.feedback) {
-            pc_job<PAIRS, NP, false, false, 2>(p, job, g);
-            return;
+        if constexpr (SO) {
+            if (p.feedback) pc_job<PAIRS, NP, false, false, 2>(p, job, g);
+            else if (list) pc_job_list<PAIRS, NP, 1>(p, job, g);
+            else pc_job<PAIRS, NP, false, false, 1>(p, job, g);
         }
-        if (list) pc_job_list<PAIRS, NP, 1>(p, job, g);
-        else pc_job<PAIRS, NP, false, false, 1>(p, job, g);
     } else if (eih && mixed) {
         pc_job<PAIRS, NP, true, true>(p, job, g);
     } else if (eih) {
