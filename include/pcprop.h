@@ -88,17 +88,19 @@ typedef struct {
  * nearby initial conditions, which Sec. 2.1 lists as guesses closer to the solution. */
 enum { PC_INIT_KEPLER = 0, PC_INIT_COLD = 1, PC_INIT_GUESS = 2 };
 enum { PC_TOL_REL = 0, PC_TOL_ABS = 1 };         /* relative or absolute stopping rule, Sec. 2.2 */
-/* Arithmetic of the sweeps.  PC_FP32_THEN_FP64 (fused path): every segment starts with
- * an FP32 phase, which ends once the relative change of every iterating IC of the job is
- * below switch_tol (or after max_fp32 FP32 sweeps).  Jobs of 16 or more ICs run one FP64
- * sweep and then increment sweeps, Y <- Y + w2 K_N dF, dF = (dv, G dr) the change of the
+/* Arithmetic of the sweeps.  PC_FP32_THEN_FP64 (fused path): every segment runs an FP32
+ * phase, which ends once the relative change of every iterating IC of the job is below
+ * switch_tol (or after max_fp32 FP32 sweeps).  Jobs whose perturber records fit in LDS
+ * (all but those of many perturbers at many nodes: nodes x (perturbers + 1) up to 2346)
+ * open with FP64 sweeps until no IC changes by more than 1e-3 (one after a warm start) and
+ * then run increment sweeps, Y <- Y + w2 K_N dF, dF = (dv, G dr) the change of the
  * force matrix to first order in the last change (dr, dv) of the iterate, G the gravity
  * gradient at the iterate of the last FP64 sweep: dF, G and the product are FP32 (matrix
  * cores), no force is evaluated, and the sweeps converge at the Picard rate.  At the
  * switch one FP64 sweep re-anchors the iterate on y0 + w2 K_N F(Y); increment sweeps from
  * there carry on until no IC of the job changes by more than tol; FP64 sweeps follow, and
  * each IC stops on the first of them that changes it by less than tol (usually the
- * first).  8-IC jobs run Picard sweeps with an FP32 force and FP32 product, then FP64
+ * first).  The other jobs run Picard sweeps with an FP32 force and FP32 product, then FP64
  * sweeps.  The accumulation into the iterate, the stopping test and all stored states stay
  * FP64.  iters_out counts all sweeps; it is usually one more than the FP64 schedule's,
  * more for ICs whose job holds a slower IC. */
@@ -133,7 +135,7 @@ typedef struct {
                              the call's shapes, options and pointers repeat (default 0) */
     double switch_tol;    /* PC_FP32_THEN_FP64: relative change below which a job leaves FP32
                              (0 = default: 1e-6 for FP32 increment sweeps, 1e-4 for FP32
-                             Picard sweeps of 8-IC jobs).  On a 262144-IC N-body ensemble
+                             Picard sweeps).  On a 262144-IC N-body ensemble
                              1e-5, 1e-6 and 1e-7 ran within 2 % of each other */
     int32_t max_fp32;     /* PC_FP32_THEN_FP64: cap on FP32 sweeps per segment (0 = default 24) */
     int32_t job_list;     /* fused FP64 forward calls: ICs per job in units of its column block
@@ -141,7 +143,9 @@ typedef struct {
                              1024 / padded nodes with tile_pairs 1024); when an IC converges,
                              its column takes the next IC of the job for the same segment.
                              0 = automatic (the longest of 1, 2, 4, 8 whose jobs fill the
-                             workgroup slots within 25 % of the fewest block-times), 1 = off,
+                             workgroup slots within 25 % of the fewest block-times; jobs of
+                             four ICs for first-order calls that have a CU for each, every
+                             group at 17 nodes or more and tile_pairs 0), 1 = off,
                              2, 4 or 8 = that many blocks.  Results do not depend on it. */
     int32_t conv;         /* PC_CONV_PER_IC (default) or PC_CONV_GROUP_MAX */
     int32_t streams;      /* plain path: groups run on this many streams at once (the
@@ -398,7 +402,9 @@ int pc_set_tile_pairs(pc_ctx* ctx, int32_t padded_nodes, int32_t pairs);
 int pc_get_tile_pairs(pc_ctx* ctx, int32_t padded_nodes, int32_t* pairs);
 
 /* Set / read the tuned job length (column blocks per job: 1, 2, 4 or 8; 0 = the untuned
- * rule) for a padded node count, used by fused FP64 calls with job_list = 0. */
+ * rule) for a padded node count, used by fused FP64 calls with job_list = 0, large or
+ * small: a length set for one of its groups also takes the place of a small call's jobs
+ * of four ICs. */
 int pc_set_job_list(pc_ctx* ctx, int32_t padded_nodes, int32_t blocks);
 int pc_get_job_list(pc_ctx* ctx, int32_t padded_nodes, int32_t* blocks);
 

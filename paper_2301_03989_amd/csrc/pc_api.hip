@@ -480,9 +480,9 @@ int choose_pairs(const pc_ctx* ctx, const pc_group* groups, int n_groups, const 
     // untuned default: the 256-thread shape up to 128 padded nodes, where two of its
     // workgroups share a CU and one's sweeps fill the other's waits at barriers, segment
     // starts and refills; both shapes hold mirrored pairs by 8 ICs.  At 128 nodes 4096 Venus
-    // orbits take 1.49 ms against 1.52 with 512-thread workgroups, 12000 eccentric ICs in
-    // refilled columns 5.72 against 6.03; at 64 nodes about 9 %.  A 256-node block of 8 ICs
-    // needs all 512 threads.
+    // orbits (8 segments) take 1.45 ms against 1.48 with 512-thread workgroups, 12000 eccentric
+    // ICs in refilled columns (16 segments) 8.24 against 9.22; at 64 nodes the latter 4.74
+    // against 4.98.  A 256-node block of 8 ICs needs all 512 threads.
     if (np_max > 128) return 2048;
     // With more than 8 perturbers near 128 nodes the records fit the large shape's LDS only; in
     // the small one every sweep reads them from memory.  Small and large shape at 128 nodes, 9 and
@@ -552,8 +552,11 @@ int make_plan(pc_ctx* ctx, int64_t n_ic, const pc_group* groups, int n_groups, c
     // as each job has a CU of its own.  Sweeps of a small call are one wave's serial chain, so fewer
     // ICs per workgroup shorten it and idle CUs take the rest (past one job per CU two jobs would
     // share it, each as long as a whole block's sweep).  With whole blocks and with four ICs: 300
-    // Venus orbits of 128 nodes 418 and 381 us, 1000 of them 424 and 387, 1000 relativistic ones of
-    // 100 nodes 691 and 584, 512 eccentric ICs of 48 nodes 766 and 631.
+    // Venus orbits of 128 nodes and 2 segments 278 and 260 us, 1000 of them 283 and 270, 1000
+    // relativistic ones of 100 nodes 459 and 394, 512 eccentric ICs of 48 nodes and 4 segments 432
+    // and 361.
+    // A job length set for one of the call's node counts (pc_set_job_list, pc_autotune) is the
+    // caller's choice and stands; at 16 nodes a wave holds 16 ICs and there is no such body.
     const bool few_can = few_ok && o.tile_pairs == 0 && o.job_list == 0 && o.path == PC_PATH_FUSED &&
                          o.precision == PC_FP64 && o.order == 1;
     if (few_can) {

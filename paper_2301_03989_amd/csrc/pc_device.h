@@ -891,8 +891,8 @@ static __device__ __forceinline__ double4 pc_eih_load(const PcEihRecs& E, int k,
 // k = m3 d.(4 v - 3 v_b) / 4,
 //   a = -N + [ (4 Phi - v^2) N + 4 v sum k + sum (m3 s d - 4 k v_b + 7/2 mu_b a_b / rho) ] / c^2,
 // one pass over the bodies and 48 FP64 instructions per body and point (22 for the central
-// body, whose v_b and a_b are zero); the terms one by one took 65 and the node's pass bounds
-// a relativistic sweep: eih_figures.
+// body, whose v_b and a_b are zero); the terms one by one took 65.  This force is about half of a
+// relativistic sweep at 200 nodes: 13509 ICs 7.29 -> 6.17 ms.
 // e: the segment's records, slot k of node j at e[k ns + j].
 template <int R>
 static __device__ __forceinline__ void pc_force_eih(const double (&x)[R], const double (&y)[R],
@@ -1323,11 +1323,11 @@ static __device__ __forceinline__ void pc_mm(const double* sF, const double* sWt
 // Rounding: a row of the operator is now U s + O d, so the early nodes' small integrals are
 // differences of sums as large as the late nodes', and an error of W shifts every node of the second
 // half alike.  W is summed in FP64 (its lanes put back in the f64 product's order), and U s and O d
-// go into two accumulators each (odd and even k steps) that are added in FP64.  32768 Venus orbits,
-// 8 segments, error of the schedule at 64, 128 and 256 nodes (median, 99th percentile, 1e-13):
-// whole operator 6.1 6.9, 6.1 7.0, 6.1 7.2; halves all in FP32 6.1 8.0, 6.2 8.2, 6.0 8.2; this 6.2
-// 7.1, 6.2 7.0, 6.1 6.9, for 3.36 against 3.38, 9.16 against 9.07 and 13.7 against 13.2 ms (the
-// last: 16384 orbits).
+// go into two accumulators each (odd and even k steps) that are added in FP64.  Venus orbits, 8
+// segments, error of the schedule at 64, 128 (262144 of them) and 200 nodes (32768), median and 99th
+// percentile in 1e-13: whole operator 6.1 6.9, 6.1 7.0, 6.1 7.1; halves all in FP32 6.1 8.1, 6.2
+// 8.2, 5.9 8.1; this 6.2 7.1, 6.2 7.0, 6.2 6.9.  It takes 25.7, 70.4 and 25.3 ms, all in FP32 25.6,
+// 67.3 and 24.3, the whole operator 31.1, 96.8 and 42.1.
 template <int PAIRS, int NP, class V>
 static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, const PcFragF& kp, f64x4 (&acc)[6],
                                                f64x4 (&wd)[3], const PcLane& L)

@@ -8,9 +8,9 @@
 // the whole propagation of those ICs on chip: for every segment it builds the initial
 // guess, then repeats {force at all nodes (FP64 VALU), y_new = y0 + w2 K_N F (FP64 MFMA
 // 16x16x4), per-IC error and stopping decision} until each IC has converged, chains the
-// last node into the next segment and finally writes the end states.  The iterate and
-// the force matrix never leave LDS, so HBM traffic is only the initial states, the
-// ephemeris records and the results; K_N fragments are re-read from L2.
+// last node into the next segment and finally writes the end states.  The iterate stays
+// in registers and the force matrix in LDS, so HBM traffic is the initial states, the
+// ephemeris records, the results and what the bodies spill; K_N fragments are re-read from L2.
 #include "pc_device.h"
 
 // ---------------------------------------------------------------------------

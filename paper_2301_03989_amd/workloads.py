@@ -231,7 +231,7 @@ def mixed_precision(n_ic: int = 262144, seed: int = 104) -> Workload:
 
 def adjoint_ensemble(n_ic: int = 16384, seed: int = 105, nodes: int = 128, eih: bool = False) -> Workload:
     """The N-body Venus ensemble at 16384 ICs over 256 days in 5 segments, tol 1e-13
-    (128 nodes; the 256-node variant runs the adjoint's node-row jobs; eih: with the
+    (128 nodes; the 256-node variant runs the adjoint's 512-thread jobs; eih: with the
     relativistic dynamics at the physical 1/c^2)."""
     w = nbody_venus(n_ic, seed, days=256.0, segments=5, tol=1e-13, nodes=nodes,
                     name="nbody-venus-16384-256d" + ("" if nodes == 128 else f"-n{nodes}") + ("-eih" if eih else ""))
