@@ -1339,9 +1339,10 @@ static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, c
     int bp[4];
     pc_kbase<PAIRS, NP>(L, (L.c >> 2) + 4 * (L.c & 3), bp);
     double ws[3] = {0.0, 0.0, 0.0};
-    f32x4 a[2][6];
+    constexpr int NA = Sh::PAR ? 2 : 1;   // at 16 padded nodes the operator is whole
+    f32x4 a[NA][6];
 #pragma unroll
-    for (int b = 0; b < 6; ++b) a[0][b] = a[1][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int b = 0; b < 6; ++b) a[0][b] = a[NA - 1][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     pc_kloop<Sh::NQ, pc_f2v, PcBf, Sh::PAR ? 4 : 3, 6, 1>(
         L.nq, [&](int q) { return kp[q]; }, [&](int q) { return kp[q]; },
         [&](int q, int u, PcBf& B) {
@@ -1354,9 +1355,9 @@ static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, c
         },
         [&](const pc_f2v& k, const PcBf& B, int u) {
 #pragma unroll
-            for (int b = 0; b < 3; ++b) a[u & 1][b] = mfma16f(B.f[b].x, k.x, a[u & 1][b]);
+            for (int b = 0; b < 3; ++b) a[u % NA][b] = mfma16f(B.f[b].x, k.x, a[u % NA][b]);
 #pragma unroll
-            for (int b = 0; b < 3; ++b) a[u & 1][3 + b] = mfma16f(B.f[b].y, k.y, a[u & 1][3 + b]);
+            for (int b = 0; b < 3; ++b) a[u % NA][3 + b] = mfma16f(B.f[b].y, k.y, a[u % NA][3 + b]);
             if constexpr (Sh::PAR) {
 #pragma unroll
                 for (int b = 0; b < 3; ++b) ws[b] = fma(B.w, (double)B.f[b].x, ws[b]);
@@ -1365,7 +1366,7 @@ static __device__ __forceinline__ void pc_mm32(const V* sF, const double* sWt, c
 #pragma unroll
     for (int b = 0; b < 6; ++b) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[b][r] = (double)a[0][b][r] + (double)a[1][b][r];
+        for (int r = 0; r < 4; ++r) acc[b][r] = Sh::PAR ? (double)a[0][b][r] + (double)a[NA - 1][b][r] : (double)a[0][b][r];
     }
     if constexpr (Sh::PAR) {
 #pragma unroll
